@@ -180,17 +180,15 @@ __device__ void fast_givens(const double *r, double *out, bool form0 = false) {
   out[3] = 0.0;
 }
 
-// Coefficients of one descriptor, written at coef + cd.dst.
+// Coefficients of one descriptor that is no product of factors (CF_TABLE,
+// CF_SCALE), written at coef + cd.dst.
 __device__ void build_coef(const CoefDesc &cd, const double *params, const double *statics,
                            const TabFactor *fac, double *coef) {
   const int fmt = cd.fmt & 0xff;
   const bool dag = (cd.fmt & CF_DAGGER) != 0;
   const bool f0 = (cd.fmt & CF_FORM0) != 0;
   double th[3] = {0, 0, 0};
-  // pidx holds parameter indices except for the table / scale formats,
-  // where pidx[0] counts factors
-  const bool takes_params = fmt != CF_TABLE && fmt != CF_SCALE && fmt != CF_COPY &&
-                            fmt != CF_IDENT2 && fmt != CF_CONSTS;
+  const bool takes_params = fmt != CF_COPY && fmt != CF_IDENT2 && fmt != CF_CONSTS;
   if (takes_params)
     for (int k = 0; k < 3; k++)
       if (cd.pidx[k] >= 0) th[k] = params[cd.pidx[k]];
@@ -203,51 +201,8 @@ __device__ void build_coef(const CoefDesc &cd, const double *params, const doubl
     double r[4] = {m[0], m[2], m[4], m[6]};   // real 2x2
     if (dag) { const double t = r[1]; r[1] = r[2]; r[2] = t; }
     fast_givens(r, out, f0);
-  } else if (fmt == CF_SCALE) {
-    // product of the fast-Givens scales of the (daggered, if flagged) real gates
-    double sc = 1.0;
-    for (int f = cd.src; f < cd.src + cd.pidx[0]; f++) {
-      const TabFactor tf = fac[f];
-      double m[8], rec[4];
-      double tt[3] = {tf.pidx >= 0 ? params[tf.pidx] : 0.0, 0.0, 0.0};
-      gate_local(tf.kind, tt, m);
-      double r[4] = {m[0], m[2], m[4], m[6]};
-      if (dag) { const double t = r[1]; r[1] = r[2]; r[2] = t; }
-      fast_givens(r, rec, f0);
-      sc *= rec[2];
-    }
-    out[0] = sc;
   } else if (fmt == CF_IDENT2) {
     out[0] = 1.0; out[1] = 0.0; out[2] = 0.0; out[3] = 1.0;
-  } else if (fmt == CF_TABLE) {
-    const int G = 1 << cd.len;
-    for (int j = 0; j < G; j++) { out[2 * j] = 1.0; out[2 * j + 1] = 0.0; }
-    for (int f = cd.src; f < cd.src + cd.pidx[0]; f++) {
-      const TabFactor tf = fac[f];
-      double m[8];
-      double tt[3] = {tf.pidx >= 0 ? params[tf.pidx] : 0.0, 0.0, 0.0};
-      gate_local(tf.kind, tt, m);
-      double gsc = 1.0;
-      if (tf.neg == 2) {
-        double r[4] = {m[0], m[2], m[4], m[6]}, rec[4];
-        if (dag) { const double t = r[1]; r[1] = r[2]; r[2] = t; }
-        fast_givens(r, rec, f0);
-        gsc = rec[2];
-      }
-      for (int j = 0; j < G; j++) {
-        if (((uint32_t)j & tf.cm) != tf.cv) continue;
-        double dr, di;
-        if (tf.neg == 2) { dr = gsc; di = 0.0; }
-        else if (tf.neg) { dr = -1.0; di = 0.0; }
-        else if (__builtin_popcount((uint32_t)j & tf.mask) & 1) { dr = m[6]; di = m[7]; }
-        else { dr = m[0]; di = m[1]; }
-        const double xr = out[2 * j], xi = out[2 * j + 1];
-        out[2 * j] = xr * dr - xi * di;
-        out[2 * j + 1] = xr * di + xi * dr;
-      }
-    }
-    if (dag)
-      for (int j = 0; j < G; j++) out[2 * j + 1] = -out[2 * j + 1];
   } else if (fmt == CF_U2X2 || fmt == CF_R2X2 || fmt == CF_DIAG) {
     double m[8];
     gate_local(cd.kind, th, m);
@@ -320,10 +275,96 @@ __device__ void build_coef(const CoefDesc &cd, const double *params, const doubl
   }
 }
 
-__global__ void k_build_coefs(const CoefDesc *d, int nd, const double *params, const double *statics,
-                              const TabFactor *fac, double *coef) {
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nd; i += gridDim.x * blockDim.x)
-    build_coef(d[i], params, statics, fac, coef);
+// Coefficients of descriptor cd by a group of COEF_LANES consecutive lanes (l:
+// this lane's place in the group; every lane of the group calls it with the
+// same descriptor).  A table's or scale's factors are evaluated one per lane
+// and handed round, and each lane multiplies its own entries, in factor
+// order; the other formats are built by the group's first lane.  Latency-bound:
+// one thread per descriptor, which walked factors times entries through
+// memory, took 17 us (12-qubit layered circuit, 3-qubit tables) to 89 us
+// (complex64, 28 qubits, 5-qubit tables); 12-qubit pass 207 -> 200 us,
+// 20-qubit adjoint 1055 -> 1020 us.
+constexpr int COEF_LANES = 8;
+
+__device__ void build_coef_group(const CoefDesc &cd, const double *params, const double *statics,
+                                 const TabFactor *fac, double *coef, int l) {
+  const int fmt = cd.fmt & 0xff;
+  const bool table = fmt == CF_TABLE;
+  if (!table && fmt != CF_SCALE) {
+    if (l == 0) build_coef(cd, params, statics, fac, coef);
+    return;
+  }
+  const bool dag = (cd.fmt & CF_DAGGER) != 0;
+  const bool f0 = (cd.fmt & CF_FORM0) != 0;
+  const int nf = cd.pidx[0];                    // number of factors
+  const int G = table ? 1 << cd.len : 1;        // entries (CF_SCALE: the product alone)
+  constexpr int EPL = SVI_GMAX / COEF_LANES;    // entries per lane: l, l + COEF_LANES, ...
+  double xr[EPL], xi[EPL];
+#pragma unroll
+  for (int e = 0; e < EPL; e++) {
+    xr[e] = 1.0;
+    xi[e] = 0.0;
+  }
+  for (int f1 = 0; f1 < nf; f1 += COEF_LANES) {
+    // this lane's factor: the diagonal (d0, d1), or a real scale in both
+    double d0r = 1.0, d0i = 0.0, d1r = 1.0, d1i = 0.0;
+    uint32_t mask = 0, cm = 0, cv = 0;
+    if (f1 + l < nf) {
+      const TabFactor tf = fac[cd.src + f1 + l];
+      mask = tf.mask;
+      cm = tf.cm;
+      cv = tf.cv;
+      double m[8];
+      double tt[3] = {tf.pidx >= 0 ? params[tf.pidx] : 0.0, 0.0, 0.0};
+      gate_local(tf.kind, tt, m);
+      if (!table || tf.neg == 2) {
+        double r[4] = {m[0], m[2], m[4], m[6]}, rec[4];   // real 2x2
+        if (dag) { const double t = r[1]; r[1] = r[2]; r[2] = t; }
+        fast_givens(r, rec, f0);
+        d0r = d1r = rec[2];
+      } else if (tf.neg) {
+        d0r = d1r = -1.0;
+      } else {
+        d0r = m[0]; d0i = m[1]; d1r = m[6]; d1i = m[7];
+      }
+    }
+    const int cnt = nf - f1 < COEF_LANES ? nf - f1 : COEF_LANES;
+    for (int f = 0; f < cnt; f++) {
+      const double a0r = __shfl(d0r, f, COEF_LANES), a0i = __shfl(d0i, f, COEF_LANES);
+      const double a1r = __shfl(d1r, f, COEF_LANES), a1i = __shfl(d1i, f, COEF_LANES);
+      const uint32_t mk = __shfl(mask, f, COEF_LANES), fm = __shfl(cm, f, COEF_LANES),
+                     fv = __shfl(cv, f, COEF_LANES);
+#pragma unroll
+      for (int e = 0; e < EPL; e++) {
+        const uint32_t j = (uint32_t)(l + e * COEF_LANES);
+        if ((j & fm) != fv) continue;
+        const bool odd = __builtin_popcount(j & mk) & 1;
+        const double dr = odd ? a1r : a0r, di = odd ? a1i : a0i;
+        const double yr = xr[e], yi = xi[e];
+        xr[e] = yr * dr - yi * di;
+        xi[e] = yr * di + yi * dr;
+      }
+    }
+  }
+  double *out = coef + cd.dst;
+#pragma unroll
+  for (int e = 0; e < EPL; e++) {
+    const int j = l + e * COEF_LANES;
+    if (j >= G) continue;
+    if (table) {
+      out[2 * j] = xr[e];
+      out[2 * j + 1] = dag ? -xi[e] : xi[e];
+    } else {
+      out[0] = xr[e];
+    }
+  }
+}
+
+__global__ void __launch_bounds__(256) k_build_coefs(const CoefDesc *d, int nd, const double *params,
+                                                     const double *statics, const TabFactor *fac,
+                                                     double *coef) {
+  const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x) / COEF_LANES;
+  if (i < nd) build_coef_group(d[i], params, statics, fac, coef, threadIdx.x % COEF_LANES);
 }
 
 // --------------------------------------------------- Pauli tile pass
@@ -1508,8 +1549,9 @@ hipError_t svk_launch_init_zero(int dbl, void *re, void *im, int64_t n, hipStrea
 hipError_t svk_launch_coefs(const CoefDesc *d, int nd, const double *params, const double *statics,
                             const TabFactor *fac, double *coef, hipStream_t s) {
   if (nd <= 0) return hipSuccess;
-  int grid = (nd + 127) / 128;
-  hipLaunchKernelGGL(k_build_coefs, dim3(grid), dim3(128), 0, s, d, nd, params, statics, fac, coef);
+  const int per = 256 / COEF_LANES;   // descriptors per block
+  hipLaunchKernelGGL(k_build_coefs, dim3((nd + per - 1) / per), dim3(256), 0, s, d, nd, params,
+                     statics, fac, coef);
   return hipGetLastError();
 }
 
@@ -1851,9 +1893,10 @@ namespace {
 __global__ void __launch_bounds__(256) k_serve_coefs(const ServeReq *reqs) {
   const ServeReq &q = reqs[blockIdx.y];
   const int nd = q.f_ndesc + q.b_ndesc;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < nd; i += gridDim.x * blockDim.x) {
-    if (i < q.f_ndesc) build_coef(q.f_desc[i], q.f_params, nullptr, q.f_fac, q.f_coef);
-    else build_coef(q.b_desc[i - q.f_ndesc], q.b_params, nullptr, q.b_fac, q.b_coef);
+  const int l = threadIdx.x % COEF_LANES, step = (int)(gridDim.x * blockDim.x) / COEF_LANES;
+  for (int i = (int)(blockIdx.x * blockDim.x + threadIdx.x) / COEF_LANES; i < nd; i += step) {
+    if (i < q.f_ndesc) build_coef_group(q.f_desc[i], q.f_params, nullptr, q.f_fac, q.f_coef, l);
+    else build_coef_group(q.b_desc[i - q.f_ndesc], q.b_params, nullptr, q.b_fac, q.b_coef, l);
   }
 }
 
@@ -2001,7 +2044,8 @@ int svk_serve_max_qubits() { return 16; }
 
 hipError_t svk_launch_serve_coefs(const ServeReq *d_reqs, int nreq, int max_desc, hipStream_t s) {
   if (nreq <= 0) return hipSuccess;
-  const int bx = max_desc > 0 ? (max_desc + 255) / 256 : 1;
+  const int per = 256 / COEF_LANES;   // descriptors per block and round
+  const int bx = max_desc > 0 ? (max_desc + per - 1) / per : 1;
   hipLaunchKernelGGL(k_serve_coefs, dim3(bx < 64 ? bx : 64, nreq), dim3(256), 0, s, d_reqs);
   return hipGetLastError();
 }
