@@ -85,20 +85,26 @@ __device__ __forceinline__ MicroOp op_at(const MicroOp *ops, int o) {
   return m;
 }
 
-// Tile-local base index of thread tid in a stage: thread-index bit k placed
-// on tile bit tpos[k] (the group bits stay zero).
-template <int M, int R>
-__device__ __forceinline__ int stage_base(int tid, const SVI_CONST StageDesc &sd) {
-  // tpos read as aligned 32-bit words (scalar loads; byte loads of the
-  // descriptor would become vector loads, whose waits also wait for the
-  // tile prefetch in flight), bytes extracted with scalar shifts
+// Tile-local base index of a thread in a stage: thread-index bit k placed on
+// tile bit tpos[k] (the group bits stay zero), as the lane's part (k < 6) and
+// the wave's, which is uniform: scalar work.  tpos is read as aligned 32-bit
+// words (scalar loads; byte loads of the descriptor would become vector loads,
+// whose waits also wait for the tile prefetch in flight).
+__device__ __forceinline__ int lane_base(int lane, const SVI_CONST StageDesc &sd) {
   const SVI_CONST int32_t *w = (const SVI_CONST int32_t *)sd.tpos;
   int b = 0;
 #pragma unroll
-  for (int k = 0; k < M - R; k++) {
-    const int pos = (w[k >> 2] >> (8 * (k & 3))) & 0xff;
-    b |= ((tid >> k) & 1) << pos;
-  }
+  for (int k = 0; k < 6; k++) b |= ((lane >> k) & 1) << ((w[k >> 2] >> (8 * (k & 3))) & 0xff);
+  return b;
+}
+
+template <int M, int R>
+__device__ __forceinline__ int wave_base(int wave, const SVI_CONST StageDesc &sd) {
+  const SVI_CONST int32_t *w = (const SVI_CONST int32_t *)sd.tpos;
+  int b = 0;
+#pragma unroll
+  for (int k = 6; k < M - R; k++)
+    b |= ((wave >> (k - 6)) & 1) << ((w[k >> 2] >> (8 * (k & 3))) & 0xff);
   return b;
 }
 
@@ -670,6 +676,7 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep(SweepArgs a) {
   __shared__ int32_t hb_s[SVI_MMAX];
 
   const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = a.m, c = a.c, nh = a.nh;
   const int mm = m > R ? m : R;              // tile bits including phantom padding
   const int ntile_el = 1 << m;               // real amplitudes per tile
@@ -749,14 +756,15 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep(SweepArgs a) {
       // beyond the tile's groups work on LDS slots above 2^mm, which are
       // never written back.
       const bool active = tid < ngroups;
-      const int gbs = swz<T>(stage_base<M, R>(tid, sd)) * (int)sizeof(C2);
+      const int gbs =
+          (swz<T>(lane_base(tid & 63, sd)) ^ swz<T>(wave_base<M, R>(wave, sd))) * (int)sizeof(C2);
       T re[NS][G], im[NS][G];
 #pragma unroll
       for (int s = 0; s < NS; s++) {
         const char *lb = (const char *)lds[s];
 #pragma unroll
         for (int j = 0; j < G; j++) {
-          const C2 v = *(const C2 *)(lb + (gbs ^ sd.ld_off[j]));
+          const C2 v = *(const C2 *)(lb + (gbs ^ sd.off[j]));
           re[s][j] = v.x;
           im[s][j] = v.y;
         }
@@ -810,7 +818,7 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep(SweepArgs a) {
       for (int s = 0; s < NS; s++) {
         char *lb = (char *)lds[s];
 #pragma unroll
-        for (int j = 0; j < G; j++) *(C2 *)(lb + (gbs ^ sd.st_off[j])) = C2{re[s][j], im[s][j]};
+        for (int j = 0; j < G; j++) *(C2 *)(lb + (gbs ^ sd.off[G + j])) = C2{re[s][j], im[s][j]};
       }
       __syncthreads();
     }
@@ -894,9 +902,13 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron(SweepArgs a) {
   constexpr int G = 1 << R;
   using C2 = typename C2T<T>::type;
   // Per-stage thread bases (tile-local slot offset of the thread's register
-  // group) depend on the thread and the stage, not on the tile: the first
-  // GTAB stages take theirs from a table built once per launch in the LDS
-  // the tile leaves free (sized so the workgroups per CU stay as they are).
+  // group) depend on the thread and the stage, not on the tile: a workgroup
+  // that runs several tiles takes those of the first GTAB stages from a table
+  // built once per launch in the LDS the tile leaves free (sized so the
+  // workgroups per CU stay as they are).  One that runs a single tile forms
+  // them as it goes: building the table cost it 3 us a launch (21 qubits, 11
+  // sweeps: 619 -> 588 us a pass), while forming them in every tile costs the
+  // large states 2% (30 qubits: 202 -> 207 ms).
   constexpr int TILE_BYTES = (1 << M) * (int)sizeof(C2);
   constexpr int GTAB_BYTES = TILE_BYTES >= 131072 ? 30720 : TILE_BYTES >= 65536 ? 14336 : 6144;
   constexpr int GTAB = GTAB_BYTES / (2 * NT) > 0 ? GTAB_BYTES / (2 * NT) : 1;
@@ -904,7 +916,8 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron(SweepArgs a) {
   __shared__ int32_t hb_s[SVI_MMAX];
   __shared__ uint16_t gtab[GTAB * NT];   // swizzled element index (tiles hold <= 2^14)
 
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = a.m, c = a.c, nh = a.nh;
   const int ntile_el = 1 << m;
   const bool init0 = (a.flags & SW_INIT_ZERO) != 0;
@@ -913,9 +926,14 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron(SweepArgs a) {
   const SVI_CONST double *coef = cptr(a.coef);
 
   if (tid < SVI_MMAX) hb_s[tid] = a.hb[tid < nh ? tid : 0];
-  const int ntab = nst < GTAB ? nst : GTAB;
+  auto base_of = [&](int st) {
+    return swz<T>(lane_base(lane, stages[st])) ^ swz<T>(wave_base<M, R>(wave, stages[st]));
+  };
+  const int ntab = a.ntiles <= gridDim.x ? 0 : nst < GTAB ? nst : GTAB;
   for (int st = 0; st < ntab; st++)   // each thread reads back only its own entries
-    gtab[st * NT + tid] = (uint16_t)swz<T>(stage_base<M, R>(tid, stages[st]));
+    gtab[st * NT + tid] = (uint16_t)base_of(st);
+  // waves whose threads hold no part of a small state (m < M) have no group
+  const bool on = wave * 64 < (m > R ? 1 << (m - R) : 1);
   __syncthreads();
 
   // Lane tid moves tile elements i = tid + k * NT (k < G) between HBM and
@@ -1045,8 +1063,7 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron(SweepArgs a) {
       // ---- stages
       for (int st = 0; live && st < nst; st++) {
         const SVI_CONST StageDesc &sd = stages[st];
-        const int gbs =
-            (st < ntab ? (int)gtab[st * NT + tid] : swz<T>(stage_base<M, R>(tid, sd))) * (int)sizeof(C2);
+        const int gbs = (st < ntab ? (int)gtab[st * NT + tid] : base_of(st)) * (int)sizeof(C2);
         // The common stage (every group bit rotated, then D_after) runs as its
         // own straight-line body from loads to stores; the general body
         // branches on the stage's parts.  Separate bodies leave nothing to
@@ -1055,7 +1072,7 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron(SweepArgs a) {
           T re[G], im[G];
 #pragma unroll
           for (int j = 0; j < G; j++) {
-            const C2 v = *(const C2 *)(lb + (gbs ^ sd.ld_off[j]));
+            const C2 v = *(const C2 *)(lb + (gbs ^ sd.off[j]));
             re[j] = v.x;
             im[j] = v.y;
           }
@@ -1067,12 +1084,15 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron(SweepArgs a) {
           }
           if (sd.dflags & SD_XCHG) lds_barrier();
 #pragma unroll
-          for (int j = 0; j < G; j++) *(C2 *)(lb + (gbs ^ sd.st_off[j])) = C2{re[j], im[j]};
+          for (int j = 0; j < G; j++) *(C2 *)(lb + (gbs ^ sd.off[G + j])) = C2{re[j], im[j]};
         };
-        if (sd.rmask == (1u << R) - 1 && (sd.dflags & 7) == 2)
+        if (!FULL && !on) {
+          if (sd.dflags & SD_XCHG) lds_barrier();
+        } else if (sd.rmask == (1u << R) - 1 && (sd.dflags & 7) == 2) {
           body(std::true_type{});
-        else
+        } else {
           body(std::false_type{});
+        }
         if (sd.dflags & SD_WLOCAL) {
           // the next stage reads only slots this wave wrote: keep the wave's
           // LDS accesses in order, no workgroup barrier
@@ -1153,6 +1173,7 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
   using C2 = typename C2T<T>::type;
   using V4 = typename V4T<T>::type;
   const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = a.m, c = a.c, nh = a.nh;
   const int mm = m > R ? m : R;
   const int ntile_el = 1 << m;
@@ -1254,14 +1275,15 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
 
     for (int st = st_begin; st < st_end; st++) {
       const SVI_CONST StageDesc &sd = stages[st];
-      const int gbs = swz<T>(stage_base<M, R>(tid, sd)) * (int)sizeof(C2);
+      const int gbs =
+          (swz<T>(lane_base(tid & 63, sd)) ^ swz<T>(wave_base<M, R>(wave, sd))) * (int)sizeof(C2);
       // a full Kronecker stage (every group bit rotated, then D_after) runs as
       // its own straight-line body, loads to stores; the general body branches
       auto body = [&](auto full_stage) {
         T re[G], im[G];
 #pragma unroll
         for (int j = 0; j < G; j++) {
-          const C2 v = *(const C2 *)(lb + (gbs ^ sd.ld_off[j]));
+          const C2 v = *(const C2 *)(lb + (gbs ^ sd.off[j]));
           re[j] = v.x;
           im[j] = v.y;
         }
@@ -1278,7 +1300,7 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
         }
         if (sd.dflags & SD_XCHG) __syncthreads();
 #pragma unroll
-        for (int j = 0; j < G; j++) *(C2 *)(lb + (gbs ^ sd.st_off[j])) = C2{re[j], im[j]};
+        for (int j = 0; j < G; j++) *(C2 *)(lb + (gbs ^ sd.off[G + j])) = C2{re[j], im[j]};
       };
       if (sd.kind == ST_KRON && sd.rmask == (1u << R) - 1 && (sd.dflags & 7) == 2)
         body(std::true_type{});
@@ -1344,7 +1366,7 @@ __device__ __forceinline__ void kron2_stage(char *lb0, char *lb1, int gbs,
   for (int s = 0; s < 2; s++) {
 #pragma unroll
     for (int j = 0; j < G; j++) {
-      const C2 v = *(const C2 *)(lb[s] + (gbs ^ sd.ld_off[j]));
+      const C2 v = *(const C2 *)(lb[s] + (gbs ^ sd.off[j]));
       re[s][j] = v.x;
       im[s][j] = v.y;
     }
@@ -1411,7 +1433,7 @@ __device__ __forceinline__ void kron2_stage(char *lb0, char *lb1, int gbs,
 #pragma unroll
   for (int s = 0; s < 2; s++) {
 #pragma unroll
-    for (int j = 0; j < G; j++) *(C2 *)(lb[s] + (gbs ^ sd.st_off[j])) = C2{re[s][j], im[s][j]};
+    for (int j = 0; j < G; j++) *(C2 *)(lb[s] + (gbs ^ sd.off[G + j])) = C2{re[s][j], im[s][j]};
   }
   if (sd.dflags & SD_WLOCAL) {
     // the next stage reads only slots this wave wrote
@@ -1440,7 +1462,7 @@ __device__ __forceinline__ void ops2_stage(char *lb0, char *lb1, int gbs,
   for (int s = 0; s < 2; s++) {
 #pragma unroll
     for (int j = 0; j < G; j++) {
-      const C2 v = *(const C2 *)(lb[s] + (gbs ^ sd.ld_off[j]));
+      const C2 v = *(const C2 *)(lb[s] + (gbs ^ sd.off[j]));
       re[s][j] = v.x;
       im[s][j] = v.y;
     }
@@ -1459,7 +1481,7 @@ __device__ __forceinline__ void ops2_stage(char *lb0, char *lb1, int gbs,
 #pragma unroll
   for (int s = 0; s < 2; s++) {
 #pragma unroll
-    for (int j = 0; j < G; j++) *(C2 *)(lb[s] + (gbs ^ sd.st_off[j])) = C2{re[s][j], im[s][j]};
+    for (int j = 0; j < G; j++) *(C2 *)(lb[s] + (gbs ^ sd.off[G + j])) = C2{re[s][j], im[s][j]};
   }
   lds_barrier();
 }
@@ -1478,20 +1500,21 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron2(SweepArgs a) {
   constexpr int NWAVE = NT / 64;
   using C2 = typename C2T<T>::type;
   using V4 = typename V4T<T>::type;
-  // per-stage thread bases from a table built once per launch (as in
-  // k_sweep_kron), in the LDS left by the tiles and the per-wave sums within
-  // the workgroup's share of the CU (one workgroup per CU for 128 KiB of
-  // tiles, two for 64 KiB)
+  // the lane parts of the stages' thread bases from a table built once per
+  // launch (as in k_sweep_kron), in the LDS left by the tiles and the per-wave
+  // sums within the workgroup's share of the CU (one workgroup per CU for
+  // 128 KiB of tiles, two for 64 KiB)
   constexpr int TILE_BYTES = 2 * (1 << M) * (int)sizeof(C2);
   constexpr int WG_LDS = TILE_BYTES >= 131072 ? 163840 : TILE_BYTES >= 65536 ? 81920 : 40960;
-  constexpr int GTAB_BYTES = WG_LDS - TILE_BYTES - NWAVE * SVI_GSLOTS_WIDE * 8 - 4 * SVI_MMAX - 256;
-  constexpr int GTAB = GTAB_BYTES / (4 * NT) > 0 ? GTAB_BYTES / (4 * NT) : 1;
+  constexpr int LTAB_BYTES = WG_LDS - TILE_BYTES - NWAVE * SVI_GSLOTS_WIDE * 8 - 4 * SVI_MMAX - 256;
+  constexpr int LTAB = LTAB_BYTES / 128 > 0 ? LTAB_BYTES / 128 : 1;
   __shared__ C2 lds[2][1 << M];
   __shared__ double wacc[NWAVE][SVI_GSLOTS_WIDE];   // per-wave sums of the gradient slots
   __shared__ int32_t hb_s[SVI_MMAX];
-  __shared__ int32_t gtab[GTAB * NT];
+  __shared__ uint16_t ltab[LTAB * 64];   // swizzled element index
 
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = a.m, c = a.c, nh = a.nh;
   const int ntile_el = 1 << m;
   const bool vec = c >= (VN == 2 ? 1 : 2);
@@ -1500,9 +1523,9 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron2(SweepArgs a) {
   const SVI_CONST double *coef = cptr(a.coef);
 
   if (tid < SVI_MMAX) hb_s[tid] = a.hb[tid < nh ? tid : 0];
-  const int ntab = nst < GTAB ? nst : GTAB;
-  for (int st = 0; st < ntab; st++)   // each thread reads back only its own entries
-    gtab[st * NT + tid] = swz<T>(stage_base<M, R>(tid, stages[st])) * (int)sizeof(C2);
+  const int ntab = nst < LTAB ? nst : LTAB;
+  for (int st = wave; st < ntab; st += NWAVE)
+    ltab[st * 64 + lane] = (uint16_t)swz<T>(lane_base(lane, stages[st]));
   for (int k = tid; k < NWAVE * SVI_GSLOTS_WIDE; k += NT) (&wacc[0][0])[k] = 0.0;
   __syncthreads();
 
@@ -1553,8 +1576,8 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron2(SweepArgs a) {
     // ---- stages
     for (int st = 0; st < nst; st++) {
       const SVI_CONST StageDesc &sd = stages[st];
-      const int gbs =
-          st < ntab ? gtab[st * NT + tid] : swz<T>(stage_base<M, R>(tid, sd)) * (int)sizeof(C2);
+      const int gbs = ((st < ntab ? (int)ltab[st * 64 + lane] : swz<T>(lane_base(lane, sd))) ^
+                       swz<T>(wave_base<M, R>(wave, sd))) * (int)sizeof(C2);
       const bool active = tid < (1 << (m > R ? m - R : 0));
       kron2_stage<T, R>((char *)lds[0], (char *)lds[1], gbs, sd, coef, a.ops, a.coef, active,
                         [&](int s0, int s1, double t) {

@@ -1030,10 +1030,6 @@ static void emit_sweep(Plan &P, std::vector<GateRec> &recs, const SweepP &sw, in
     }
     StageDesc sd;
     std::memset(&sd, 0, sizeof sd);
-    int sorted[SVI_RMAX];
-    for (int i = 0; i < R; i++) sorted[i] = st.gq[i];
-    std::sort(sorted, sorted + R);
-    for (int i = 0; i < SVI_RMAX; i++) sd.sbits[i] = i < R ? sorted[i] : 0;
     std::vector<MicroOp> leadp, trailp, body;
     if (st.kron) {
       // mops holds every record's micro-op in stage order; split by role
@@ -1172,19 +1168,19 @@ static void emit_sweep(Plan &P, std::vector<GateRec> &recs, const SweepP &sw, in
       if (st.kron) {
         int xl = spread_local(j, st.gq, R);
         for (size_t k = st.lead.size(); k-- > 0;) xl = perm_tile(st.lead[k], xl);
-        sd.ld_off[j] = svi_swz(xl, SWB) * EB;
+        sd.off[j] = svi_swz(xl, SWB) * EB;
         int xs = spread_local(j, st.gq, R);
         for (size_t k = 0; k < st.trail.size(); k++) xs = perm_tile(st.trail[k], xs);
-        sd.st_off[j] = svi_swz(xs, SWB) * EB;
+        sd.off[(1 << R) + j] = svi_swz(xs, SWB) * EB;
         xbits |= (xl | xs) & ~gmask;
         continue;
       }
       int jl = j;
       for (size_t k = leadp.size(); k-- > 0;) jl = perm_apply(leadp[k], jl);
-      sd.ld_off[j] = svi_swz(spread_local(jl, st.gq, R), SWB) * EB;
+      sd.off[j] = svi_swz(spread_local(jl, st.gq, R), SWB) * EB;
       int js = j;
       for (size_t k = 0; k < trailp.size(); k++) js = perm_apply(trailp[k], js);
-      sd.st_off[j] = svi_swz(spread_local(js, st.gq, R), SWB) * EB;
+      sd.off[(1 << R) + j] = svi_swz(spread_local(js, st.gq, R), SWB) * EB;
     }
     st_gmask.push_back(gmask);
     st_xbits.push_back(xbits);

@@ -90,20 +90,22 @@ enum { ST_OPS = 0, ST_KRON = 1 };
 #define SD_XCHG 8
 #define SD_WLOCAL 16
 
-struct StageDesc {
-  int32_t sbits[SVI_RMAX];     // tile-local bit positions of the group bits, ascending
-  int32_t op_begin, op_end;    // micro-ops [op_begin, op_end)
-  int32_t kind;                // ST_OPS / ST_KRON
+// A stage's descriptor: one 64-byte line, then the 2^R load offsets and the
+// 2^R store offsets (one more line for 3-qubit groups).
+struct alignas(64) StageDesc {
   uint32_t rmask;              // ST_KRON: group bits carrying a real 2x2
   int32_t dflags;              // ST_KRON: 1 = D_before, 2 = D_after; SD_* (any kind)
   int32_t kcoef;               // ST_KRON: coefficient offset (doubles)
+  int32_t kind;                // ST_OPS / ST_KRON
+  int8_t tpos[16] __attribute__((aligned(4)));   // tile bit of thread-index bit k (see above)
+  int32_t op_begin, op_end;    // micro-ops [op_begin, op_end)
   int32_t g1, g2;              // ST_KRON: MO_GRAD ops [op_begin, g1) run on the stage input,
                                // [g1, g2) after D_before, [g2, op_end) after the rotations
   uint32_t gdiag;              // ST_KRON: bit p set when every MO_GRAD op of range p
                                // (0, 1, 2 as above) has a diagonal generator
-  int8_t tpos[16] __attribute__((aligned(4)));   // tile bit of thread-index bit k (see above)
-  int32_t ld_off[SVI_GMAX];    // swizzled tile-local BYTE offset loaded into slot j
-  int32_t st_off[SVI_GMAX];    // swizzled tile-local BYTE offset slot j is stored to
+  int32_t pad[3];
+  int32_t off[2 * SVI_GMAX];   // swizzled tile-local BYTE offsets: slot j is loaded from
+                               // off[j] and stored to off[2^R + j]
 };
 
 // LDS swizzle of a tile-local element index (B = 3 for 16-byte complex

@@ -1915,7 +1915,8 @@ __global__ void __launch_bounds__(1 << (M - R)) k_serve(ServeArgs sa) {
   C2 *const lt = (C2 *)tiles;
   const int tid = threadIdx.x;
   // the queue counter is taken by wave 0 as a whole wave (one lane adds 1)
-  const bool wave0 = __builtin_amdgcn_readfirstlane(tid) == 0;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const bool wave0 = wave == 0;
   const int one = tid == 0 ? 1 : 0;
   for (;;) {
     if (wave0) {
@@ -1998,7 +1999,8 @@ __global__ void __launch_bounds__(1 << (M - R)) k_serve(ServeArgs sa) {
         __syncthreads();
         for (int st = 0; st < nst; st++) {
           const SVI_CONST StageDesc &sd = stages[st];
-          const int gbs = swz<T>(stage_base<M, R>(tid, sd)) * (int)sizeof(C2);
+          const int gbs = (swz<T>(lane_base(tid & 63, sd)) ^ swz<T>(wave_base<M, R>(wave, sd))) *
+                          (int)sizeof(C2);
           auto sink = [&](int s0, int s1, double t) {
             wave_deposit2(wacc[tid >> 6], s0, s1, t, tid & 63);
           };
