@@ -75,7 +75,7 @@ __device__ void pauli_tiles(const SVI_CONST PauliPassArgs &p, int64_t t0, int64_
     const uint64_t base = tile_base(tile, c, L.hb, nh);
     for (int i = tid; i < nel; i += NT) {
       const uint64_t g = base + spread_row(i >> c, L.hb, nh) + (uint64_t)(i & ((1 << c) - 1));
-      L.tile[swz<T>(i)] = C2{pre[g], pim[g]};
+      L.tile[swz<T>(i)] = C2{state_load<true>(pre + g), state_load<true>(pim + g)};
     }
     __syncthreads();
     for (int t = 0; t < nterm; t++) {
@@ -142,9 +142,8 @@ __global__ void __launch_bounds__(1 << (M - R)) k_batch(BatchKernelArgs b) {
       // Bounded wait for the circuit's earlier units.  Every unit this one
       // depends on precedes it in the queue and was taken by a running
       // workgroup, so the wait ends; the bound turns a broken plan into an
-      // error flag instead of a hang.  The polls are relaxed agent-scope loads
-      // (coherent across XCDs, no cache maintenance per poll); the acquire
-      // fence below runs once, after the wait.
+      // error flag instead of a hang.  The polls are relaxed agent-scope loads,
+      // like the state accesses after them.
       bool expired = b.spin_limit < 0;
       for (int32_t spins = 0; !expired; spins++) {
         const int d = __builtin_amdgcn_readfirstlane(
@@ -156,14 +155,13 @@ __global__ void __launch_bounds__(1 << (M - R)) k_batch(BatchKernelArgs b) {
       if (expired) __hip_atomic_fetch_or(b.err, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-    // acquire: the producers' state writes are visible to this wave's loads
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    // (state accesses are coherent across XCDs: no cache maintenance here)
     if (un.kind == UK_SWEEP)
-      sweep_tiles<T, M, R, KO>(cptr(b.sweeps)[un.arg], un.t0, un.t1, L.tile, L.hb);
+      sweep_tiles<T, M, R, KO, true>(cptr(b.sweeps)[un.arg], un.t0, un.t1, L.tile);
     else
       pauli_tiles<T, M, R>(cptr(b.passes)[un.arg], un.t0, un.t1, b.part + un.part, L);
-    // release: this wave's writes are visible device-wide before the count
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    // this wave's state stores are in memory before the count
+    stores_done();
     __syncthreads();
     if (wave0) __hip_atomic_fetch_add(b.done + circ, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }

@@ -1157,27 +1157,45 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron(SweepArgs a) {
 }
 
 // ------------------------------------------------ tile sweep, one workgroup
+// State accesses of kernels whose workgroups hand a state on to each other
+// within one launch (CO): relaxed agent-scope accesses, which go past the L1
+// and the XCD's L2 to memory that every XCD sees.  A workgroup publishes its
+// stores by waiting for them (stores_done) and then counting up; a reader
+// needs no more than to see the count.  (Ordinary accesses with agent-scope
+// fences write back and invalidate the whole L2 at every hand-over: the
+// 96-circuit batch took 13.1 ms that way.)
+template <bool CO, typename T>
+__device__ __forceinline__ T state_load(const T *p) {
+  if constexpr (CO) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else return *p;
+}
+
+template <bool CO, typename T>
+__device__ __forceinline__ void state_store(T *p, T v) {
+  if constexpr (CO) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else *p = v;
+}
+
+// Every store of this wave has reached memory.
+__device__ __forceinline__ void stores_done() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
+
 // Tiles [t0, t1) of one sweep of one state, run by one workgroup of 2^(M-R)
-// threads through the LDS tile `lt` (2^M amplitudes) with the tile's
-// high-bit table staged in `hb` (LDS, SVI_MMAX entries).  No qubit remapping
+// threads through the LDS tile `lt` (2^M amplitudes).  No qubit remapping
 // on the way out (SW_OPERM is not taken).  KO: every stage is a Kronecker
 // stage (no micro-op interpreter in the caller's kernel).
-template <typename T, int M, int R, bool KO>
+template <typename T, int M, int R, bool KO, bool CO>
 __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1,
-                            typename C2T<T>::type *lt, int32_t *hb) {
+                            typename C2T<T>::type *lt) {
   constexpr int NT = 1 << (M - R);
   constexpr int G = 1 << R;
-  constexpr int VN = V4T<T>::N;
-  constexpr int LV = VN == 2 ? 1 : 2;
-  constexpr int NIT = (1 << M) / (VN * NT);
   using C2 = typename C2T<T>::type;
-  using V4 = typename V4T<T>::type;
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = a.m, c = a.c, nh = a.nh;
   const int mm = m > R ? m : R;
   const int ntile_el = 1 << m;
-  const bool vec = c >= LV;
   const bool init0 = (a.flags & SW_INIT_ZERO) != 0;
   const int st_begin = a.stage_begin, st_end = a.stage_end;
   const SVI_CONST StageDesc *stages = cptr(a.stages);
@@ -1185,54 +1203,55 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
   const double *coef = a.coef;
   T *const pre = (T *)a.re, *const pim = (T *)a.im;
 
-  if (tid < SVI_MMAX) hb[tid] = a.hb[tid < nh ? tid : 0];
-  __syncthreads();
-  uint64_t roff[NIT];
+  // Thread tid moves tile elements i = tid + k * NT, one amplitude per access
+  // (consecutive lanes on consecutive addresses).  Offsets: a deposit of the
+  // element index by the descriptor's positions, read as scalars, so it splits
+  // into the thread's part and a uniform part of k.
+  auto off_of = [&](int i) {
+    uint64_t o = (uint64_t)(i & ((1 << c) - 1));
+    for (int k = 0; k < nh; k++) o |= (uint64_t)((i >> (c + k)) & 1) << a.hb[k];
+    return o;
+  };
+  uint64_t toff = off_of(tid);
+  uint64_t kb[R];
 #pragma unroll
-  for (int k = 0; k < NIT; k++) {
-    const int i = (tid + k * NT) * (vec ? VN : 1);
-    roff[k] = spread_row(i >> c, hb, nh) + (uint64_t)(i & ((1 << c) - 1));
-  }
-  const int tsw = swz<T>(tid * VN);
+  for (int r = 0; r < R; r++) kb[r] = off_of(NT << r);
+  // (re-declared opaque in every tile: the addresses are formed next to their
+  // use, not hoisted into registers that the stages need)
+  auto koff = [&](int k) {
+    uint64_t o = 0;
+#pragma unroll
+    for (int r = 0; r < R; r++)
+      if ((k >> r) & 1) o += kb[r];
+    return o;
+  };
+  const int tsl = swz<T>(tid);
   char *const lb = (char *)lt;
+  // waves whose threads hold no part of a small state (m < M) have no group
+  const bool on = wave * 64 < (1 << (mm - R));
 
   // tile bases: a sparse sweep deposits the tile index on the support's
   // qubits outside the tile only (bz, read from the descriptor)
   const bool sparse = (a.flags & SW_SPARSE) != 0;
+  const int nz = sparse ? a.nbz : nh;
   for (int64_t tile = t0; tile < t1; tile++) {
-    uint64_t base;
-    if (sparse) {
-      base = (uint64_t)tile << c;
-      for (int k = 0; k < a.nbz; k++) {
-        const int p = a.bz[k];
-        base = ((base >> p) << (p + 1)) | (base & ((1ull << p) - 1ull));
-      }
-    } else {
-      base = tile_base(tile, c, hb, nh);
+    uint64_t base = (uint64_t)tile << c;
+    for (int k = 0; k < nz; k++) {
+      const int p = sparse ? a.bz[k] : a.hb[k];
+      base = ((base >> p) << (p + 1)) | (base & ((1ull << p) - 1ull));
     }
+    T *const tr = pre + base, *const ti = pim + base;
+    asm volatile("" : "+v"(toff));
     if (init0 && base != 0) {
       // From |0..0> every tile but the one holding index 0 stays zero (a
       // sweep's gates act within tiles): it is written as zeros, with no
       // stages and no LDS (uniform over the workgroup)
-      if (vec) {
-        V4 z;
-        if constexpr (VN == 2) z = V4{(T)0, (T)0};
-        else z = V4{(T)0, (T)0, (T)0, (T)0};
 #pragma unroll
-        for (int k = 0; k < NIT; k++) {
-          const int i = (tid + k * NT) * VN;
-          if (i < ntile_el) {
-            *(V4 *)(pre + base + roff[k]) = z;
-            *(V4 *)(pim + base + roff[k]) = z;
-          }
+      for (int k = 0; k < G; k++)
+        if (tid + k * NT < ntile_el) {
+          state_store<CO>(tr + koff(k) + toff, (T)0);
+          state_store<CO>(ti + koff(k) + toff, (T)0);
         }
-      } else {
-        for (int i = tid; i < ntile_el; i += NT) {
-          const uint64_t g = base + spread_row(i >> c, hb, nh) + (uint64_t)(i & ((1 << c) - 1));
-          pre[g] = (T)0;
-          pim[g] = (T)0;
-        }
-      }
       continue;
     }
     if (mm > m) {
@@ -1242,34 +1261,20 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
     }
     if (init0) {
       for (int i = tid; i < ntile_el; i += NT) {
-        const T v = (base == 0 && i == 0) ? (T)1 : (T)0;
+        const T v = i == 0 ? (T)1 : (T)0;
         lt[swz<T>(i)] = C2{v, 0};
       }
-    } else if (vec) {
-#pragma unroll
-      for (int k = 0; k < NIT; k++) {
-        const int i = (tid + k * NT) * VN;
-        if (i < ntile_el) {
-          const uint64_t g = base + roff[k];
-          const V4 vr = *(const V4 *)(pre + g);
-          const V4 vi = *(const V4 *)(pim + g);
-          const int si = tsw ^ swz<T>(k * NT * VN);
-          if constexpr (VN == 2) {
-            lt[si] = C2{vr.x, vi.x};
-            lt[si ^ 1] = C2{vr.y, vi.y};
-          } else {
-            lt[si] = C2{vr.x, vi.x};
-            lt[si ^ 1] = C2{vr.y, vi.y};
-            lt[si ^ 2] = C2{vr.z, vi.z};
-            lt[si ^ 3] = C2{vr.w, vi.w};
-          }
-        }
-      }
     } else {
-      for (int i = tid; i < ntile_el; i += NT) {
-        const uint64_t g = base + spread_row(i >> c, hb, nh) + (uint64_t)(i & ((1 << c) - 1));
-        lt[swz<T>(i)] = C2{pre[g], pim[g]};
-      }
+      T vr[G], vi[G];
+#pragma unroll
+      for (int k = 0; k < G; k++)
+        if (tid + k * NT < ntile_el) {
+          vr[k] = state_load<CO>(tr + koff(k) + toff);
+          vi[k] = state_load<CO>(ti + koff(k) + toff);
+        }
+#pragma unroll
+      for (int k = 0; k < G; k++)
+        if (tid + k * NT < ntile_el) lt[tsl ^ swz<T>(k * NT)] = C2{vr[k], vi[k]};
     }
     __syncthreads();
 
@@ -1298,51 +1303,37 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
             apply_op<T, R>(op, re, im, coef);
           }
         }
-        if (sd.dflags & SD_XCHG) __syncthreads();
+        if (sd.dflags & SD_XCHG) lds_barrier();
 #pragma unroll
         for (int j = 0; j < G; j++) *(C2 *)(lb + (gbs ^ sd.off[G + j])) = C2{re[j], im[j]};
       };
-      if (sd.kind == ST_KRON && sd.rmask == (1u << R) - 1 && (sd.dflags & 7) == 2)
+      if (!on) {
+        if (sd.dflags & SD_XCHG) lds_barrier();
+      } else if (sd.kind == ST_KRON && sd.rmask == (1u << R) - 1 && (sd.dflags & 7) == 2) {
         body(std::true_type{});
-      else
+      } else {
         body(std::false_type{});
-      __syncthreads();
+      }
+      if (sd.dflags & SD_WLOCAL) {
+        // the next stage reads only slots this wave wrote
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+      } else {
+        lds_barrier();
+      }
     }
 
-    if (vec) {
+    asm volatile("" : "+v"(toff));
 #pragma unroll
-      for (int k = 0; k < NIT; k++) {
-        const int i = (tid + k * NT) * VN;
-        if (i < ntile_el) {
-          const uint64_t g = base + roff[k];
-          const int si = tsw ^ swz<T>(k * NT * VN);
-          V4 vr, vi;
-          if constexpr (VN == 2) {
-            const C2 p0 = lt[si], p1 = lt[si ^ 1];
-            vr = V4{p0.x, p1.x};
-            vi = V4{p0.y, p1.y};
-          } else {
-            const C2 p0 = lt[si], p1 = lt[si ^ 1], p2 = lt[si ^ 2], p3 = lt[si ^ 3];
-            vr = V4{p0.x, p1.x, p2.x, p3.x};
-            vi = V4{p0.y, p1.y, p2.y, p3.y};
-          }
-          *(V4 *)(pre + g) = vr;
-          *(V4 *)(pim + g) = vi;
-        }
+    for (int k = 0; k < G; k++)
+      if (tid + k * NT < ntile_el) {
+        const C2 p = lt[tsl ^ swz<T>(k * NT)];
+        state_store<CO>(tr + koff(k) + toff, p.x);
+        state_store<CO>(ti + koff(k) + toff, p.y);
       }
-    } else {
-      for (int i = tid; i < ntile_el; i += NT) {
-        const uint64_t g = base + spread_row(i >> c, hb, nh) + (uint64_t)(i & ((1 << c) - 1));
-        const C2 p = lt[swz<T>(i)];
-        pre[g] = p.x;
-        pim[g] = p.y;
-      }
-    }
     __syncthreads();
   }
-  // a zero tile ends without the barrier above, and a caller's next sweep
-  // starts by rewriting hb, which the last tiles' addresses were read from
-  if (init0) __syncthreads();
 }
 
 // ------------------------------------------- two-state Kronecker stage

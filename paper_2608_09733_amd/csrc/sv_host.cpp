@@ -839,7 +839,9 @@ static void assign_thread_maps(Plan &P, int first, const std::vector<int> &gm,
     std::vector<int> w = wr;
     const int nwp = nw - nwr;
     for (int i = (int)phant.size() - nwp; i < (int)phant.size(); i++) w.push_back(phant[i]);
-    if (keep || (s > 0 && w == wprev)) P.stages[first + s - 1].dflags |= SD_WLOCAL;
+    // (a stage that exchanges across waves reads or leaves slots of others)
+    const bool xw = ((sd.dflags | (s > 0 ? P.stages[first + s - 1].dflags : 0)) & SD_XCHG) != 0;
+    if (!xw && (keep || (s > 0 && w == wprev))) P.stages[first + s - 1].dflags |= SD_WLOCAL;
     int wmask = 0;
     for (int p : w) wmask |= 1 << p;
     // lane bits: the real ones first, then the remaining phantom ones
@@ -3152,9 +3154,19 @@ extern "C" sv_status sv_batch_plan(const sv_circuit_desc *circuits, int32_t n_ci
   b->state_off.resize(n_circuits);
   std::vector<std::pair<int, double>> const_init;   // (param slot, value)
 
+  // Tiles per unit.  A Pauli unit's tiles are summed together, so their number
+  // depends on the circuit alone (a circuit's values are the same alone and in
+  // any mix).  A sweep's tiles are independent: they are grouped only as far as
+  // the batch keeps every CU busy anyway (about four units per CU and level),
+  // since a unit's tiles run one after the other on one CU and the circuit's
+  // next sweep waits for them.
   auto tiles_per_unit = [](int64_t ntiles) -> int64_t {
     return std::max<int64_t>(1, std::min<int64_t>(8, ntiles / 32));
   };
+  int64_t width = 0;   // tiles of one level over all circuits
+  for (int k = 0; k < n_circuits; k++)
+    width += (int64_t)1 << std::max(0, circuits[k].n_qubits - M);
+  const int64_t sweep_cap = std::max<int64_t>(1, width / 1024);
 
   for (int k = 0; k < n_circuits; k++) {
     const sv_circuit_desc &d = circuits[k];
@@ -3235,7 +3247,7 @@ extern "C" sv_status sv_batch_plan(const sv_circuit_desc *circuits, int32_t n_ci
       const int idx = (int)sweeps.size();
       sweeps.push_back(a);
       std::vector<BatchUnit> lu;
-      const int64_t tpu = tiles_per_unit(a.ntiles);
+      const int64_t tpu = std::min(sweep_cap, tiles_per_unit(a.ntiles));
       for (int64_t t = 0; t < a.ntiles; t += tpu) {
         BatchUnit u{};
         u.kind = UK_SWEEP;

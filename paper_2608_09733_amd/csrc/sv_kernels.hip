@@ -1932,7 +1932,7 @@ __global__ void __launch_bounds__(1 << (M - R)) k_serve(ServeArgs sa) {
     // ---- forward: the circuit from |0..0> (the first sweep synthesises it)
     for (int s = 0; s < q.f_nsweeps; s++) {
       const SVI_CONST SweepArgs &a = cptr(sa.sweeps)[q.f_sweep + s];
-      sweep_tiles<T, M, R, !GEN>(a, 0, a.ntiles, lt, hb_s);
+      sweep_tiles<T, M, R, !GEN, false>(a, 0, a.ntiles, lt);
     }
     __syncthreads();
 
