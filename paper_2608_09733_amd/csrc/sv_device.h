@@ -1181,6 +1181,70 @@ __device__ __forceinline__ void stores_done() {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
+// The stages of one sweep on the tile in LDS (a workgroup of 2^(M-R) threads);
+// ends with a barrier after the last stage.
+template <typename T, int M, int R, bool KO>
+__device__ __forceinline__ void tile_stages(const SVI_CONST SweepArgs &a,
+                                            typename C2T<T>::type *lt) {
+  constexpr int G = 1 << R;
+  using C2 = typename C2T<T>::type;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int mm = a.m > R ? a.m : R;
+  const int st_begin = a.stage_begin, st_end = a.stage_end;
+  const SVI_CONST StageDesc *stages = cptr(a.stages);
+  const MicroOp *ops = a.ops;
+  const double *coef = a.coef;
+  char *const lb = (char *)lt;
+  // waves whose threads hold no part of a small state (m < M) have no group
+  const bool on = wave * 64 < (1 << (mm - R));
+      for (int st = st_begin; st < st_end; st++) {
+        const SVI_CONST StageDesc &sd = stages[st];
+        const int gbs =
+            (swz<T>(lane_base(tid & 63, sd)) ^ swz<T>(wave_base<M, R>(wave, sd))) * (int)sizeof(C2);
+        // a full Kronecker stage (every group bit rotated, then D_after) runs as
+        // its own straight-line body, loads to stores; the general body branches
+        auto body = [&](auto full_stage) {
+          T re[G], im[G];
+  #pragma unroll
+          for (int j = 0; j < G; j++) {
+            const C2 v = *(const C2 *)(lb + (gbs ^ sd.off[j]));
+            re[j] = v.x;
+            im[j] = v.y;
+          }
+          if constexpr (decltype(full_stage)::value) {
+            kron_rot_all<T, R>(re, im, cptr(coef) + sd.kcoef);
+            mo_diagt<T, R>(re, im, cptr(coef) + sd.kcoef + 4 * R + 2 * G);
+          } else if (KO || sd.kind == ST_KRON) {
+            kron_stage<T, R>(re, im, cptr(coef) + sd.kcoef, sd.rmask, sd.dflags);
+          } else {
+            for (int o = sd.op_begin; o < sd.op_end; o++) {
+              const MicroOp op = op_at(ops, o);
+              apply_op<T, R>(op, re, im, coef);
+            }
+          }
+          if (sd.dflags & SD_XCHG) lds_barrier();
+  #pragma unroll
+          for (int j = 0; j < G; j++) *(C2 *)(lb + (gbs ^ sd.off[G + j])) = C2{re[j], im[j]};
+        };
+        if (!on) {
+          if (sd.dflags & SD_XCHG) lds_barrier();
+        } else if (sd.kind == ST_KRON && sd.rmask == (1u << R) - 1 && (sd.dflags & 7) == 2) {
+          body(std::true_type{});
+        } else {
+          body(std::false_type{});
+        }
+        if (sd.dflags & SD_WLOCAL) {
+          // the next stage reads only slots this wave wrote
+          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+          __builtin_amdgcn_wave_barrier();
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+        } else {
+          lds_barrier();
+        }
+      }
+}
+
 // Tiles [t0, t1) of one sweep of one state, run by one workgroup of 2^(M-R)
 // threads through the LDS tile `lt` (2^M amplitudes).  No qubit remapping
 // on the way out (SW_OPERM is not taken).  KO: every stage is a Kronecker
@@ -1192,15 +1256,10 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
   constexpr int G = 1 << R;
   using C2 = typename C2T<T>::type;
   const int tid = threadIdx.x;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int m = a.m, c = a.c, nh = a.nh;
   const int mm = m > R ? m : R;
   const int ntile_el = 1 << m;
   const bool init0 = (a.flags & SW_INIT_ZERO) != 0;
-  const int st_begin = a.stage_begin, st_end = a.stage_end;
-  const SVI_CONST StageDesc *stages = cptr(a.stages);
-  const MicroOp *ops = a.ops;
-  const double *coef = a.coef;
   T *const pre = (T *)a.re, *const pim = (T *)a.im;
 
   // Thread tid moves tile elements i = tid + k * NT, one amplitude per access
@@ -1226,9 +1285,6 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
     return o;
   };
   const int tsl = swz<T>(tid);
-  char *const lb = (char *)lt;
-  // waves whose threads hold no part of a small state (m < M) have no group
-  const bool on = wave * 64 < (1 << (mm - R));
 
   // tile bases: a sparse sweep deposits the tile index on the support's
   // qubits outside the tile only (bz, read from the descriptor)
@@ -1278,51 +1334,7 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
     }
     __syncthreads();
 
-    for (int st = st_begin; st < st_end; st++) {
-      const SVI_CONST StageDesc &sd = stages[st];
-      const int gbs =
-          (swz<T>(lane_base(tid & 63, sd)) ^ swz<T>(wave_base<M, R>(wave, sd))) * (int)sizeof(C2);
-      // a full Kronecker stage (every group bit rotated, then D_after) runs as
-      // its own straight-line body, loads to stores; the general body branches
-      auto body = [&](auto full_stage) {
-        T re[G], im[G];
-#pragma unroll
-        for (int j = 0; j < G; j++) {
-          const C2 v = *(const C2 *)(lb + (gbs ^ sd.off[j]));
-          re[j] = v.x;
-          im[j] = v.y;
-        }
-        if constexpr (decltype(full_stage)::value) {
-          kron_rot_all<T, R>(re, im, cptr(coef) + sd.kcoef);
-          mo_diagt<T, R>(re, im, cptr(coef) + sd.kcoef + 4 * R + 2 * G);
-        } else if (KO || sd.kind == ST_KRON) {
-          kron_stage<T, R>(re, im, cptr(coef) + sd.kcoef, sd.rmask, sd.dflags);
-        } else {
-          for (int o = sd.op_begin; o < sd.op_end; o++) {
-            const MicroOp op = op_at(ops, o);
-            apply_op<T, R>(op, re, im, coef);
-          }
-        }
-        if (sd.dflags & SD_XCHG) lds_barrier();
-#pragma unroll
-        for (int j = 0; j < G; j++) *(C2 *)(lb + (gbs ^ sd.off[G + j])) = C2{re[j], im[j]};
-      };
-      if (!on) {
-        if (sd.dflags & SD_XCHG) lds_barrier();
-      } else if (sd.kind == ST_KRON && sd.rmask == (1u << R) - 1 && (sd.dflags & 7) == 2) {
-        body(std::true_type{});
-      } else {
-        body(std::false_type{});
-      }
-      if (sd.dflags & SD_WLOCAL) {
-        // the next stage reads only slots this wave wrote
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-      } else {
-        lds_barrier();
-      }
-    }
+    tile_stages<T, M, R, KO>(a, lt);
 
     asm volatile("" : "+v"(toff));
 #pragma unroll

@@ -3634,11 +3634,12 @@ extern "C" sv_status sv_batch_autotune(const sv_circuit_desc *circuits, int32_t 
 }
 
 // ---------------------------------------------------------------- serving
-// Small adjoint requests run whole inside one workgroup each (k_serve): the
+// Small adjoint requests run in one persistent launch (k_serve), those of up to
+// 12 qubits whole inside one workgroup each, larger ones tile by tile: the
 // forward and backward plans are built for 12-qubit tiles and cached per
 // request structure; a submission copies one staging block (request
-// descriptors, sweep arguments, observables, parameters) to the device and
-// launches two kernels.  A ring of staging slots lets submissions queue on the
+// descriptors, sweep arguments, units, observables, parameters) to the device
+// and launches two kernels.  A ring of staging slots lets submissions queue on the
 // stream while earlier ones run.
 
 struct ServePlan {
@@ -3791,6 +3792,13 @@ extern "C" sv_status sv_serve_submit(sv_serve *sv, const sv_circuit_desc *reques
       if (!s) s = upload_plan(sp->B);
       if (s) return s;
     }
+  // requests of the lean kernel first, then those of the general one
+  std::vector<int> pos(n_requests);
+  int n_lean = 0;
+  for (int r = 0; r < n_requests; r++)
+    if (!plans[r]->general) pos[r] = n_lean++;
+  for (int r = 0, g = n_lean; r < n_requests; r++)
+    if (plans[r]->general) pos[r] = g++;
   // ---- layout: staged part (copied from host) | device-only part
   auto align = [](size_t v) { return (v + 255) & ~(size_t)255; };
   size_t off = 256;   // [0], [1]: queue heads of the lean and the general kernel
@@ -3805,6 +3813,52 @@ extern "C" sv_status sv_serve_submit(sv_serve *sv, const sv_circuit_desc *reques
   }
   const size_t o_sweeps = off;
   off = align(off + (size_t)nsw * sizeof(SweepArgs));
+  const size_t o_ctl = off;   // per request: units done, a wait expired
+  off = align(off + (size_t)n_requests * 8);
+  // Units, in queue order: phase by phase, so that every unit depends only on
+  // units before it; the first phase of the requests of several tiles (most
+  // tiles first: they have the longest way to go), then the requests that are
+  // one unit (most stages first), then the further phases.  The requests of the
+  // lean kernel and of the general one have queues of their own (each request
+  // always runs in the same kernel, whatever the mix).
+  std::vector<ServeUnit> units[2];
+  {
+    struct Item { int r; int64_t nt, cost; int phases; };
+    std::vector<Item> multi, single;
+    for (int r = 0; r < n_requests; r++) {
+      const Plan &F = plans[r]->F, &B = plans[r]->B;
+      Item it;
+      it.r = r;
+      it.nt = (int64_t)1 << std::max(0, requests[r].n_qubits - kServeFwd.M);
+      it.cost = (int64_t)F.stages.size() + 2 * (int64_t)B.stages.size();
+      it.phases = (int)std::max<size_t>(F.steps.size(), 1) + 1 + (int)B.steps.size() + 1;
+      (it.nt > 1 ? multi : single).push_back(it);
+    }
+    std::stable_sort(multi.begin(), multi.end(), [](const Item &x, const Item &y) {
+      return x.nt != y.nt ? x.nt > y.nt : x.phases > y.phases;
+    });
+    std::stable_sort(single.begin(), single.end(),
+                     [](const Item &x, const Item &y) { return x.cost > y.cost; });
+    auto push = [&](const Item &it, int phase, int64_t tile) {
+      ServeUnit u;
+      u.req = pos[it.r];
+      u.phase = phase;
+      u.tile = (int32_t)tile;
+      u.wait = phase > 0 ? (int32_t)(phase * it.nt) : 0;
+      units[plans[it.r]->general ? 1 : 0].push_back(u);
+    };
+    int maxph = 0;
+    for (const Item &it : multi) maxph = std::max(maxph, it.phases);
+    for (int ph = 0; ph == 0 || ph < maxph; ph++) {
+      for (const Item &it : multi)
+        for (int64_t t = 0; ph < it.phases && t < (ph == it.phases - 1 ? 1 : it.nt); t++) push(it, ph, t);
+      if (ph == 0)
+        for (const Item &it : single) push(it, -1, 0);
+    }
+  }
+  const size_t n_units = units[0].size() + units[1].size();
+  const size_t o_units = off;
+  off = align(off + n_units * sizeof(ServeUnit));
   const size_t o_terms = off;
   off = align(off + std::max<size_t>(nterm, 1) * sizeof(PauliTermDev));
   std::vector<size_t> o_fp(n_requests), o_bp(n_requests);
@@ -3825,19 +3879,11 @@ extern "C" sv_status sv_serve_submit(sv_serve *sv, const sv_circuit_desc *reques
     off = align(off + (size_t)(plans[r]->B.ncoef + 1) * 8);
     o_st[r] = off;
     off += 4 * plane;
-    o_sl[r] = off;
-    off = align(off + (size_t)(plans[r]->B.n_gslots + 1) * 8);
+    o_sl[r] = off;   // slot sums and energy parts of every tile
+    const size_t nt = (size_t)1 << std::max(0, requests[r].n_qubits - kServeFwd.M);
+    off = align(off + nt * (size_t)(plans[r]->B.n_gslots + 1) * 8);
   }
   const size_t total = off;
-  // queue order: requests of the lean kernel first, then those of the general
-  // one (each request always runs in the same kernel, whatever the mix)
-  std::vector<int> pos(n_requests);
-  int n_lean = 0;
-  for (int r = 0; r < n_requests; r++)
-    if (!plans[r]->general) pos[r] = n_lean++;
-  for (int r = 0, g = n_lean; r < n_requests; r++)
-    if (plans[r]->general) pos[r] = g++;
-
   // ---- a free staging slot (waits for the run that used it last)
   ServeSlot &sl = sv->slot[sv->next];
   sv->next = (sv->next + 1) % SVS_SLOTS;
@@ -3860,6 +3906,9 @@ extern "C" sv_status sv_serve_submit(sv_serve *sv, const sv_circuit_desc *reques
   char *h = (char *)sl.h_buf;
   char *d = (char *)sl.d_buf;
   std::memset(h, 0, 256);
+  std::memset(h + o_ctl, 0, (size_t)n_requests * 8);
+  std::copy(units[0].begin(), units[0].end(), (ServeUnit *)(h + o_units));
+  std::copy(units[1].begin(), units[1].end(), (ServeUnit *)(h + o_units) + units[0].size());
   ServeReq *hq = (ServeReq *)(h + o_reqs);
   SweepArgs *hs = (SweepArgs *)(h + o_sweeps);
   PauliTermDev *ht = (PauliTermDev *)(h + o_terms);
@@ -3892,7 +3941,11 @@ extern "C" sv_status sv_serve_submit(sv_serve *sv, const sv_circuit_desc *reques
     q.lre = d + o_st[r] + 2 * plane;
     q.lim = d + o_st[r] + 3 * plane;
     q.terms = (const PauliTermDev *)(d + o_terms) + it;
+    q.n_tiles = 1 << std::max(0, n - kServeFwd.M);
+    q.n_gslots = B.n_gslots;
     q.slots = (double *)(d + o_sl[r]);
+    q.epart = q.slots + (size_t)q.n_tiles * B.n_gslots;
+    q.ctl = (int32_t *)(d + o_ctl) + 2 * pos[r];
     q.rowptr = B.d_rowptr;
     q.gslots = B.d_gslots;
     q.out = d_out + out_off;
@@ -3961,13 +4014,16 @@ extern "C" sv_status sv_serve_submit(sv_serve *sv, const sv_circuit_desc *reques
   const ServeReq *d_reqs = (const ServeReq *)(d + o_reqs);
   const SweepArgs *d_sweeps = (const SweepArgs *)(d + o_sweeps);
   hipError_t e = svk_launch_serve_coefs(d_reqs, n_requests, max_desc, stream);
-  const int n_gen = n_requests - n_lean;
-  if (e == hipSuccess && n_lean)
-    e = svk_launch_serve(d_reqs, d_sweeps, (int32_t *)d, n_lean, 0,
-                         std::min(n_lean, std::max(1, di.cus)), stream);
-  if (e == hipSuccess && n_gen)
-    e = svk_launch_serve(d_reqs + n_lean, d_sweeps, (int32_t *)d + 1, n_gen, 1,
-                         std::min(n_gen, std::max(1, di.cus)), stream);
+  for (int g = 0; g < 2 && e == hipSuccess; g++) {
+    ServeArgs a;
+    a.reqs = d_reqs;
+    a.sweeps = d_sweeps;
+    a.units = (const ServeUnit *)(d + o_units) + (g ? units[0].size() : 0);
+    a.head = (int32_t *)d + g;
+    a.nunits = (int32_t)units[g].size();
+    a.spin_limit = 1 << 20;   // about a second
+    e = svk_launch_serve(a, g, std::min(a.nunits, std::max(1, di.cus)), stream);
+  }
   if (e != hipSuccess) return fail(SV_EDEVICE, "serving kernels: %s", hipGetErrorString(e));
   HIPCHK(hipEventRecord(sl.done, stream));
   sl.busy = true;

@@ -244,10 +244,20 @@ struct BatchKernelArgs {
   int32_t spin_limit;  // polls before a wait expires; < 0: every wait expires at once
 };
 
-// Serving: one workgroup takes one small request off the queue and runs its
-// whole adjoint -- forward sweeps, lambda = H psi and E = <psi|H|psi>, the
-// backward sweeps with their gradient slots, the gather into dE/dtheta --
-// with the request's planes in L2.  Coefficients are built by a launch before.
+// Serving: a persistent launch drains a device queue of units.  A request that
+// fits one tile is one unit: a workgroup runs its whole adjoint -- forward
+// sweep, lambda = H psi and E = <psi|H|psi>, the backward sweeps with their
+// gradient slots, the gather into dE/dtheta -- with psi and lambda in LDS.  A
+// larger request is cut into one unit per phase and tile (phases: each forward
+// sweep, lambda, each backward sweep, the gather), with its planes in memory.
+// Coefficients are built by a launch before.
+struct ServeUnit {
+  int32_t req;                // request
+  int32_t phase;              // < 0: the whole request
+  int32_t tile;
+  int32_t wait;               // units of this request that must be complete first
+};
+
 struct ServeReq {
   int32_t n;                  // qubits
   int32_t n_params;           // user parameters (gradient length)
@@ -255,7 +265,8 @@ struct ServeReq {
   int32_t b_sweep, b_nsweeps; // backward sweeps
   int32_t f_ndesc, b_ndesc;   // coefficient descriptors of the two plans
   int32_t n_terms;            // observable terms
-  int32_t pad;
+  int32_t n_tiles;            // tiles of the state
+  int32_t n_gslots;           // gradient slots of the backward plan
   const CoefDesc *f_desc, *b_desc;
   const TabFactor *f_fac, *b_fac;
   const double *f_params, *b_params;  // user parameters, then the plan's constants
@@ -263,7 +274,9 @@ struct ServeReq {
   void *re, *im;              // psi (2^n elements each)
   void *lre, *lim;            // lambda
   const PauliTermDev *terms;  // x, z, c of each term
-  double *slots;              // gradient slot sums of the backward plan
+  double *slots;              // gradient slot sums of each tile [tile][slot]
+  double *epart;              // each tile's part of E
+  int32_t *ctl;               // units done; a wait expired (both zero at launch)
   const int32_t *rowptr;      // parameter p takes slots gslots[rowptr[p] .. rowptr[p+1])
   const int32_t *gslots;
   double *out;                // E, then dE/dtheta_p
@@ -272,6 +285,8 @@ struct ServeReq {
 struct ServeArgs {
   const ServeReq *reqs;
   const SweepArgs *sweeps;
-  int32_t *head;              // next request to take (zero at launch)
-  int32_t nreq;
+  const ServeUnit *units;
+  int32_t *head;              // next unit to take (zero at launch)
+  int32_t nunits;
+  int32_t spin_limit;         // polls before a wait expires
 };

@@ -1900,148 +1900,304 @@ __global__ void __launch_bounds__(256) k_serve_coefs(const ServeReq *reqs) {
   }
 }
 
+// One full tile of a request's planes between memory (coherent accesses) and
+// LDS: element i = tid + k NT sits at base + a deposit of i by the sweep's
+// positions, split into the thread's part and a uniform part of k.
+template <typename T>
+struct ServeTile {
+  const SVI_CONST SweepArgs &a;
+  uint32_t base, toff;
+  __device__ __forceinline__ uint32_t off_of(uint32_t i) const {
+    const int c = a.c, nh = a.nh;
+    uint32_t o = i & ((1u << c) - 1);
+    for (int k = 0; k < nh; k++) o |= ((i >> (c + k)) & 1u) << a.hb[k];
+    return o;
+  }
+  __device__ __forceinline__ ServeTile(const SVI_CONST SweepArgs &args, int32_t tile) : a(args) {
+    base = (uint32_t)tile << a.c;
+    for (int k = 0; k < a.nh; k++) {
+      const int p = a.hb[k];
+      base = ((base >> p) << (p + 1)) | (base & ((1u << p) - 1u));
+    }
+    toff = off_of(threadIdx.x);
+  }
+  template <int NT, int G>
+  __device__ __forceinline__ void load(const T *pr, const T *pi, typename C2T<T>::type *t) const {
+    T vr[G], vi[G];
+#pragma unroll
+    for (int k = 0; k < G; k++) {
+      const uint32_t ko = base + off_of((uint32_t)(k * NT));
+      vr[k] = state_load<true>(pr + ko + toff);
+      vi[k] = state_load<true>(pi + ko + toff);
+    }
+#pragma unroll
+    for (int k = 0; k < G; k++) t[swz<T>((int)threadIdx.x + k * NT)] = {vr[k], vi[k]};
+  }
+  template <int NT, int G>
+  __device__ __forceinline__ void store(T *pr, T *pi, const typename C2T<T>::type *t) const {
+#pragma unroll
+    for (int k = 0; k < G; k++) {
+      const uint32_t ko = base + off_of((uint32_t)(k * NT));
+      const auto v = t[swz<T>((int)threadIdx.x + k * NT)];
+      state_store<true>(pr + ko + toff, v.x);
+      state_store<true>(pi + ko + toff, v.y);
+    }
+  }
+  __device__ __forceinline__ void zero(T *p, int NT, int G) const {
+    for (int k = 0; k < G; k++) state_store<true>(p + base + off_of((uint32_t)(k * NT)) + toff, (T)0);
+  }
+};
+
+// The stages of one backward sweep on the psi and lambda tiles in LDS, the
+// gradient terms into the waves' rows of wacc; then the sweep's slot sums
+// (in wave order) to slots[0 .. n_gslots).
+template <typename T, int M, int R, bool GEN>
+__device__ __forceinline__ void serve_backward(const SVI_CONST SweepArgs &a,
+                                               typename C2T<T>::type *lt,
+                                               double (*wacc)[SVI_GSLOTS_MAX], double *slots) {
+  constexpr int NT = 1 << (M - R);
+  constexpr int NWAVE = NT / 64;
+  using C2 = typename C2T<T>::type;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nact = 1 << (a.m > R ? a.m - R : 0);   // threads that hold the state
+  for (int k = tid; k < NWAVE * SVI_GSLOTS_MAX; k += NT) (&wacc[0][0])[k] = 0.0;
+  __syncthreads();
+  const SVI_CONST double *coef = cptr(a.coef);
+  for (int st = a.stage_begin; st < a.stage_end; st++) {
+    const SVI_CONST StageDesc &sd = cptr(a.stages)[st];
+    if (wave * 64 >= nact) {   // no part of a small state: the barriers only
+      if (sd.dflags & SD_XCHG) lds_barrier();
+      if ((GEN && sd.kind != ST_KRON) || !(sd.dflags & SD_WLOCAL)) lds_barrier();
+      continue;
+    }
+    const int gbs =
+        (swz<T>(lane_base(tid & 63, sd)) ^ swz<T>(wave_base<M, R>(wave, sd))) * (int)sizeof(C2);
+    auto sink = [&](int s0, int s1, double t) { wave_deposit2(wacc[wave], s0, s1, t, tid & 63); };
+    if (!GEN || sd.kind == ST_KRON)
+      kron2_stage<T, R>((char *)lt, (char *)(lt + (1 << M)), gbs, sd, coef, a.ops, a.coef, tid < nact,
+                        sink);
+    else if constexpr (GEN)
+      ops2_stage<T, R>((char *)lt, (char *)(lt + (1 << M)), gbs, sd, a.ops, a.coef, tid < nact, sink);
+  }
+  __syncthreads();
+  for (int sl = tid; sl < a.n_gslots; sl += NT) {
+    double v = 0.0;
+    for (int w = 0; w < NWAVE; w++) v += wacc[w][sl];
+    state_store<true>(slots + a.gslot_begin + sl, v);
+  }
+  __syncthreads();
+}
+
 // GEN: the requests' plans hold micro-op (interpreter) stages; without it
 // every stage of every sweep is a Kronecker stage and the kernel is leaner.
+// Bound by the stages of one CU, so a request of 13 to 16 qubits, whose sweeps
+// run 2 to 16 tiles, is spread over as many workgroups: run by one workgroup
+// each, 30 layers at 12 / 13 / 14 qubits took 1.10 / 2.11 / 4.14 ms.
 template <typename T, int M, int R, bool GEN>
 __global__ void __launch_bounds__(1 << (M - R)) k_serve(ServeArgs sa) {
   constexpr int NT = 1 << (M - R);
+  constexpr int G = 1 << R;
   constexpr int NWAVE = NT / 64;
   using C2 = typename C2T<T>::type;
   __shared__ __align__(16) char tiles[2 * (1 << M) * sizeof(C2)];
   __shared__ double wacc[NWAVE][SVI_GSLOTS_MAX];
   __shared__ double wred[NWAVE];
-  __shared__ int32_t hb_s[SVI_MMAX];
-  __shared__ int32_t req_s;
-  C2 *const lt = (C2 *)tiles;
+  __shared__ int32_t unit_s;
+  C2 *const lt = (C2 *)tiles, *const ll = lt + (1 << M);   // psi, lambda
   const int tid = threadIdx.x;
   // the queue counter is taken by wave 0 as a whole wave (one lane adds 1)
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const bool wave0 = wave == 0;
+  const bool wave0 = __builtin_amdgcn_readfirstlane(tid) == 0;
   const int one = tid == 0 ? 1 : 0;
   for (;;) {
     if (wave0) {
       const int v = __hip_atomic_fetch_add(sa.head, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (tid == 0) req_s = v;
+      if (tid == 0) unit_s = v;
     }
     __syncthreads();
-    const int r = __builtin_amdgcn_readfirstlane(req_s);
+    const int u = __builtin_amdgcn_readfirstlane(unit_s);
     __syncthreads();
-    if (r >= sa.nreq) break;
-    const ServeReq &q = sa.reqs[r];
-
-    // ---- forward: the circuit from |0..0> (the first sweep synthesises it)
-    for (int s = 0; s < q.f_nsweeps; s++) {
-      const SVI_CONST SweepArgs &a = cptr(sa.sweeps)[q.f_sweep + s];
-      sweep_tiles<T, M, R, !GEN, false>(a, 0, a.ntiles, lt);
+    if (u >= sa.nunits) break;
+    const SVI_CONST ServeUnit &un = cptr(sa.units)[u];
+    const SVI_CONST ServeReq &q = cptr(sa.reqs)[un.req];
+    const bool whole = un.phase < 0;
+    const int nf = q.f_nsweeps, nb = q.b_nsweeps;
+    const int n = q.n, N1 = n < M ? 1 << n : 1 << M;   // amplitudes of a tile
+    if (wave0 && un.wait > 0) {
+      // Bounded wait for the request's earlier units, which precede this one
+      // in the queue: running workgroups have taken them, so the wait ends.
+      // One that expired all the same makes the request's results NaN.
+      bool expired = false;
+      for (int32_t spins = 0; !expired; spins++) {
+        const int d = __builtin_amdgcn_readfirstlane(
+            __hip_atomic_load(q.ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        if (d >= un.wait) break;
+        if (spins >= sa.spin_limit) expired = true;
+        else __builtin_amdgcn_s_sleep(16);
+      }
+      if (expired) __hip_atomic_fetch_or(q.ctl + 1, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
-
-    // ---- lambda = H psi and E = Re <psi|lambda> (paper Section 4.4 Pauli
-    // action: P|b> = i^{nY} (-1)^{popcount(b & z)} |b ^ x>)
-    double e = 0.0;
-    {
-      const int64_t N = (int64_t)1 << q.n;
-      const T *pr = (const T *)q.re, *pim = (const T *)q.im;
-      T *lr = (T *)q.lre, *li = (T *)q.lim;
-      for (int64_t b = tid; b < N; b += NT) {
-        double ar = 0.0, ai = 0.0;
+    const int p0 = whole ? 0 : un.phase, p1 = whole ? nf + nb + 2 : un.phase + 1;
+    for (int ph = p0; ph < p1; ph++) {
+      if (ph < nf) {
+        // ---- forward: the circuit from |0..0>
+        const SVI_CONST SweepArgs &a = cptr(sa.sweeps)[q.f_sweep + ph];
+        const bool init0 = (a.flags & SW_INIT_ZERO) != 0;
+        const ServeTile<T> io(a, whole ? 0 : un.tile);
+        if (init0 && io.base != 0) {
+          // every tile but the one holding index 0 stays zero
+          io.zero((T *)a.re, NT, G);
+          io.zero((T *)a.im, NT, G);
+        } else {
+          if (init0) {
+            for (int i = tid; i < N1; i += NT) lt[swz<T>(i)] = C2{i == 0 ? (T)1 : (T)0, 0};
+          } else if (!whole) {
+            io.template load<NT, G>((const T *)a.re, (const T *)a.im, lt);
+          }
+          __syncthreads();
+          tile_stages<T, M, R, !GEN>(a, lt);
+          // (a state of one tile stays in LDS)
+          if (!whole) io.template store<NT, G>((T *)a.re, (T *)a.im, lt);
+          __syncthreads();
+        }
+      } else if (ph == nf) {
+        // ---- lambda = H psi and E = Re <psi|lambda> over this tile's block of
+        // 2^M amplitudes (paper Section 4.4 Pauli action: P|b> = i^{nY}
+        // (-1)^{popcount(b & z)} |b ^ x>); partners from LDS, those of another
+        // block from memory
+        const T *pr = (const T *)q.re, *pim = (const T *)q.im;
+        const uint32_t b0 = whole ? 0u : (uint32_t)un.tile << M;
+        T sr[G], si[G];
+        double ar[G], ai[G];
+#pragma unroll
+        for (int k = 0; k < G; k++) {
+          const int i = tid + k * NT;
+          sr[k] = si[k] = 0;
+          ar[k] = ai[k] = 0.0;
+          if (i < N1) {
+            if (whole) {
+              const C2 v = lt[swz<T>(i)];
+              sr[k] = v.x;
+              si[k] = v.y;
+            } else {
+              sr[k] = state_load<true>(pr + b0 + i);
+              si[k] = state_load<true>(pim + b0 + i);
+            }
+          }
+        }
+        if (!whole) {
+#pragma unroll
+          for (int k = 0; k < G; k++) lt[swz<T>(tid + k * NT)] = C2{sr[k], si[k]};
+          __syncthreads();
+        }
         for (int t = 0; t < q.n_terms; t++) {
-          const uint64_t x = q.terms[t].x, z = q.terms[t].z;
-          const double c = q.terms[t].c;
-          const uint64_t src = (uint64_t)b ^ x;
-          const double sr = (double)pr[src], si = (double)pim[src];
-          double tr, ti;
-          switch (__builtin_popcountll(x & z) & 3) {   // i^{nY}
-            case 0: tr = sr; ti = si; break;
-            case 1: tr = -si; ti = sr; break;
-            case 2: tr = -sr; ti = -si; break;
-            default: tr = si; ti = -sr; break;
+          const PauliTermDev pt = term_at(q.terms, t);
+          const uint32_t x = (uint32_t)pt.x, z = (uint32_t)pt.z;
+          const int ny = __builtin_popcount(x & z) & 3;
+#pragma unroll
+          for (int k = 0; k < G; k++) {
+            const int i = tid + k * NT;
+            if (i >= N1) continue;
+            const uint32_t src = (b0 + (uint32_t)i) ^ x;
+            double ur, ui;
+            if (x == 0) {
+              ur = (double)sr[k];
+              ui = (double)si[k];
+            } else if ((x >> M) == 0) {
+              const C2 v = lt[swz<T>((int)(src & ((1u << M) - 1)))];
+              ur = (double)v.x;
+              ui = (double)v.y;
+            } else {
+              ur = (double)state_load<true>(pr + src);
+              ui = (double)state_load<true>(pim + src);
+            }
+            const double c = __builtin_popcount(src & z) & 1 ? -pt.c : pt.c;
+            switch (ny) {   // i^{nY}
+              case 0: ar[k] += c * ur; ai[k] += c * ui; break;
+              case 1: ar[k] += c * -ui; ai[k] += c * ur; break;
+              case 2: ar[k] += c * -ur; ai[k] += c * -ui; break;
+              default: ar[k] += c * ui; ai[k] += c * -ur; break;
+            }
           }
-          if (__builtin_popcountll(src & z) & 1) { tr = -tr; ti = -ti; }
-          ar += c * tr;
-          ai += c * ti;
         }
-        lr[b] = (T)ar;
-        li[b] = (T)ai;
-        e += (double)pr[b] * ar + (double)pim[b] * ai;
-      }
-      e = wave_sum(e);
-      if ((tid & 63) == 0) wred[tid >> 6] = e;
-      __syncthreads();
-      e = 0.0;
-      for (int w = 0; w < NWAVE; w++) e += wred[w];
-    }
-    __syncthreads();
-
-    // ---- backward: two-state sweeps; each gradient term is summed over the
-    // wave, then added to the wave's LDS row of its slot (in tile and stage
-    // order: deterministic), and the rows are summed per sweep
-    for (int s = 0; s < q.b_nsweeps; s++) {
-      const SVI_CONST SweepArgs &a = cptr(sa.sweeps)[q.b_sweep + s];
-      const int m = a.m, c = a.c, nh = a.nh;
-      const int ntile_el = 1 << m;
-      const int nst = a.stage_end - a.stage_begin;
-      const SVI_CONST StageDesc *stages = cptr(a.stages + a.stage_begin);
-      const SVI_CONST double *coef = cptr(a.coef);
-      T *const pr[2] = {(T *)a.re, (T *)a.re2};
-      T *const pi[2] = {(T *)a.im, (T *)a.im2};
-      if (tid < SVI_MMAX) hb_s[tid] = a.hb[tid < nh ? tid : 0];
-      for (int k = tid; k < NWAVE * SVI_GSLOTS_MAX; k += NT) (&wacc[0][0])[k] = 0.0;
-      __syncthreads();
-      const bool active = tid < (1 << (m > R ? m - R : 0));
-      for (int64_t tile = 0; tile < a.ntiles; tile++) {
-        const uint64_t base = tile_base(tile, c, hb_s, nh);
-        for (int st2 = 0; st2 < 2; st2++)
-          for (int i = tid; i < ntile_el; i += NT) {
-            const uint64_t g = base + spread_row(i >> c, hb_s, nh) + (uint64_t)(i & ((1 << c) - 1));
-            lt[st2 * (1 << M) + swz<T>(i)] = C2{pr[st2][g], pi[st2][g]};
+        double e = 0.0;
+#pragma unroll
+        for (int k = 0; k < G; k++) {
+          const int i = tid + k * NT;
+          if (i >= N1) continue;
+          e += (double)sr[k] * ar[k] + (double)si[k] * ai[k];
+          if (whole) {
+            ll[swz<T>(i)] = C2{(T)ar[k], (T)ai[k]};
+          } else {
+            state_store<true>((T *)q.lre + b0 + i, (T)ar[k]);
+            state_store<true>((T *)q.lim + b0 + i, (T)ai[k]);
           }
-        __syncthreads();
-        for (int st = 0; st < nst; st++) {
-          const SVI_CONST StageDesc &sd = stages[st];
-          const int gbs = (swz<T>(lane_base(tid & 63, sd)) ^ swz<T>(wave_base<M, R>(wave, sd))) *
-                          (int)sizeof(C2);
-          auto sink = [&](int s0, int s1, double t) {
-            wave_deposit2(wacc[tid >> 6], s0, s1, t, tid & 63);
-          };
-          if (!GEN || sd.kind == ST_KRON)
-            kron2_stage<T, R>((char *)lt, (char *)(lt + (1 << M)), gbs, sd, coef, a.ops, a.coef, active,
-                              sink);
-          else if constexpr (GEN)
-            ops2_stage<T, R>((char *)lt, (char *)(lt + (1 << M)), gbs, sd, a.ops, a.coef, active, sink);
         }
-        for (int st2 = 0; st2 < 2; st2++)
-          for (int i = tid; i < ntile_el; i += NT) {
-            const uint64_t g = base + spread_row(i >> c, hb_s, nh) + (uint64_t)(i & ((1 << c) - 1));
-            const C2 p = lt[st2 * (1 << M) + swz<T>(i)];
-            pr[st2][g] = p.x;
-            pi[st2][g] = p.y;
-          }
+        e = wave_sum(e);
+        if ((tid & 63) == 0) wred[tid >> 6] = e;
+        __syncthreads();
+        if (tid == 0) {
+          e = 0.0;
+          for (int w = 0; w < NWAVE; w++) e += wred[w];
+          state_store<true>(q.epart + (whole ? 0 : un.tile), e);
+        }
+        __syncthreads();
+      } else if (ph <= nf + nb) {
+        // ---- backward: two-state sweeps; each gradient term is summed over
+        // the wave, then added to the wave's LDS row of its slot (in stage
+        // order: deterministic), and the rows are summed per sweep and tile
+        const SVI_CONST SweepArgs &a = cptr(sa.sweeps)[q.b_sweep + ph - nf - 1];
+        double *slots = q.slots + (whole ? 0 : (int64_t)un.tile * q.n_gslots);
+        const ServeTile<T> io(a, whole ? 0 : un.tile);
+        if (!whole) {
+          io.template load<NT, G>((const T *)a.re, (const T *)a.im, lt);
+          io.template load<NT, G>((const T *)a.re2, (const T *)a.im2, ll);
+        }
+        serve_backward<T, M, R, GEN>(a, lt, wacc, slots);
+        if (!whole) {
+          io.template store<NT, G>((T *)a.re, (T *)a.im, lt);
+          io.template store<NT, G>((T *)a.re2, (T *)a.im2, ll);
+          __syncthreads();
+        }
+      } else {
+        // ---- E and dE/dtheta_p: the parameter's slots in slot order, each
+        // summed over the tiles in tile order
+        if (whole) {
+          stores_done();   // this workgroup's slot sums
+          __syncthreads();
+        }
+        const bool bad = __builtin_amdgcn_readfirstlane(__hip_atomic_load(
+                             q.ctl + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) != 0;
+        const double nan = __builtin_nan("");
+        for (int p = tid; p < q.n_params; p += NT) {
+          double g = 0.0;
+          for (int k = q.rowptr[p]; k < q.rowptr[p + 1]; k++)
+            for (int t = 0; t < q.n_tiles; t++)
+              g += state_load<true>(q.slots + (int64_t)t * q.n_gslots + q.gslots[k]);
+          q.out[1 + p] = bad ? nan : g;
+        }
+        if (tid == 0) {
+          double e = 0.0;
+          for (int t = 0; t < q.n_tiles; t++) e += state_load<true>(q.epart + t);
+          q.out[0] = bad ? nan : e;
+        }
         __syncthreads();
       }
-      for (int sl = tid; sl < a.n_gslots; sl += NT) {
-        double v = 0.0;
-        for (int w = 0; w < NWAVE; w++) v += wacc[w][sl];
-        q.slots[a.gslot_begin + sl] = v;
-      }
+    }
+    if (!whole) {
+      // this wave's stores are in memory before the count
+      stores_done();
       __syncthreads();
+      if (wave0) __hip_atomic_fetch_add(q.ctl, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-
-    // ---- dE/dtheta_p: the parameter's slots in slot order
-    for (int p = tid; p < q.n_params; p += NT) {
-      double g = 0.0;
-      for (int k = q.rowptr[p]; k < q.rowptr[p + 1]; k++) g += q.slots[q.gslots[k]];
-      q.out[1 + p] = g;
-    }
-    if (tid == 0) q.out[0] = e;
-    __syncthreads();
   }
 }
 
 }  // namespace
 
 // Requests of up to 16 qubits: beyond the 12-qubit tile a request's planes
-// (at most 4 x 512 KiB) stay in the L2 and last-level caches between sweeps.
+// (at most 4 x 512 KiB) stay in the last-level cache between sweeps.
 int svk_serve_max_qubits() { return 16; }
 
 hipError_t svk_launch_serve_coefs(const ServeReq *d_reqs, int nreq, int max_desc, hipStream_t s) {
@@ -2052,14 +2208,8 @@ hipError_t svk_launch_serve_coefs(const ServeReq *d_reqs, int nreq, int max_desc
   return hipGetLastError();
 }
 
-hipError_t svk_launch_serve(const ServeReq *d_reqs, const SweepArgs *d_sweeps, int32_t *d_head,
-                            int nreq, int general, int grid, hipStream_t s) {
-  if (nreq <= 0) return hipSuccess;
-  ServeArgs a;
-  a.reqs = d_reqs;
-  a.sweeps = d_sweeps;
-  a.head = d_head;
-  a.nreq = nreq;
+hipError_t svk_launch_serve(const ServeArgs &a, int general, int grid, hipStream_t s) {
+  if (a.nunits <= 0) return hipSuccess;
   if (general)
     hipLaunchKernelGGL((k_serve<double, SVS_M, SVS_R, true>), dim3(grid), dim3(1 << (SVS_M - SVS_R)), 0,
                        s, a);
