@@ -896,6 +896,8 @@ static void emit_sweep(Plan &P, std::vector<GateRec> &recs, const SweepP &sw, in
   }
   a.ntiles = (int64_t)1 << (n - sw.m);
   a.stage_begin = (int)P.stages.size();
+  a.op_begin = (int)P.ops.size();
+  a.coef_begin = P.ncoef;
   a.gslot_begin = gslot_base;
   int gs = 0;
   std::vector<int> st_gmask, st_xbits;   // per stage: group bits, exchanged bits
@@ -1190,6 +1192,8 @@ static void emit_sweep(Plan &P, std::vector<GateRec> &recs, const SweepP &sw, in
     P.n_blocks++;
   }
   a.stage_end = (int)P.stages.size();
+  a.op_end = (int)P.ops.size();
+  a.coef_end = P.ncoef;
   assign_thread_maps(P, a.stage_begin, st_gmask, st_xbits, R, std::max(sw.m, R));
   a.n_gslots = gs;
   // the two-state Kronecker kernel takes at most SVI_GSLOTS_MAX gradient slots per sweep

@@ -137,6 +137,8 @@ struct SweepArgs {
   int32_t nh;                // m - c
   int32_t hb[SVI_MMAX];      // qubit index of tile bit c+k (ascending)
   int32_t stage_begin, stage_end;
+  int32_t op_begin, op_end;      // micro-ops and coefficients (doubles) of the stages
+  int32_t coef_begin, coef_end;
   int32_t flags;             // SW_INIT_ZERO ...
   int32_t gslot_begin, n_gslots;  // adjoint: gradient slots used by this sweep
   int64_t ntiles;

@@ -2050,11 +2050,13 @@ __global__ void __launch_bounds__(1 << (M - R)) k_serve(ServeArgs sa) {
           io.zero((T *)a.re, NT, G);
           io.zero((T *)a.im, NT, G);
         } else {
+          const int warm = warm_sweep<NT>(a);
           if (init0) {
             for (int i = tid; i < N1; i += NT) lt[swz<T>(i)] = C2{i == 0 ? (T)1 : (T)0, 0};
           } else if (!whole) {
             io.template load<NT, G>((const T *)a.re, (const T *)a.im, lt);
           }
+          asm volatile("" ::"v"(warm));
           __syncthreads();
           tile_stages<T, M, R, !GEN>(a, lt);
           // (a state of one tile stays in LDS)
@@ -2150,10 +2152,12 @@ __global__ void __launch_bounds__(1 << (M - R)) k_serve(ServeArgs sa) {
         const SVI_CONST SweepArgs &a = cptr(sa.sweeps)[q.b_sweep + ph - nf - 1];
         double *slots = q.slots + (whole ? 0 : (int64_t)un.tile * q.n_gslots);
         const ServeTile<T> io(a, whole ? 0 : un.tile);
+        const int warm = warm_sweep<NT>(a);
         if (!whole) {
           io.template load<NT, G>((const T *)a.re, (const T *)a.im, lt);
           io.template load<NT, G>((const T *)a.re2, (const T *)a.im2, ll);
         }
+        asm volatile("" ::"v"(warm));
         serve_backward<T, M, R, GEN>(a, lt, wacc, slots);
         if (!whole) {
           io.template store<NT, G>((T *)a.re, (T *)a.im, lt);
