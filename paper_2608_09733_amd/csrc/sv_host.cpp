@@ -1357,6 +1357,7 @@ static sv_status ensure_scratch(sv_state *st, size_t bytes) {
     HIPCHK(hipStreamSynchronize(st->stream));
     HIPCHK(hipFree(st->scratch));
     st->scratch = nullptr;
+    st->scratch_bytes = 0;
   }
   size_t b = std::max(bytes, (size_t)1 << 20);
   HIPCHK(hipMalloc(&st->scratch, b));
@@ -2665,6 +2666,7 @@ extern "C" sv_status sv_adjoint_grad_device(sv_state *st, const sv_op *ops, int3
 // prefix, the samples, then `extra_bytes` for the caller.
 struct SampleScratch {
   double *QE = nullptr;
+  double *R = nullptr;
   uint64_t *samples = nullptr;
   void *extra = nullptr;
 };
@@ -2672,12 +2674,20 @@ struct SampleScratch {
 static sv_status sample_scratch(sv_state *st, int64_t shots, size_t extra_bytes, SampleScratch &sc) {
   const int64_t K = sample_K(st->n), J = K / (K < 1024 ? K : 1024);
   const size_t qe_bytes = (((size_t)(2 * J + 1) * 8) + 255) & ~(size_t)255;
+  size_t run_bytes = (svk_sampling_run_bytes(st->dtype == SV_C128, st->n, shots) + 255) & ~(size_t)255;
   const size_t smp_bytes = ((size_t)shots * 8 + 255) & ~(size_t)255;
-  sv_status s = ensure_scratch(st, qe_bytes + smp_bytes + extra_bytes + 1024);
+  const size_t rest = qe_bytes + smp_bytes + extra_bytes + 1024;
+  sv_status s = ensure_scratch(st, rest + run_bytes);
+  if (s && run_bytes) {   // no room for the running sums: draw without them
+    (void)hipGetLastError();
+    run_bytes = 0;
+    s = ensure_scratch(st, rest);
+  }
   if (s) return s;
   sc.QE = (double *)st->scratch;
-  sc.samples = (uint64_t *)((char *)st->scratch + qe_bytes);
-  sc.extra = (char *)st->scratch + qe_bytes + smp_bytes;
+  sc.R = run_bytes ? (double *)((char *)st->scratch + qe_bytes) : nullptr;
+  sc.samples = (uint64_t *)((char *)st->scratch + qe_bytes + run_bytes);
+  sc.extra = (char *)st->scratch + qe_bytes + run_bytes + smp_bytes;
   return SV_OK;
 }
 
@@ -2686,7 +2696,7 @@ static sv_status sample_on_device(sv_state *st, const void *re, const void *im, 
   double *S, *P;
   void *a, *b, *c, *d;
   ws_layout(st, &S, &P, &a, &b, &c, &d);
-  hipError_t e = svk_launch_sampling(st->dtype == SV_C128, re, im, st->n, S, P, sc.QE, seed, shots,
+  hipError_t e = svk_launch_sampling(st->dtype == SV_C128, re, im, st->n, S, P, sc.QE, sc.R, seed, shots,
                                      qubits, nq, sc.samples, st->stream);
   if (e != hipSuccess) return fail(SV_EDEVICE, "sampling: %s", hipGetErrorString(e));
   return SV_OK;

@@ -1159,6 +1159,13 @@ __device__ __forceinline__ double prob_at(const T *re, const T *im, uint64_t b) 
   return __fma_rn(x, x, y * y);
 }
 
+// Orders a wave's LDS accesses (no barrier: LDS serves them in order).
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 template <typename T>
 __global__ void __launch_bounds__(256) k_chunk_sums(const T *re, const T *im, int cbits, int64_t K,
                                                     double *S) {
@@ -1200,7 +1207,6 @@ __device__ __forceinline__ double chain_lds(const double *v, double *w, int len,
   return acc;
 }
 
-// One wave per block of G chunk sums: P[jG + i] <- L, Q[j] <- block total.
 // Chunk sums for 1024-amplitude chunks, one wave per chunk and no LDS: lane l
 // reads amplitudes 128 j + 2 l, +1 of each of the chunk's eight 128-wide
 // slabs (coalesced), adds each pair (tree level 1), combines adjacent blocks
@@ -1228,6 +1234,105 @@ __global__ void __launch_bounds__(256) k_chunk_sums_wave(const T *re, const T *i
   }
 }
 
+// Chunk sums and, for the draws, each 1024-amplitude chunk's left-to-right
+// running sum after every 64 amplitudes (R[16 k + j], j < 16), in one read of
+// the state.  A wave takes CH chunks, E = 1024 / CH amplitudes of each per step:
+// lanes on consecutive amplitudes load (the next step's loads are issued before
+// this step's sums), the probabilities pass through LDS, 64 / CH lanes per chunk
+// add their 16 pairwise and combine across lanes (the levels of k_chunk_sums'
+// tree below E), and one lane per chunk continues its running sum.  HBM-bound:
+// 5.0 TB/s at 30 qubits with 4 chunks per wave (8: 4.9, 16: 4.8).
+#define SVI_RUNS 16
+
+template <typename T, int CH>
+__global__ void __launch_bounds__(256) k_chunk_runs(const T *re, const T *im, int64_t K, double *S,
+                                                    double *R) {
+  typedef T V2 __attribute__((ext_vector_type(2)));
+  constexpr int E = 1024 / CH, LPC = 64 / CH, NP = E / 2;   // NP: pairs per chunk and step
+  constexpr int ROW = E + 2;           // doubles per chunk and step, padded
+  __shared__ double lds[4][CH * ROW];
+  __shared__ double sub[4][CH * (CH + 1)];   // sums of E amplitudes: [chunk][step]
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  double *const v = lds[w], *const u = sub[w];
+  const int64_t ng = (K + CH - 1) / CH;
+  for (int64_t g = (int64_t)blockIdx.x * 4 + w; g < ng; g += (int64_t)gridDim.x * 4) {
+    const int64_t k0 = g * CH;
+    const int nc = (int)(K - k0 < CH ? K - k0 : CH);
+    V2 x[8], y[8];
+    // pair q = 64 i + lane of a step: chunk q / NP, amplitudes 2 (q % NP), + 1
+    auto fetch = [&](int j) {
+#pragma unroll
+      for (int i = 0; i < 8; i++) {
+        const int q = 64 * i + lane, ch = q / NP;
+        const int64_t b = (k0 + (ch < nc ? ch : 0)) * 1024 + j * E + 2 * (q % NP);
+        x[i] = *(const V2 *)(re + b);
+        y[i] = *(const V2 *)(im + b);
+      }
+    };
+    fetch(0);
+    double acc = 0.0;
+    for (int j = 0; j < CH; j++) {
+#pragma unroll
+      for (int i = 0; i < 8; i++) {
+        const int q = 64 * i + lane;
+        const double x0 = (double)x[i].x, y0 = (double)y[i].x;
+        const double x1 = (double)x[i].y, y1 = (double)y[i].y;
+        double2 p;
+        p.x = __fma_rn(x0, x0, y0 * y0);
+        p.y = __fma_rn(x1, x1, y1 * y1);
+        *(double2 *)(v + (q / NP) * ROW + 2 * (q % NP)) = p;
+      }
+      if (j + 1 < CH) fetch(j + 1);
+      wave_lds_fence();
+      {
+        // lane LPC c + q: amplitudes 16 q .. 16 q + 15 of chunk c
+        const double *r = v + (lane / LPC) * ROW + 16 * (lane % LPC);
+        double t[8];
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+          const double2 p = *(const double2 *)(r + 2 * i);
+          t[i] = p.x + p.y;
+        }
+        double s16 = ((t[0] + t[1]) + (t[2] + t[3])) + ((t[4] + t[5]) + (t[6] + t[7]));
+#pragma unroll
+        for (int d = 1; d < LPC; d <<= 1) s16 = s16 + __shfl_down(s16, d);
+        if (lane % LPC == 0) u[(lane / LPC) * (CH + 1) + j] = s16;
+      }
+      if (lane < CH) {
+        const double *r = v + lane * ROW;
+        for (int e0 = 0; e0 < E; e0 += 64) {
+#pragma unroll
+          for (int i0 = 0; i0 < 64; i0 += 16) {
+            double2 p[8];
+#pragma unroll
+            for (int i = 0; i < 8; i++) p[i] = *(const double2 *)(r + e0 + i0 + 2 * i);
+#pragma unroll
+            for (int i = 0; i < 8; i++) {
+              acc = acc + p[i].x;
+              acc = acc + p[i].y;
+            }
+          }
+          if (lane < nc) R[(k0 + lane) * SVI_RUNS + (j * E + e0) / 64] = acc;
+        }
+      }
+      wave_lds_fence();
+    }
+    if (lane < nc) {
+      const double *r = u + lane * (CH + 1);
+      double t[CH];
+#pragma unroll
+      for (int i = 0; i < CH; i++) t[i] = r[i];
+#pragma unroll
+      for (int h = CH / 2; h >= 1; h >>= 1)
+#pragma unroll
+        for (int i = 0; i < h; i++) t[i] = t[2 * i] + t[2 * i + 1];
+      S[k0 + lane] = t[0];
+    }
+    wave_lds_fence();
+  }
+}
+
+// One wave per block of G chunk sums: P[jG + i] <- L, Q[j] <- block total.
 __global__ void __launch_bounds__(64) k_prefix_local(const double *S, int G, double *P, double *Q) {
   __shared__ double v[1024], w[1024];
   const int64_t base = (int64_t)blockIdx.x * G;
@@ -1277,6 +1382,7 @@ __device__ __forceinline__ uint64_t splitmix64(uint64_t seed, uint64_t s) {
 struct SampleArgs {
   const void *re, *im;
   const double *S, *P;
+  const double *R;     // running sums inside the chunks (k_chunk_runs)
   int64_t K;
   int32_t cbits;
   int32_t nq;
@@ -1342,7 +1448,64 @@ __global__ void __launch_bounds__(256) k_sample(SampleArgs a) {
   }
 }
 
-// FP64 draws with chunks of >= 8 amplitudes, done cooperatively: the 64
+// Draws with the running sums of k_chunk_runs: the first run whose sum exceeds
+// the remainder holds the drawn index (the running sums never decrease), and
+// the same left-to-right accumulation goes on from the run before.  A shot
+// reads at most 64 amplitudes instead of half a chunk on the mean.
+template <typename T>
+__global__ void __launch_bounds__(256) k_sample_runs(SampleArgs a) {
+  const T *re = (const T *)a.re, *im = (const T *)a.im;
+  const double Tot = a.P[a.K];
+  for (int64_t s = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; s < a.shots;
+       s += (int64_t)gridDim.x * blockDim.x) {
+    const double u = (double)(splitmix64(a.seed, (uint64_t)s) >> 11) * 0x1.0p-53;
+    const double t = u * Tot;
+    // first k with P[k+1] > t (P non-decreasing)
+    int64_t lo = 0, hi = a.K;   // answer in [0, K]; K means none
+    while (lo < hi) {
+      const int64_t mid = (lo + hi) >> 1;
+      if (a.P[mid + 1] > t) hi = mid; else lo = mid + 1;
+    }
+    int64_t ks = lo;
+    if (ks >= a.K) {
+      ks = -1;
+      for (int64_t k = a.K - 1; k >= 0; k--)
+        if (a.S[k] > 0.0) { ks = k; break; }
+      if (ks < 0) ks = 0;
+    }
+    const double r = t - a.P[ks];
+    const double *run = a.R + ks * SVI_RUNS;
+    int j0 = 0, j1 = SVI_RUNS;   // first run j with run[j] > r; SVI_RUNS means none
+    while (j0 < j1) {
+      const int mid = (j0 + j1) >> 1;
+      if (run[mid] > r) j1 = mid; else j0 = mid + 1;
+    }
+    // none: the chunk's last nonzero amplitude, found by the full walk
+    const int64_t b0 = ks * 1024;
+    const bool none = j0 == SVI_RUNS;
+    const int i_lo = none ? 0 : 64 * j0, i_hi = none ? 1024 : 64 * j0 + 64;
+    double acc = none || j0 == 0 ? 0.0 : run[j0 - 1];
+    int64_t pick = -1, lastpos = -1;
+    for (int i0 = i_lo; i0 < i_hi && pick < 0; i0 += 16) {
+      double p[16];
+#pragma unroll
+      for (int j = 0; j < 16; j++) p[j] = prob_at(re, im, (uint64_t)(b0 + i0 + j));
+#pragma unroll
+      for (int j = 0; j < 16; j++)
+        if (pick < 0) {
+          acc = acc + p[j];
+          if (p[j] > 0.0) lastpos = b0 + i0 + j;
+          if (acc > r) pick = b0 + i0 + j;
+        }
+    }
+    if (pick < 0) pick = lastpos >= 0 ? lastpos : b0;
+    uint64_t o = 0;
+    for (int i = 0; i < a.nq; i++) o |= (((uint64_t)pick >> a.qubits[i]) & 1ull) << i;
+    a.out[s] = o;
+  }
+}
+
+// FP64 draws with chunks of >= 8 amplitudes without running sums, done cooperatively: the 64
 // shots of a wave walk their chunks together, 8 amplitudes per shot per step.
 // Eight lanes fetch one shot's 8 re and 8 im values as 16-byte pieces (a
 // 64-byte run per plane, so a load instruction covers 8 shots' runs instead
@@ -1735,13 +1898,30 @@ hipError_t svk_launch_energy_terms(const double *vals, const PauliTermDev *terms
   return hipGetLastError();
 }
 
+// The running sums cost the one read of the state its last 15% of bandwidth
+// (30 qubits: 3.4 against 2.9 ms) and save each shot the walk through half a
+// chunk, so a state of 8 GiB or more takes them from a quarter as many shots as
+// chunks (30 qubits, 1000 shots: 3.16 ms without, 3.59 with; 2^20 shots: 4.80
+// and 4.45), a smaller one always (27 qubits: 0.61 and 0.51, 3.03 and 1.24).
+size_t svk_sampling_run_bytes(int dbl, int n, int64_t shots) {
+  if (n < 10) return 0;   // chunks of fewer than 1024 amplitudes
+  const int64_t K = 1ll << (n - 10);
+  if (((int64_t)(dbl ? 16 : 8) << n) >= (1ll << 33) && shots < K / 4) return 0;
+  return (size_t)K * SVI_RUNS * 8;
+}
+
 hipError_t svk_launch_sampling(int dbl, const void *re, const void *im, int n, double *S, double *P,
-                               double *QE, uint64_t seed, int64_t shots, const int32_t *qubits,
-                               int nq, uint64_t *out, hipStream_t s) {
+                               double *QE, double *R, uint64_t seed, int64_t shots,
+                               const int32_t *qubits, int nq, uint64_t *out, hipStream_t s) {
   const int cbits = n < 10 ? n : 10;
   const int64_t K = (1ll << n) >> cbits;
   int grid = (int)(K < 4096 ? K : 4096);
-  if (cbits == 10) {
+  const bool runs = R != nullptr;
+  if (runs) {
+    const int gw = (int)std::min<int64_t>((K + 15) / 16, 8192);   // 4 chunks per wave
+    if (dbl) hipLaunchKernelGGL((k_chunk_runs<double, 4>), dim3(gw), dim3(256), 0, s, (const double *)re, (const double *)im, K, S, R);
+    else hipLaunchKernelGGL((k_chunk_runs<float, 4>), dim3(gw), dim3(256), 0, s, (const float *)re, (const float *)im, K, S, R);
+  } else if (cbits == 10) {
     const int gw = (int)std::min<int64_t>((K + 3) / 4, 8192);
     if (dbl) hipLaunchKernelGGL(k_chunk_sums_wave<double>, dim3(gw), dim3(256), 0, s, (const double *)re, (const double *)im, K, S);
     else hipLaunchKernelGGL(k_chunk_sums_wave<float>, dim3(gw), dim3(256), 0, s, (const float *)re, (const float *)im, K, S);
@@ -1762,17 +1942,23 @@ hipError_t svk_launch_sampling(int dbl, const void *re, const void *im, int n, d
   if (e != hipSuccess) return e;
   if (shots <= 0) return hipSuccess;
   SampleArgs a;
-  a.re = re; a.im = im; a.S = S; a.P = P; a.K = K; a.cbits = cbits; a.nq = nq;
+  a.re = re; a.im = im; a.S = S; a.P = P; a.R = R; a.K = K; a.cbits = cbits; a.nq = nq;
   for (int i = 0; i < 64; i++) a.qubits[i] = i < nq ? qubits[i] : 0;
   a.seed = seed; a.shots = shots; a.out = out;
   int64_t blocks = (shots + 255) / 256;
   int g2 = (int)(blocks < 4096 ? blocks : 4096);
-  // both kernels draw the same indices; the cooperative one pays off once
-  // there are enough waves to keep the memory system busy
-  if (dbl && cbits >= 3 && shots >= 4096)
+  if (runs) {
+    if (dbl) hipLaunchKernelGGL(k_sample_runs<double>, dim3(g2), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL(k_sample_runs<float>, dim3(g2), dim3(256), 0, s, a);
+  } else if (dbl && cbits == 10 && shots >= 4096) {
+    // the cooperative draws pay off once there are enough waves to keep the
+    // memory system busy
     hipLaunchKernelGGL(k_sample_coop, dim3(g2), dim3(256), 0, s, a);
-  else if (dbl) hipLaunchKernelGGL(k_sample<double>, dim3(g2), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(k_sample<float>, dim3(g2), dim3(256), 0, s, a);
+  } else if (dbl) {
+    hipLaunchKernelGGL(k_sample<double>, dim3(g2), dim3(256), 0, s, a);
+  } else {
+    hipLaunchKernelGGL(k_sample<float>, dim3(g2), dim3(256), 0, s, a);
+  }
   return hipGetLastError();
 }
 

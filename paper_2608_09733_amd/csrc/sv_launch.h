@@ -63,9 +63,12 @@ hipError_t svk_launch_energy_terms(const double *vals, const PauliTermDev *terms
                                    double *out, hipStream_t s);
 hipError_t svk_launch_energy(const double *terms, const double *coef, int nt, double *out,
                              hipStream_t s);
-// QE: 2 * (K / min(K, 1024)) + 1 doubles of device scratch (block totals and offsets).
+// QE: 2 * (K / min(K, 1024)) + 1 doubles of device scratch (block totals and
+// offsets); R: running sums inside the chunks (svk_sampling_run_bytes of device
+// scratch), or NULL to draw without.
+size_t svk_sampling_run_bytes(int dbl, int n, int64_t shots);
 hipError_t svk_launch_sampling(int dbl, const void *re, const void *im, int n, double *S,
-                               double *P, double *QE, uint64_t seed, int64_t shots,
+                               double *P, double *QE, double *R, uint64_t seed, int64_t shots,
                                const int32_t *qubits, int nq, uint64_t *out, hipStream_t s);
 
 // counts[0 .. 2^nq) <- histogram of samples (zeroed first)
