@@ -95,10 +95,13 @@ struct GateRec {
   int nt = 0;
   int t[5] = {0, 0, 0, 0, 0};
   int nc = 0;
-  int c[5] = {0, 0, 0, 0, 0};
+  int c[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   uint32_t cs = 0;
   int pidx[3] = {-1, -1, -1};
   uint64_t qmask = 0;        // targets | controls
+  // Controls that need not be in the register group (dense-stage plans): the
+  // gate runs in the threads whose index has pval on these qubits.
+  uint64_t pmask = 0, pval = 0;
   int mo = MO_NOP;
   int coef_kind = 0;         // kind used to build the coefficients
   int fmt = 0;               // CF_* (0 = none)
@@ -211,7 +214,7 @@ static bool generator_of(const GateRec &g, uint64_t &x, uint64_t &z, double &alp
 struct StageP {
   std::vector<int> recs;      // indices into the record list, program order
   int gq[SVI_RMAX];           // tile-local position of group bit i
-  bool dense = false;
+  bool dense = false;         // one record's dense matrix; Tiling::dense: the stage's matrix
   bool kron = false;          // canonical Kronecker stage
   std::vector<int> lead, dbefore, rops, dafter, trail;   // kron: records by role
 };
@@ -235,6 +238,7 @@ static bool is_diag(const GateRec &g) { return g.mo == MO_P || g.mo == MO_NEG; }
 // that follow a rotation), Y on the rotated qubit for an RY (evaluated after the
 // leading diagonal table; the other rotations act on other qubits).
 static bool kron_eligible(const GateRec &g) {
+  if (g.pmask) return false;
   if (g.mo == MO_R) return g.nc == 0 && g.nt == 1 && g.kind == SV_RY;
   if (g.grad) return g.mo == MO_P && g.gx == 0;
   return g.mo == MO_P || g.mo == MO_NEG || g.mo == MO_X || g.mo == MO_SWAP;
@@ -300,6 +304,7 @@ struct SweepP {
 
 struct Tiling {
   int M = 13, c = 3, R = 5;
+  bool dense = false;         // stages that are no Kronecker stage run as dense matrices
 };
 
 static int popc(uint64_t v) { return __builtin_popcountll(v); }
@@ -382,12 +387,18 @@ static uint64_t tile_mask(const SweepP &sw) {
 }
 
 // Split one sweep's records into register stages of <= R qubits.
+// dense: a stage that is no Kronecker stage becomes one 2^R x 2^R matrix, which
+// takes every record inside its group; a record with controls outside its
+// group (pmask) is a stage of its own.
 static void plan_stages(const std::vector<GateRec> &recs, const std::vector<int> &take, SweepP &sw,
-                        int R, int n, bool allow_kron = false) {
+                        int R, int n, bool allow_kron = false, bool dense = false) {
   std::vector<char> done(recs.size(), 0);
   std::vector<char> veto(recs.size(), 0);
-  for (int r : take)
-    if (recs[r].mo == MO_DENSE) veto[r] = 1;
+  bool mixed = false;   // some record fits no Kronecker stage
+  for (int r : take) {
+    if (dense ? recs[r].pmask != 0 : recs[r].mo == MO_DENSE) veto[r] = 1;
+    mixed = mixed || !kron_eligible(recs[r]);
+  }
   const uint64_t Ttile = tile_mask(sw);
   size_t left = take.size();
   const int mm = std::max(sw.m, R);
@@ -397,31 +408,9 @@ static void plan_stages(const std::vector<GateRec> &recs, const std::vector<int>
       if (!done[r]) { first = r; break; }
     StageP st;
     std::vector<int> grp;   // qubits (global) in group order
-    if (allow_kron && kron_eligible(recs[first])) {
-      uint64_t S = recs[first].qmask;
-      while (popc(S) < R) {
-        int best = -1, bestv = closure_kron(recs, take, done, S, Ttile, nullptr);
-        for (int q = 0; q < n; q++) {
-          if (!(Ttile & (1ull << q)) || (S & (1ull << q))) continue;
-          int v = closure_kron(recs, take, done, S | (1ull << q), Ttile, nullptr);
-          if (v > bestv) { bestv = v; best = q; }
-        }
-        if (best < 0) break;
-        S |= 1ull << best;
-      }
-      st.kron = true;
-      closure_kron(recs, take, done, S, Ttile, &st);
-      for (int r : st.recs) { done[r] = 1; left--; }
-      for (int q = 0; q < n; q++)
-        if (S & (1ull << q)) grp.push_back(q);
-    } else if (recs[first].mo == MO_DENSE) {
-      st.dense = true;
-      st.recs.push_back(first);
-      done[first] = 1;
-      left--;
-      for (int i = 0; i < recs[first].nt; i++) grp.push_back(recs[first].t[i]);
-      for (int i = 0; i < recs[first].nc; i++) grp.push_back(recs[first].c[i]);
-    } else {
+    // register group around the first pending record, grown by the qubit that
+    // lets it take most records
+    auto grow = [&]() {
       uint64_t S = recs[first].qmask;
       while (popc(S) < R) {
         int best = -1, bestv = closure(recs, take, done, S, nullptr, &veto);
@@ -441,10 +430,68 @@ static void plan_stages(const std::vector<GateRec> &recs, const std::vector<int>
         }
         S |= 1ull << best;
       }
+      return S;
+    };
+    bool kron = allow_kron && kron_eligible(recs[first]);
+    if (kron && dense && mixed) {
+      // a dense stage costs about 1.3 Kronecker stages: taken if it holds more
+      // records for that (27 qubits, 200 mixed gates: 28.4 ms with 1.3 as with
+      // 1.8 and with 1, most sweeps being bound by memory)
+      StageP probe;
+      uint64_t S = recs[first].qmask;
+      while (popc(S) < R) {
+        int best = -1, bestv = closure_kron(recs, take, done, S, Ttile, nullptr);
+        for (int q = 0; q < n; q++) {
+          if (!(Ttile & (1ull << q)) || (S & (1ull << q))) continue;
+          int v = closure_kron(recs, take, done, S | (1ull << q), Ttile, nullptr);
+          if (v > bestv) { bestv = v; best = q; }
+        }
+        if (best < 0) break;
+        S |= 1ull << best;
+      }
+      closure_kron(recs, take, done, S, Ttile, &probe);
+      std::vector<int> got;
+      closure(recs, take, done, grow(), &got, &veto);
+      if (10 * got.size() > 13 * probe.recs.size()) kron = false;
+    }
+    if (kron) {
+      uint64_t S = recs[first].qmask;
+      while (popc(S) < R) {
+        int best = -1, bestv = closure_kron(recs, take, done, S, Ttile, nullptr);
+        for (int q = 0; q < n; q++) {
+          if (!(Ttile & (1ull << q)) || (S & (1ull << q))) continue;
+          int v = closure_kron(recs, take, done, S | (1ull << q), Ttile, nullptr);
+          if (v > bestv) { bestv = v; best = q; }
+        }
+        if (best < 0) break;
+        S |= 1ull << best;
+      }
+      st.kron = true;
+      closure_kron(recs, take, done, S, Ttile, &st);
+      for (int r : st.recs) { done[r] = 1; left--; }
+      for (int q = 0; q < n; q++)
+        if (S & (1ull << q)) grp.push_back(q);
+    } else if (dense && recs[first].pmask) {
+      st.dense = true;
+      st.recs.push_back(first);
+      done[first] = 1;
+      left--;
+      for (int q = 0; q < n; q++)
+        if ((recs[first].qmask & ~recs[first].pmask) >> q & 1) grp.push_back(q);
+    } else if (!dense && recs[first].mo == MO_DENSE) {
+      st.dense = true;
+      st.recs.push_back(first);
+      done[first] = 1;
+      left--;
+      for (int i = 0; i < recs[first].nt; i++) grp.push_back(recs[first].t[i]);
+      for (int i = 0; i < recs[first].nc; i++) grp.push_back(recs[first].c[i]);
+    } else {
+      const uint64_t S = grow();
       std::vector<int> got;
       closure(recs, take, done, S, &got, &veto);
       for (int r : got) { done[r] = 1; left--; }
       st.recs = got;
+      st.dense = dense;
       for (int q = 0; q < n; q++)
         if (S & (1ull << q)) grp.push_back(q);
     }
@@ -557,7 +604,7 @@ static void plan_auto(const std::vector<GateRec> &recs, int n, const Tiling &tl,
     }
     SweepP sw;
     set_tile(sw, n, T, c, occ.data());
-    plan_stages(recs, take, sw, tl.R, n, kron);
+    plan_stages(recs, take, sw, tl.R, n, kron, tl.dense);
     for (int r : take) { done[r] = 1; left--; }
     if (remap) {
       std::vector<int> want = occ;
@@ -701,7 +748,8 @@ static void plan_fused(const std::vector<GateRec> &recs, int n, const Tiling &tl
 
 struct Step {
   int kind = 0;              // 0 = tile sweep, 1 = single-gate kernel
-  bool all_kron = false;     // every stage is a Kronecker stage (lean kernel)
+  bool all_kron = false;     // every stage is a Kronecker or a dense stage (lean kernels)
+  bool has_dense = false;    // some stage is a dense stage
   SweepArgs sa{};            // tile sweep (pointers patched at launch)
   GateArgsHost ga{};         // single gate
   int gate_coef = -1;
@@ -711,6 +759,8 @@ struct Plan {
   int n = 0;
   bool dbl = true;
   int M = 13, R = 5, NS = 1;
+  bool dense = false;                // dense stages (Tiling::dense)
+  std::vector<DenseDesc> denses;
   std::vector<Step> steps;
   std::vector<StageDesc> stages;
   std::vector<MicroOp> ops;
@@ -733,6 +783,7 @@ struct Plan {
   MicroOp *d_ops = nullptr;
   CoefDesc *d_coefdesc = nullptr;
   TabFactor *d_factors = nullptr;
+  DenseDesc *d_denses = nullptr;
   double *d_coef = nullptr;
   double *d_params = nullptr;        // user params + constants
   double *d_statics = nullptr;
@@ -870,6 +921,15 @@ static void assign_thread_maps(Plan &P, int first, const std::vector<int> &gm,
     for (int p : lanes) sd.tpos[k++] = (int8_t)p;
     for (int p : lanep) sd.tpos[k++] = (int8_t)p;
     for (int p : w) sd.tpos[k++] = (int8_t)p;
+    if (sd.kind == ST_DENSE && sd.pm) {
+      uint32_t pm = 0, pv = 0;
+      for (int i = 0; i < k; i++) {
+        pm |= ((sd.pm >> sd.tpos[i]) & 1u) << i;
+        pv |= ((sd.pv >> sd.tpos[i]) & 1u) << i;
+      }
+      sd.pm = pm;
+      sd.pv = pv;
+    }
     for (; k < 16; k++) sd.tpos[k] = 0;
     wprev = w;
   }
@@ -918,6 +978,7 @@ static void emit_sweep(Plan &P, std::vector<GateRec> &recs, const SweepP &sw, in
       grad_mop.push_back(none);
       uint32_t cm = 0, cv = 0;
       for (int i = 0; i < g.nc; i++) {
+        if ((g.pmask >> g.c[i]) & 1) continue;   // the stage's condition on the thread
         int l = local_of(g.c[i]);
         cm |= 1u << l;
         if ((g.cs >> i) & 1u) cv |= 1u << l;
@@ -1026,7 +1087,11 @@ static void emit_sweep(Plan &P, std::vector<GateRec> &recs, const SweepP &sw, in
           op.t1 = (int)(pa ^ pb);
           break;
         }
-        case MO_DENSE: op.mask = g.nt; break;   // targets are group bits 0..k-1
+        case MO_DENSE:   // targets are group bits 0..k-1 (dense stages: any bits, in order)
+          op.mask = g.nt;
+          if (P.dense)
+            for (int i = 0; i < g.nt; i++) op.t0 |= local_of(g.t[i]) << (4 * i);
+          break;
         default: break;
       }
       mops.push_back(op);
@@ -1137,6 +1202,23 @@ static void emit_sweep(Plan &P, std::vector<GateRec> &recs, const SweepP &sw, in
         cd.dst = sd.kcoef + 4 * R + 4 * G;
         P.coefs.push_back(cd);
       }
+    } else if (P.dense) {
+      // the micro-ops become the stage's matrix (DenseDesc); pm and pv are the
+      // condition on tile bits here (assign_thread_maps: on thread-index bits)
+      sd.kind = ST_DENSE;
+      sd.op_begin = (int)P.ops.size();
+      for (const MicroOp &m : mops) P.ops.push_back(m);
+      sd.op_end = sd.g1 = sd.g2 = (int)P.ops.size();
+      sd.kcoef = P.ncoef;
+      P.ncoef += (2 << (2 * R)) + 2;
+      P.denses.push_back(DenseDesc{sd.op_begin, sd.op_end, sd.kcoef, 0});
+      const GateRec &g = recs[st.recs[0]];
+      for (int q = 0; q < n; q++)
+        if ((g.pmask >> q) & 1) {
+          const int p = tile_pos(sw, q);
+          sd.pm |= 1u << p;
+          if ((g.pval >> q) & 1) sd.pv |= 1u << p;
+        }
     } else {
       // fold leading / trailing permutations into the LDS offsets
       size_t lead = 0;
@@ -1198,8 +1280,10 @@ static void emit_sweep(Plan &P, std::vector<GateRec> &recs, const SweepP &sw, in
   a.n_gslots = gs;
   // the two-state Kronecker kernel takes at most SVI_GSLOTS_MAX gradient slots per sweep
   s.all_kron = gs <= SVI_GSLOTS_MAX;
-  for (int k = a.stage_begin; k < a.stage_end; k++)
-    if (P.stages[k].kind != ST_KRON) s.all_kron = false;
+  for (int k = a.stage_begin; k < a.stage_end; k++) {
+    if (P.stages[k].kind == ST_OPS) s.all_kron = false;
+    if (P.stages[k].kind == ST_DENSE) s.has_dense = true;
+  }
   gslots_used = gs;
   P.steps.push_back(s);
   P.n_sweeps++;
@@ -1247,7 +1331,8 @@ static sv_status upload_plan(Plan &P) {
   size_t o_ops = align(o_st + P.stages.size() * sizeof(StageDesc));
   size_t o_cd = align(o_ops + P.ops.size() * sizeof(MicroOp));
   size_t o_fa = align(o_cd + P.coefs.size() * sizeof(CoefDesc));
-  size_t o_cf = align(o_fa + (P.factors.size() + 1) * sizeof(TabFactor));
+  size_t o_de = align(o_fa + (P.factors.size() + 1) * sizeof(TabFactor));
+  size_t o_cf = align(o_de + P.denses.size() * sizeof(DenseDesc));
   size_t o_pa = align(o_cf + (size_t)std::max(P.ncoef, 1) * 8);
   size_t npar = (size_t)P.n_user_params + P.constants.size();
   size_t o_stc = align(o_pa + std::max<size_t>(npar, 1) * 8);
@@ -1264,6 +1349,9 @@ static sv_status upload_plan(Plan &P) {
   P.d_factors = (TabFactor *)(b + o_fa);
   if (!P.factors.empty())
     HIPCHK(hipMemcpy(P.d_factors, P.factors.data(), P.factors.size() * sizeof(TabFactor), hipMemcpyHostToDevice));
+  P.d_denses = (DenseDesc *)(b + o_de);
+  if (!P.denses.empty())
+    HIPCHK(hipMemcpy(P.d_denses, P.denses.data(), P.denses.size() * sizeof(DenseDesc), hipMemcpyHostToDevice));
   P.d_params = (double *)(b + o_pa);
   P.d_statics = (double *)(b + o_stc);
   P.d_rowptr = (int32_t *)(b + o_rp);
@@ -1541,7 +1629,8 @@ static std::string plan_key(int mode, int n, const Tiling &tl, bool dbl, const s
   std::string k;
   k.reserve(64 + (size_t)n_ops * 24);
   char buf[96];
-  snprintf(buf, sizeof buf, "%d|%d|%d,%d,%d|%d|%d|", mode, n, tl.M, tl.c, tl.R, (int)dbl, n_params);
+  snprintf(buf, sizeof buf, "%d|%d|%d,%d,%d,%d|%d|%d|", mode, n, tl.M, tl.c, tl.R, (int)tl.dense,
+           (int)dbl, n_params);
   k += buf;
   for (int i = 0; i < n_ops; i++) {
     const sv_op &o = ops[i];
@@ -1582,7 +1671,11 @@ static void collect_user_mats(Plan &P, const sv_op *ops, int n_ops) {
 static double plan_model(const std::vector<SweepP> &sweeps, int R) {
   const double w = R <= 3 ? 1.0 : R == 4 ? 1.2 : 1.6;
   double t = 0.0;
-  for (const SweepP &sw : sweeps) t += std::max(11.0, 5.3 + w * (double)sw.stages.size());
+  for (const SweepP &sw : sweeps) {
+    double s = 0.0;
+    for (const StageP &st : sw.stages) s += st.dense ? 1.3 * w : w;
+    t += std::max(11.0, 5.3 + s);
+  }
   return t;
 }
 
@@ -1633,6 +1726,7 @@ static sv_status build_forward_plan(int mode, int n, bool dbl, const Tiling &tl,
   P.M = tl.M;
   P.R = tl.R;
   P.NS = 1;
+  P.dense = tl.dense;
   P.n_user_params = n_params;
   collect_user_mats(P, ops, n_ops);
   std::vector<GateRec> recs;
@@ -1644,6 +1738,14 @@ static sv_status build_forward_plan(int mode, int n, bool dbl, const Tiling &tl,
       half_pi = n_params + (int)P.constants.size() - 1;
     }
     return half_pi;
+  };
+  // dense stages: a gate on more qubits than a group holds keeps its targets
+  // and as many controls as fit; the other controls become its condition
+  auto to_group = [&](GateRec &g) {
+    for (int i = g.nc - 1; i >= 0 && popc(g.qmask & ~g.pmask) > tl.R; i--) {
+      g.pmask |= 1ull << g.c[i];
+      if ((g.cs >> i) & 1u) g.pval |= 1ull << g.c[i];
+    }
   };
   // one-qubit record of `kind` on qubit q, parameter slot p
   auto push1 = [&](int kind, int q, int p) {
@@ -1681,9 +1783,40 @@ static sv_status build_forward_plan(int mode, int n, bool dbl, const Tiling &tl,
       }
       if (split) continue;
     }
+    if (tl.dense && op.kind == SV_DEXC) {
+      // The rotated patterns 3 and 12 differ in all four targets: with
+      // CX(t0 -> t1), CX(t0 -> t2), CX(t0 -> t3) before and after, it is the
+      // rotation of t0 between them, controlled by t1 = 0, t2 = 1, t3 = 1
+      // (pattern 3 has t0 = 1 there, so the angle's sign turns).
+      sv_op x{};
+      x.kind = SV_X;
+      x.n_targets = x.n_controls = 1;
+      x.controls[0] = op.targets[0];
+      x.control_states = 1;
+      auto cxs = [&]() {
+        for (int k = 1; k < 4; k++) {
+          x.targets[0] = op.targets[k];
+          recs.push_back(lower_one(x, -1));
+        }
+      };
+      GateRec g = lower_one(op, -1);
+      g.kind = SV_RY;
+      g.nt = 1;
+      for (int k = 0; k < 3; k++) g.c[g.nc++] = op.targets[k + 1];
+      g.cs |= 6u << op.n_controls;
+      g.coef_kind = 0;
+      set_mo(g);
+      g.dagger = true;
+      to_group(g);
+      cxs();
+      recs.push_back(g);
+      cxs();
+      continue;
+    }
     GateRec g = lower_one(ops[i], ops[i].kind == SV_UNITARY ? um : -1);
     if (ops[i].kind == SV_UNITARY) um++;
     if (g.mo == MO_NOP) continue;
+    if (tl.dense) to_group(g);
     recs.push_back(g);
   }
   if (mode == 0) {
@@ -1877,6 +2010,8 @@ static sv_status upload_call_data(sv_state *st, Plan &P, const sv_op *ops, int n
   }
   hipError_t e = svk_launch_coefs(P.d_coefdesc, (int)P.coefs.size(), P.d_params, P.d_statics,
                                   P.d_factors, P.d_coef, st->stream);
+  if (e == hipSuccess && !P.denses.empty())
+    e = svk_launch_denses(P.d_denses, (int)P.denses.size(), P.d_ops, P.d_coef, st->stream);
   if (e != hipSuccess) return fail(SV_EDEVICE, "coefficient kernel: %s", hipGetErrorString(e));
   return SV_OK;
 }
@@ -1950,7 +2085,8 @@ static sv_status run_steps(sv_state *st, Plan &P, void *re, void *im, void *re2,
         e1 = next_event(st);
         if (e0) (void)hipEventRecord(e0, st->stream);
       }
-      hipError_t e = lean ? svk_launch_sweep_kron(dbl, P.M, P.R, P.NS, a, (int)g, st->stream)
+      hipError_t e = stp.has_dense ? svk_launch_sweep_dense(a, (int)g, st->stream)
+                     : lean ? svk_launch_sweep_kron(dbl, P.M, P.R, P.NS, a, (int)g, st->stream)
                           : svk_launch_sweep(dbl, P.M, P.R, P.NS, a, (int)g, st->stream);
       if (e != hipSuccess) return fail(SV_EDEVICE, "sweep kernel: %s", hipGetErrorString(e));
       if (a.flags & SW_INIT_ZERO) st->pending_zero = false;
@@ -1971,6 +2107,17 @@ static sv_status run_steps(sv_state *st, Plan &P, void *re, void *im, void *re2,
     }
   }
   return SV_OK;
+}
+
+// Tilings whose AUTO plans run every stage in the lean kernels, stages that are
+// no Kronecker stage as dense 8 x 8 matrices on 3-qubit groups (a matrix needs
+// every slot of its group to hold an amplitude: 3 qubits).  The micro-op kernel
+// took groups as wide as the circuit's widest gate and spilled: 200 gates of
+// all kinds on 27 qubits took 92.6 ms in 5-qubit groups (13-bit tiles, and 160
+// to 200 ms in 3- and 4-qubit ones), 28.4 ms so.  FP64 with 13-bit tiles, the
+// default; other tilings, fused blocks and FP32 keep the micro-op kernel.
+static bool dense_plan(int n, bool dbl, const Tiling &tl) {
+  return dbl && tl.M == 13 && tl.R == 3 && n >= 3;
 }
 
 // Smallest compiled register-group width >= need (same tile size if possible).
@@ -1996,8 +2143,12 @@ extern "C" sv_status sv_apply_layer(sv_state *st, const sv_op *ops, int32_t n_op
   int need = fuse_width >= 2 ? fuse_width : 1;
   for (int i = 0; i < n_ops; i++)
     need = std::max(need, ops[i].n_targets + ops[i].n_controls);
-  s = widen_groups(st->dtype == SV_C128, need, tl);
-  if (s) return s;
+  if (fuse_width == SV_FUSE_AUTO && dense_plan(st->n, st->dtype == SV_C128, tl)) {
+    tl.dense = true;
+  } else {
+    s = widen_groups(st->dtype == SV_C128, need, tl);
+    if (s) return s;
+  }
   Plan *P = nullptr;
   s = get_plan(st, fuse_width, tl, ops, n_ops, n_params, false, &P);
   if (s) return s;
@@ -2535,8 +2686,12 @@ static sv_status adjoint_enqueue(sv_state *st, const sv_op *ops, int n_ops, cons
   Tiling tb = st->adj_tiling;
   int width = 1;
   for (int i = 0; i < n_ops; i++) width = std::max(width, ops[i].n_targets + ops[i].n_controls);
-  s = widen_groups(st->dtype == SV_C128, width, tf);
-  if (s) return s;
+  if (dense_plan(st->n, st->dtype == SV_C128, tf)) {
+    tf.dense = true;
+  } else {
+    s = widen_groups(st->dtype == SV_C128, width, tf);
+    if (s) return s;
+  }
   if (width > tb.R) {
     // wider ops need wider backward register groups (same tile if compiled)
     bool found = false;

@@ -73,7 +73,11 @@ struct MicroOp {
 //              form 1: x' = k x - y, y' = x + k y      (k = c/s, scale s)
 //            FP64 plans always take form 0 (CF_FORM0); FP32 plans take form 1
 //            when |s| > |c|, so that |k| <= 1.
-enum { ST_OPS = 0, ST_KRON = 1 };
+//   ST_DENSE: one 2^R x 2^R complex matrix on the group (row-major at kcoef, and
+//            behind it the mask of the entries that are not zero), made on the
+//            device from the stage's micro-ops, in the threads whose index has
+//            pv on the bits pm.
+enum { ST_OPS = 0, ST_KRON = 1, ST_DENSE = 2 };
 
 // Thread mapping of a stage: thread-index bit k sits on tile bit tpos[k]
 // (k < tile bits - group bits); the lane bits (k < 6) hold every tile bit that
@@ -96,14 +100,15 @@ struct alignas(64) StageDesc {
   uint32_t rmask;              // ST_KRON: group bits carrying a real 2x2
   int32_t dflags;              // ST_KRON: 1 = D_before, 2 = D_after; SD_* (any kind)
   int32_t kcoef;               // ST_KRON: coefficient offset (doubles)
-  int32_t kind;                // ST_OPS / ST_KRON
+  int32_t kind;                // ST_OPS / ST_KRON / ST_DENSE
   int8_t tpos[16] __attribute__((aligned(4)));   // tile bit of thread-index bit k (see above)
   int32_t op_begin, op_end;    // micro-ops [op_begin, op_end)
   int32_t g1, g2;              // ST_KRON: MO_GRAD ops [op_begin, g1) run on the stage input,
                                // [g1, g2) after D_before, [g2, op_end) after the rotations
   uint32_t gdiag;              // ST_KRON: bit p set when every MO_GRAD op of range p
                                // (0, 1, 2 as above) has a diagonal generator
-  int32_t pad[3];
+  uint32_t pm, pv;             // ST_DENSE: condition on the thread index
+  int32_t pad;
   int32_t off[2 * SVI_GMAX];   // swizzled tile-local BYTE offsets: slot j is loaded from
                                // off[j] and stored to off[2^R + j]
 };
@@ -195,6 +200,13 @@ struct CoefDesc {
   int32_t dst;         // offset in doubles
   int32_t src;         // CF_COPY: offset into static area
   int32_t len;         // CF_COPY: doubles
+};
+
+// A dense stage's matrix: the micro-ops [op_begin, op_end) in order, at dst.
+struct DenseDesc {
+  int32_t op_begin, op_end;
+  int32_t dst;
+  int32_t pad;
 };
 
 // Expectation / H|psi> tile pass.

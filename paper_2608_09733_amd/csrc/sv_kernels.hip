@@ -367,6 +367,51 @@ __global__ void __launch_bounds__(256) k_build_coefs(const CoefDesc *d, int nd, 
   if (i < nd) build_coef_group(d[i], params, statics, fac, coef, threadIdx.x % COEF_LANES);
 }
 
+// Matrices of dense stages on 3-qubit groups: lane j applies the stage's
+// micro-ops, in order, to basis vector j, which is then column j.  A three-
+// qubit user matrix takes its target i on group bit (t0 >> 4i) & 3.  Behind
+// the matrix goes the mask of its nonzero entries (bit 8 row + column).
+__global__ void __launch_bounds__(64) k_dense_mats(const DenseDesc *d, const MicroOp *ops,
+                                                   double *coef) {
+  const DenseDesc dd = d[blockIdx.x];
+  const int j = threadIdx.x & 7;
+  double re[8], im[8];
+#pragma unroll
+  for (int r = 0; r < 8; r++) {
+    re[r] = r == j ? 1.0 : 0.0;
+    im[r] = 0.0;
+  }
+  for (int o = dd.op_begin; o < dd.op_end; o++) {
+    const MicroOp op = op_at(ops, o);
+    int a0 = 0, a1 = 1;   // swaps that bring the targets to bits 0, 1, 2
+    if (op.type == MO_DENSE) {
+      int p[3] = {op.t0 & 15, (op.t0 >> 4) & 15, (op.t0 >> 8) & 15};
+      a0 = p[0];
+      a1 = p[1] == 0 ? a0 : p[1];
+      dispatch_swap<double, 3>(0, a0, re, im, 0, 0);
+      dispatch_swap<double, 3>(1, a1, re, im, 0, 0);
+    }
+    apply_op<double, 3>(op, re, im, coef);
+    if (op.type == MO_DENSE) {
+      dispatch_swap<double, 3>(1, a1, re, im, 0, 0);
+      dispatch_swap<double, 3>(0, a0, re, im, 0, 0);
+    }
+  }
+  uint64_t nz = 0;
+#pragma unroll
+  for (int r = 0; r < 8; r++)
+    nz |= (__ballot(re[r] != 0.0 || im[r] != 0.0) & 0xffull) << (8 * r);
+  double *u = coef + dd.dst;
+  if (threadIdx.x < 8) {
+#pragma unroll
+    for (int r = 0; r < 8; r++) {
+      u[(8 * r + j) * 2] = re[r];
+      u[(8 * r + j) * 2 + 1] = im[r];
+    }
+  }
+  if (threadIdx.x == 0) *(uint64_t *)(u + 128) = nz;
+}
+
 // --------------------------------------------------- Pauli tile pass
 // Expectation values <P_j> and (optionally) lam = sum_j c_j P_j psi for the
 // terms whose x-mask lies inside the tile (paper Section 4.4 Pauli action:
@@ -1715,6 +1760,12 @@ hipError_t svk_launch_coefs(const CoefDesc *d, int nd, const double *params, con
   const int per = 256 / COEF_LANES;   // descriptors per block
   hipLaunchKernelGGL(k_build_coefs, dim3((nd + per - 1) / per), dim3(256), 0, s, d, nd, params,
                      statics, fac, coef);
+  return hipGetLastError();
+}
+
+hipError_t svk_launch_denses(const DenseDesc *d, int nd, const MicroOp *ops, double *coef,
+                             hipStream_t s) {
+  hipLaunchKernelGGL(k_dense_mats, dim3(nd), dim3(64), 0, s, d, ops, coef);
   return hipGetLastError();
 }
 

@@ -24,6 +24,11 @@ hipError_t svk_launch_sweep_kron(int dbl, int M, int R, int NS, const SweepArgs 
                                  hipStream_t s);
 int svk_sweep_kron_occupancy(int dbl, int M, int R, int NS);
 int svk_has_sweep(int dbl, int M, int R, int NS);
+// FP64, 13-bit tiles, 3-qubit groups: Kronecker and dense stages
+hipError_t svk_launch_sweep_dense(const SweepArgs &a, int grid, hipStream_t s);
+// matrices of dense stages (3-qubit groups) from their micro-ops
+hipError_t svk_launch_denses(const DenseDesc *d, int nd, const MicroOp *ops, double *coef,
+                             hipStream_t s);
 hipError_t svk_launch_gate(int dbl, const GateArgsHost &a, hipStream_t s);
 hipError_t svk_launch_init_zero(int dbl, void *re, void *im, int64_t n, hipStream_t s);
 hipError_t svk_launch_coefs(const CoefDesc *d, int nd, const double *params,

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include "sv_device.h"
+#include "sv_launch.h"
 #include "sv_variants.h"
 
 #if !defined(SVI_VT) || !defined(SVI_VM) || !defined(SVI_VR) || !defined(SVI_VNS)
@@ -42,6 +43,14 @@ int SVI_VNAME(occk, SVI_VT, SVI_VM, SVI_VR, SVI_VNS)() {
   return nb > 0 ? nb : 1;
 }
 #else
+#if SVI_VM == 13 && SVI_VR == 3
+hipError_t svk_launch_sweep_dense(const SweepArgs &a, int grid, hipStream_t s) {
+  hipLaunchKernelGGL((svk::k_sweep_kron<SVI_VT, SVI_VM, SVI_VR, true>), dim3(grid),
+                     dim3(1 << (SVI_VM - SVI_VR)), 0, s, a);
+  return hipGetLastError();
+}
+#endif
+
 hipError_t SVI_VNAME(launchk, SVI_VT, SVI_VM, SVI_VR, SVI_VNS)(const SweepArgs &a, int grid,
                                                                hipStream_t s) {
   hipLaunchKernelGGL((svk::k_sweep_kron<SVI_VT, SVI_VM, SVI_VR>), dim3(grid),

@@ -1,0 +1,81 @@
+"""Double-precision circuits whose gates fit no Kronecker stage: their stages
+run as 8 x 8 matrices on 3-qubit groups, gates on more qubits under a condition
+on the other controls."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2608_09733_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-12   # max-abs bar of a double amplitude
+
+
+def _unitary(rng, k):
+    q, _ = np.linalg.qr(rng.normal(size=(1 << k, 1 << k)) + 1j * rng.normal(size=(1 << k, 1 << k)))
+    return q
+
+
+def _run(n, ops, params, adjoint=False):
+    from paper_2608_09733_amd import sv
+    circ = I.Circuit(n, ops, params)
+    st = sv.State(n, adjoint=adjoint)
+    try:
+        st.run(circ)
+        return st.to_numpy(), circ
+    finally:
+        st.close()
+
+
+# the group's own size, states smaller than a tile, one tile, two and many
+@pytest.mark.parametrize("n", [3, 4, 5, 9, 12, 13, 14, 17])
+def test_every_kind_with_up_to_five_qubits(n):
+    rng = np.random.default_rng(n)
+    ops, par = [I.Op("ry", (q,), params=(q,)) for q in range(n)], list(rng.uniform(0, 6, n))
+    for kind, (nt, npar) in sorted(I.GATES.items()):
+        for nt in (1, 2, 3) if kind == "unitary" else (nt,):
+            for nc in range(min(5, n) - nt + 1):
+                q = [int(v) for v in rng.permutation(n)]
+                par += list(rng.uniform(-6, 6, npar))
+                ops.append(I.Op(kind, tuple(q[:nt]), tuple(q[nt:nt + nc]),
+                                int(rng.integers(0, 1 << nc)) if nc else None,
+                                tuple(range(len(par) - npar, len(par))),
+                                _unitary(rng, nt) if kind == "unitary" else None))
+    order = [int(v) for v in rng.permutation(len(ops) - n)]
+    got, circ = _run(n, ops[:n] + [ops[n + k] for k in order], np.array(par))
+    assert np.max(np.abs(got - O.run_circuit(circ))) <= TOL
+
+
+@pytest.mark.parametrize("perm", [(0, 1, 2), (0, 2, 1), (1, 0, 2), (1, 2, 0), (2, 0, 1), (2, 1, 0)])
+def test_three_qubit_matrix_target_order(perm):
+    rng = np.random.default_rng(7)
+    n, q = 14, (3, 8, 13)
+    ops = [I.Op("ry", (k,), params=(k,)) for k in range(n)]
+    ops.append(I.Op("unitary", tuple(q[p] for p in perm), matrix=_unitary(rng, 3)))
+    got, circ = _run(n, ops, rng.uniform(0, 6, n))
+    assert np.max(np.abs(got - O.run_circuit(circ))) <= TOL
+
+
+def test_amplitudes_that_are_not_finite_stay_in_their_pairs():
+    from paper_2608_09733_amd import sv
+    n = 14
+    rng = np.random.default_rng(3)
+    re, im = rng.normal(size=(2, 1 << n))
+    bad = 0b10110000000101
+    ops = [I.Op("unitary", (4,), matrix=_unitary(rng, 1)), I.Op("rxx", (1, 7), (9,), 1, (0,))]
+    st = sv.State(n)
+    st.set_planes(re, im)
+    st.apply(ops, np.array([0.4]))
+    want = st.to_numpy()
+    re[bad] = np.inf
+    st.set_planes(re, im)
+    st.apply(ops, np.array([0.4]))
+    got = st.to_numpy()
+    st.close()
+    # the pair of qubit 4; RXX acts where qubit 9 is 1, and there on qubits 1 and 7
+    reach = {bad ^ a for a in (0, 1 << 4)}
+    if bad >> 9 & 1:
+        reach |= {x ^ 0b10000010 for x in reach}
+    rest = np.array(sorted(set(range(1 << n)) - reach))
+    assert np.array_equal(got[rest], want[rest])
