@@ -383,9 +383,11 @@ __device__ __forceinline__ double mo_grad(const T *pr, const T *pi, const T *lr,
 }
 
 // Fast-Givens rotation on group bit TB (record {form, k, scale, 0}, form 0 or
-// 1, always 0 for FP64; the scale is applied separately).  Gentleman's scaled
-// rotation: each output is one FMA with a +-1 coefficient on one input.
-template <typename T, int R, int TB, typename CP>
+// 1; the scale is applied separately).  Gentleman's scaled rotation: each
+// output is one FMA with a +-1 coefficient on one input.  F0: the form is 0
+// (FP64 always, CF_FORM0; FP32 nearly always): straight-line FMAs, with no
+// branch whose two arms the compiler would merge with copies.
+template <typename T, int R, int TB, bool F0, typename CP>
 __device__ __forceinline__ void mo_fastr(T *re, T *im, CP cf) {
   const T k = (T)cf[1];
 #define SVI_FR(XR, XI, YR, YI)                                   \
@@ -395,9 +397,7 @@ __device__ __forceinline__ void mo_fastr(T *re, T *im, CP cf) {
     const T xr = re[j], xi = im[j], yr = re[l], yi = im[l];      \
     re[j] = XR; im[j] = XI; re[l] = YR; im[l] = YI;              \
   }
-  if constexpr (sizeof(T) == 8) {
-    // FP64 coefficients are always form 0 (CF_FORM0): straight-line FMAs,
-    // with no branch whose two arms the compiler would merge with copies
+  if constexpr (F0) {
     SVI_FR(xr - k * yr, xi - k * yi, k * xr + yr, k * xi + yi)
   } else {
     const int form = (int)cf[0];
@@ -417,23 +417,33 @@ __device__ __forceinline__ void kron_pre(T *re, T *im, CP cf, int dflags) {
   if (dflags & 1) mo_diagt<T, R>(re, im, cf + 4 * R);
 }
 
-template <typename T, int R, typename CP>
+template <typename T, int R, bool F0 = sizeof(T) == 8, typename CP>
 __device__ __forceinline__ void kron_rot(T *re, T *im, CP cf, uint32_t rmask) {
-  if (rmask & 1u) mo_fastr<T, R, 0>(re, im, cf + 0);
-  if (rmask & 2u) mo_fastr<T, R, 1>(re, im, cf + 4);
-  if constexpr (R > 2) { if (rmask & 4u) mo_fastr<T, R, 2>(re, im, cf + 8); }
-  if constexpr (R > 3) { if (rmask & 8u) mo_fastr<T, R, 3>(re, im, cf + 12); }
-  if constexpr (R > 4) { if (rmask & 16u) mo_fastr<T, R, 4>(re, im, cf + 16); }
+  if (rmask & 1u) mo_fastr<T, R, 0, F0>(re, im, cf + 0);
+  if (rmask & 2u) mo_fastr<T, R, 1, F0>(re, im, cf + 4);
+  if constexpr (R > 2) { if (rmask & 4u) mo_fastr<T, R, 2, F0>(re, im, cf + 8); }
+  if constexpr (R > 3) { if (rmask & 8u) mo_fastr<T, R, 3, F0>(re, im, cf + 12); }
+  if constexpr (R > 4) { if (rmask & 16u) mo_fastr<T, R, 4, F0>(re, im, cf + 16); }
 }
 
 // Every group bit rotated (rmask full), no conditionals.
-template <typename T, int R, typename CP>
+template <typename T, int R, bool F0 = sizeof(T) == 8, typename CP>
 __device__ __forceinline__ void kron_rot_all(T *re, T *im, CP cf) {
-  mo_fastr<T, R, 0>(re, im, cf + 0);
-  mo_fastr<T, R, 1>(re, im, cf + 4);
-  if constexpr (R > 2) mo_fastr<T, R, 2>(re, im, cf + 8);
-  if constexpr (R > 3) mo_fastr<T, R, 3>(re, im, cf + 12);
-  if constexpr (R > 4) mo_fastr<T, R, 4>(re, im, cf + 16);
+  mo_fastr<T, R, 0, F0>(re, im, cf + 0);
+  mo_fastr<T, R, 1, F0>(re, im, cf + 4);
+  if constexpr (R > 2) mo_fastr<T, R, 2, F0>(re, im, cf + 8);
+  if constexpr (R > 3) mo_fastr<T, R, 3, F0>(re, im, cf + 12);
+  if constexpr (R > 4) mo_fastr<T, R, 4, F0>(re, im, cf + 16);
+}
+
+// Whether a stage's rotations all have form 0 (uniform, on the forms' bits).
+template <typename T, int R, typename CP>
+__device__ __forceinline__ bool kron_form0(CP cf, uint32_t rmask) {
+  if constexpr (sizeof(T) == 8) return true;
+  uint32_t f = 0;
+#pragma unroll
+  for (int t = 0; t < R; t++) f |= (rmask >> t) & 1u ? __float_as_uint((float)cf[4 * t]) : 0u;
+  return f == 0;
 }
 
 template <typename T, int R, typename CP>
@@ -448,10 +458,10 @@ __device__ __forceinline__ void kron_post(T *re, T *im, CP cf, int dflags) {
   }
 }
 
-template <typename T, int R, typename CP>
+template <typename T, int R, bool F0 = sizeof(T) == 8, typename CP>
 __device__ __forceinline__ void kron_stage(T *re, T *im, CP cf, uint32_t rmask, int dflags) {
   kron_pre<T, R>(re, im, cf, dflags);
-  kron_rot<T, R>(re, im, cf, rmask);
+  kron_rot<T, R, F0>(re, im, cf, rmask);
   kron_post<T, R>(re, im, cf, dflags);
 }
 
@@ -984,7 +994,12 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron(SweepArgs a) {
   const bool init0 = (a.flags & SW_INIT_ZERO) != 0;
   const SVI_CONST StageDesc *stages = cptr(a.stages + a.stage_begin);
   const int nst = a.stage_end - a.stage_begin;
-  const SVI_CONST double *coef = cptr(a.coef);
+  // FP32: coefficients rounded once, where they are formed (28 qubits, 20
+  // layers, 5-qubit groups: 33.9 ms with every wave converting them at every
+  // use and a branch on each rotation's form, 30.3 with neither).
+  const SVI_CONST T *coef;
+  if constexpr (sizeof(T) == 8) coef = cptr(a.coef);
+  else coef = cptr(a.coef32);
 
   if (tid < SVI_MMAX) hb_s[tid] = a.hb[tid < nh ? tid : 0];
   auto base_of = [&](int st) {
@@ -1127,9 +1142,11 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron(SweepArgs a) {
         const int gbs = (st < ntab ? (int)gtab[st * NT + tid] : base_of(st)) * (int)sizeof(C2);
         // The common stage (every group bit rotated, then D_after) runs as its
         // own straight-line body from loads to stores; the general body
-        // branches on the stage's parts.  Separate bodies leave nothing to
-        // merge, so neither pays register copies for the other's branches.
-        auto body = [&](auto full_stage) {
+        // branches on the stage's parts, and in FP32 a third one on the forms
+        // too.  Separate bodies leave nothing to merge, so none pays register
+        // copies for another's branches.
+        auto body = [&](auto full_stage, auto form0) {
+          constexpr bool F0 = decltype(form0)::value;
           T re[G], im[G];
 #pragma unroll
           for (int j = 0; j < G; j++) {
@@ -1138,10 +1155,10 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron(SweepArgs a) {
             im[j] = v.y;
           }
           if constexpr (decltype(full_stage)::value) {
-            kron_rot_all<T, R>(re, im, coef + sd.kcoef);
+            kron_rot_all<T, R, F0>(re, im, coef + sd.kcoef);
             mo_diagt<T, R>(re, im, coef + sd.kcoef + 4 * R + 2 * G);
           } else {
-            kron_stage<T, R>(re, im, coef + sd.kcoef, sd.rmask, sd.dflags);
+            kron_stage<T, R, F0>(re, im, coef + sd.kcoef, sd.rmask, sd.dflags);
           }
           if (sd.dflags & SD_XCHG) lds_barrier();
 #pragma unroll
@@ -1166,10 +1183,12 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron(SweepArgs a) {
               });
             }
           }
+        } else if (!kron_form0<T, R>(coef + sd.kcoef, sd.rmask)) {
+          if constexpr (sizeof(T) == 4) body(std::false_type{}, std::false_type{});
         } else if (sd.rmask == (1u << R) - 1 && (sd.dflags & 7) == 2) {
-          body(std::true_type{});
+          body(std::true_type{}, std::true_type{});
         } else {
-          body(std::false_type{});
+          body(std::false_type{}, std::true_type{});
         }
         if (sd.dflags & SD_WLOCAL) {
           // the next stage reads only slots this wave wrote: keep the wave's
@@ -1437,7 +1456,7 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
 template <typename T, int R, typename Sink>
 __device__ __forceinline__ void kron2_stage(char *lb0, char *lb1, int gbs,
                                             const SVI_CONST StageDesc &sd,
-                                            const SVI_CONST double *coef, const MicroOp *ops,
+                                            const SVI_CONST T *coef, const MicroOp *ops,
                                             const double *gcoef, bool active, Sink &&sink) {
   constexpr int G = 1 << R;
   using C2 = typename C2T<T>::type;
@@ -1452,7 +1471,7 @@ __device__ __forceinline__ void kron2_stage(char *lb0, char *lb1, int gbs,
       im[s][j] = v.y;
     }
   }
-  const SVI_CONST double *kc = coef + sd.kcoef;
+  const SVI_CONST T *kc = coef + sd.kcoef;
   auto grads = [&](int b, int e, double mult, int point) {
     // two terms at a time, summed over the wave in one chain of lane moves
     // (groups of four, in any arrangement, measured slower)
@@ -1502,10 +1521,15 @@ __device__ __forceinline__ void kron2_stage(char *lb0, char *lb1, int gbs,
   kron_pre<T, R>(re[0], im[0], kc, sd.dflags);
   kron_pre<T, R>(re[1], im[1], kc, sd.dflags);
   grads(sd.g1, sd.g2, 1.0, 1);
-  kron_rot<T, R>(re[0], im[0], kc, sd.rmask);
-  kron_rot<T, R>(re[1], im[1], kc, sd.rmask);
+  if (__builtin_expect(kron_form0<T, R>(kc, sd.rmask), 1)) {
+    kron_rot<T, R, true>(re[0], im[0], kc, sd.rmask);
+    kron_rot<T, R, true>(re[1], im[1], kc, sd.rmask);
+  } else if constexpr (sizeof(T) == 4) {
+    kron_rot<T, R>(re[0], im[0], kc, sd.rmask);
+    kron_rot<T, R>(re[1], im[1], kc, sd.rmask);
+  }
   if (sd.g2 < sd.op_end) {
-    const double sc = kc[4 * R + 4 * G];
+    const double sc = cptr(gcoef)[sd.kcoef + 4 * R + 4 * G];
     grads(sd.g2, sd.op_end, sc * sc, 2);
   }
   kron_post<T, R>(re[0], im[0], kc, sd.dflags);
@@ -1601,7 +1625,9 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron2(SweepArgs a) {
   const bool vec = c >= (VN == 2 ? 1 : 2);
   const SVI_CONST StageDesc *stages = cptr(a.stages + a.stage_begin);
   const int nst = a.stage_end - a.stage_begin;
-  const SVI_CONST double *coef = cptr(a.coef);
+  const SVI_CONST T *coef;   // FP32: rounded once, where they are formed
+  if constexpr (sizeof(T) == 8) coef = cptr(a.coef);
+  else coef = cptr(a.coef32);
 
   if (tid < SVI_MMAX) hb_s[tid] = a.hb[tid < nh ? tid : 0];
   const int ntab = nst < LTAB ? nst : LTAB;

@@ -305,6 +305,7 @@ struct SweepP {
 struct Tiling {
   int M = 13, c = 3, R = 5;
   bool dense = false;         // stages that are no Kronecker stage run as dense matrices
+  bool pick = false;          // a default: FP32 plans may choose R
 };
 
 static int popc(uint64_t v) { return __builtin_popcountll(v); }
@@ -785,6 +786,7 @@ struct Plan {
   TabFactor *d_factors = nullptr;
   DenseDesc *d_denses = nullptr;
   double *d_coef = nullptr;
+  float *d_coef32 = nullptr;         // FP32 plans: Kronecker stages' coefficients as floats
   double *d_params = nullptr;        // user params + constants
   double *d_statics = nullptr;
   int32_t *d_rowptr = nullptr, *d_gslots = nullptr;
@@ -1333,7 +1335,8 @@ static sv_status upload_plan(Plan &P) {
   size_t o_fa = align(o_cd + P.coefs.size() * sizeof(CoefDesc));
   size_t o_de = align(o_fa + (P.factors.size() + 1) * sizeof(TabFactor));
   size_t o_cf = align(o_de + P.denses.size() * sizeof(DenseDesc));
-  size_t o_pa = align(o_cf + (size_t)std::max(P.ncoef, 1) * 8);
+  size_t o_c32 = align(o_cf + (size_t)std::max(P.ncoef, 1) * 8);
+  size_t o_pa = align(o_c32 + (P.dbl ? 0 : (size_t)std::max(P.ncoef, 1) * 4));
   size_t npar = (size_t)P.n_user_params + P.constants.size();
   size_t o_stc = align(o_pa + std::max<size_t>(npar, 1) * 8);
   size_t o_rp = align(o_stc + (size_t)std::max(P.nstatic, 1) * 8);
@@ -1346,6 +1349,7 @@ static sv_status upload_plan(Plan &P) {
   P.d_ops = (MicroOp *)(b + o_ops);
   P.d_coefdesc = (CoefDesc *)(b + o_cd);
   P.d_coef = (double *)(b + o_cf);
+  if (!P.dbl) P.d_coef32 = (float *)(b + o_c32);
   P.d_factors = (TabFactor *)(b + o_fa);
   if (!P.factors.empty())
     HIPCHK(hipMemcpy(P.d_factors, P.factors.data(), P.factors.size() * sizeof(TabFactor), hipMemcpyHostToDevice));
@@ -1466,6 +1470,7 @@ static Tiling default_tiling(int n, sv_dtype dt, int NS) {
     if (NS == 2) { t.M = 13; t.R = 4; t.c = 3; }
     else { t.M = 14; t.R = 5; t.c = 3; }
   }
+  t.pick = NS == 1;
   (void)n;
   return t;
 }
@@ -1529,6 +1534,7 @@ extern "C" sv_status sv_set_tiling(sv_state *st, int32_t tile_bits, int32_t low_
                                    int32_t group_bits) {
   if (!st) return fail(SV_EINVAL, "null handle");
   Tiling t = default_tiling(st->n, st->dtype, 1);
+  if (tile_bits || low_bits || group_bits) t.pick = false;
   if (tile_bits) t.M = tile_bits;
   if (low_bits) t.c = low_bits;
   if (group_bits) {
@@ -1629,8 +1635,8 @@ static std::string plan_key(int mode, int n, const Tiling &tl, bool dbl, const s
   std::string k;
   k.reserve(64 + (size_t)n_ops * 24);
   char buf[96];
-  snprintf(buf, sizeof buf, "%d|%d|%d,%d,%d,%d|%d|%d|", mode, n, tl.M, tl.c, tl.R, (int)tl.dense,
-           (int)dbl, n_params);
+  snprintf(buf, sizeof buf, "%d|%d|%d,%d,%d,%d,%d|%d|%d|", mode, n, tl.M, tl.c, tl.R, (int)tl.dense,
+           (int)tl.pick, (int)dbl, n_params);
   k += buf;
   for (int i = 0; i < n_ops; i++) {
     const sv_op &o = ops[i];
@@ -1718,7 +1724,7 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, const Tiling
 // batch planner keeps them whole: a batch launches its Kronecker-only kernel
 // only when every circuit qualifies, and a circuit must round the same alone
 // and in any mix.
-static sv_status build_forward_plan(int mode, int n, bool dbl, const Tiling &tl, const sv_op *ops,
+static sv_status build_forward_plan(int mode, int n, bool dbl, Tiling tl, const sv_op *ops,
                                     int n_ops, int n_params, Plan &P, bool remap = true,
                                     bool split1q = true) {
   P.n = n;
@@ -1818,6 +1824,14 @@ static sv_status build_forward_plan(int mode, int n, bool dbl, const Tiling &tl,
     if (g.mo == MO_NOP) continue;
     if (tl.dense) to_group(g);
     recs.push_back(g);
+  }
+  if (tl.pick && !dbl && mode < 0) {
+    // FP32 circuits whose stages are all Kronecker stages take 4-qubit groups:
+    // 16 wavefronts a CU instead of 8 (28 qubits, 20 layers: 29.8 -> 28.1 ms,
+    // HEA 33.0 -> 29.7).  The micro-op kernel spills less in 5-qubit ones.
+    bool kron = true;
+    for (const GateRec &g : recs) kron = kron && kron_eligible(g) && popc(g.qmask) <= 4;
+    if (kron) P.R = tl.R = 4;
   }
   if (mode == 0) {
     for (GateRec &g : recs) {
@@ -2009,7 +2023,7 @@ static sv_status upload_call_data(sv_state *st, Plan &P, const sv_op *ops, int n
     HIPCHK(hipStreamSynchronize(st->stream));
   }
   hipError_t e = svk_launch_coefs(P.d_coefdesc, (int)P.coefs.size(), P.d_params, P.d_statics,
-                                  P.d_factors, P.d_coef, st->stream);
+                                  P.d_factors, P.d_coef, st->stream, P.d_coef32);
   if (e == hipSuccess && !P.denses.empty())
     e = svk_launch_denses(P.d_denses, (int)P.denses.size(), P.d_ops, P.d_coef, st->stream);
   if (e != hipSuccess) return fail(SV_EDEVICE, "coefficient kernel: %s", hipGetErrorString(e));
@@ -2070,6 +2084,7 @@ static sv_status run_steps(sv_state *st, Plan &P, void *re, void *im, void *re2,
       a.stages = P.d_stages;
       a.ops = P.d_ops;
       a.coef = P.d_coef;
+      a.coef32 = P.d_coef32;
       a.gpart = gpart;
       // the two-state lean kernel takes gradient terms over whole register
       // groups, so it needs tiles at least one group wide

@@ -72,7 +72,7 @@ struct MicroOp {
 //              form 0: x' = x - k y, y' = k x + y      (k = s/c, scale c)
 //              form 1: x' = k x - y, y' = x + k y      (k = c/s, scale s)
 //            FP64 plans always take form 0 (CF_FORM0); FP32 plans take form 1
-//            when |s| > |c|, so that |k| <= 1.
+//            when |c| < 2^-12 |s| (fast_givens).
 //   ST_DENSE: one 2^R x 2^R complex matrix on the group (row-major at kcoef, and
 //            behind it the mask of the entries that are not zero), made on the
 //            device from the stage's micro-ops, in the threads whose index has
@@ -135,6 +135,7 @@ struct SweepArgs {
   const StageDesc *stages;
   const MicroOp *ops;
   const double *coef;
+  const float *coef32;       // FP32 plans: Kronecker stages' coefficients as floats
   double *gpart;             // adjoint: gradient partials [slot][grid]
   int32_t n;                 // qubits of the state
   int32_t m;                 // tile bits actually used (<= template M)

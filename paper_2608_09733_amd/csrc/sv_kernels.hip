@@ -162,15 +162,27 @@ __device__ void gate_local(int kind, const double *th, double *m /* interleaved,
 // (Gentleman 1973): out = {form, k, scale, 0}, r = scale * (form matrix).
 // form0: a rotation always takes form 0 (k = s / c; c is never exactly zero
 // for a rotation angle that is a double, so k is finite, and the error of
-// (x - k y) c stays within a few ulps of |x c| + |y s|).
+// (x - k y) c stays within a few ulps of |x c| + |y s|).  FP32 takes form 0
+// while |c| >= 2^-12 |s|, so that the products of a stage's k (up to 2^60 for
+// five rotations) and scales stay well inside the range of a float, and its k
+// is a float with the scale that makes the two an exact rotation: rounding k
+// then turns the angle by at most a quarter ulp, whatever |k|, and loses no
+// norm.
 __device__ void fast_givens(const double *r, double *out, bool form0 = false) {
   // rotation [[c,-s],[s,c]] vs reflection [[a,b],[b,-a]]
   const bool rot = fabs(r[0] - r[3]) + fabs(r[1] + r[2]) <= fabs(r[0] + r[3]) + fabs(r[1] - r[2]);
   if (rot) {
     // [[c, -s], [s, c]]
     const double c = r[0], s = r[2];
-    if (form0 || fabs(c) >= fabs(s)) { out[0] = 0; out[1] = s / c; out[2] = c; }
-    else { out[0] = 1; out[1] = c / s; out[2] = s; }
+    if (form0) {
+      out[0] = 0; out[1] = s / c; out[2] = c;
+    } else {
+      const bool f1 = fabs(c) < 0x1p-12 * fabs(s);
+      const double k = (double)(float)(f1 ? c / s : s / c);
+      out[0] = f1 ? 1 : 0;
+      out[1] = k;
+      out[2] = copysign(1.0 / sqrt(1.0 + k * k), f1 ? s : c);
+    }
   } else {
     // [[a, b], [b, -a]]
     const double a = r[0], b = r[1];
@@ -287,11 +299,16 @@ __device__ void build_coef(const CoefDesc &cd, const double *params, const doubl
 constexpr int COEF_LANES = 8;
 
 __device__ void build_coef_group(const CoefDesc &cd, const double *params, const double *statics,
-                                 const TabFactor *fac, double *coef, int l) {
+                                 const TabFactor *fac, double *coef, int l,
+                                 float *coef32 = nullptr) {
   const int fmt = cd.fmt & 0xff;
   const bool table = fmt == CF_TABLE;
   if (!table && fmt != CF_SCALE) {
-    if (l == 0) build_coef(cd, params, statics, fac, coef);
+    if (l == 0) {
+      build_coef(cd, params, statics, fac, coef);
+      if (coef32 && fmt == CF_FASTR)
+        for (int k = 0; k < 4; k++) coef32[cd.dst + k] = (float)coef[cd.dst + k];
+    }
     return;
   }
   const bool dag = (cd.fmt & CF_DAGGER) != 0;
@@ -352,19 +369,25 @@ __device__ void build_coef_group(const CoefDesc &cd, const double *params, const
     const int j = l + e * COEF_LANES;
     if (j >= G) continue;
     if (table) {
+      const double yi = dag ? -xi[e] : xi[e];
       out[2 * j] = xr[e];
-      out[2 * j + 1] = dag ? -xi[e] : xi[e];
+      out[2 * j + 1] = yi;
+      if (coef32) {
+        coef32[cd.dst + 2 * j] = (float)xr[e];
+        coef32[cd.dst + 2 * j + 1] = (float)yi;
+      }
     } else {
       out[0] = xr[e];
+      if (coef32) coef32[cd.dst] = (float)xr[e];
     }
   }
 }
 
 __global__ void __launch_bounds__(256) k_build_coefs(const CoefDesc *d, int nd, const double *params,
                                                      const double *statics, const TabFactor *fac,
-                                                     double *coef) {
+                                                     double *coef, float *coef32) {
   const int i = (int)(blockIdx.x * blockDim.x + threadIdx.x) / COEF_LANES;
-  if (i < nd) build_coef_group(d[i], params, statics, fac, coef, threadIdx.x % COEF_LANES);
+  if (i < nd) build_coef_group(d[i], params, statics, fac, coef, threadIdx.x % COEF_LANES, coef32);
 }
 
 // Matrices of dense stages on 3-qubit groups: lane j applies the stage's
@@ -1755,11 +1778,11 @@ hipError_t svk_launch_init_zero(int dbl, void *re, void *im, int64_t n, hipStrea
 }
 
 hipError_t svk_launch_coefs(const CoefDesc *d, int nd, const double *params, const double *statics,
-                            const TabFactor *fac, double *coef, hipStream_t s) {
+                            const TabFactor *fac, double *coef, hipStream_t s, float *coef32) {
   if (nd <= 0) return hipSuccess;
   const int per = 256 / COEF_LANES;   // descriptors per block
   hipLaunchKernelGGL(k_build_coefs, dim3((nd + per - 1) / per), dim3(256), 0, s, d, nd, params,
-                     statics, fac, coef);
+                     statics, fac, coef, coef32);
   return hipGetLastError();
 }
 

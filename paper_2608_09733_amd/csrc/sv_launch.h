@@ -33,7 +33,7 @@ hipError_t svk_launch_gate(int dbl, const GateArgsHost &a, hipStream_t s);
 hipError_t svk_launch_init_zero(int dbl, void *re, void *im, int64_t n, hipStream_t s);
 hipError_t svk_launch_coefs(const CoefDesc *d, int nd, const double *params,
                             const double *statics, const TabFactor *fac, double *coef,
-                            hipStream_t s);
+                            hipStream_t s, float *coef32 = nullptr);
 hipError_t svk_launch_pauli(int dbl, int M, const PauliPassArgs &a, int grid, hipStream_t s);
 int svk_pauli_occupancy(int dbl);
 hipError_t svk_launch_pauli_wide(int dbl, const void *re, const void *im, void *lre, void *lim,
