@@ -414,7 +414,8 @@ sv_status sv_serve_free(sv_serve *s);
 
 /* ------------------------------------------------------- plan inspection
  * Number of full-state sweeps and register blocks sv_apply_layer would use
- * for this circuit with these settings (host-only; for tests and tuning). */
+ * for this circuit with these settings (host-only; for tests and tuning).  From
+ * 26 qubits on, that of a state other than |0..0>, whose plan is chosen apart. */
 sv_status sv_plan_stats(int32_t n_qubits, const sv_op *ops, int32_t n_ops, int32_t fuse_width,
                         int32_t tile_bits, int32_t low_bits, int32_t group_bits,
                         int32_t *n_sweeps, int32_t *n_blocks);
@@ -430,7 +431,9 @@ sv_status sv_adjoint_plan_stats(int32_t n_qubits, const sv_op *ops, int32_t n_op
 /* Default tiling of sv_apply_layer (backward = 0) or of the backward sweeps
  * of sv_adjoint_grad (backward = 1) for an n_qubits state of this dtype, as
  * used by a handle without sv_set_tiling / sv_set_adjoint_tiling (host-only).
- * Writes the three values (see sv_set_tiling); SV_EINVAL on a bad dtype or
+ * From 24 qubits on SV_FUSE_AUTO may choose other low_bits for a circuit than
+ * this default, and FP32 circuits of Kronecker stages take 4 group_bits; a
+ * tiling that was set is kept to.  Writes the three values (see sv_set_tiling); SV_EINVAL on a bad dtype or
  * null output. */
 sv_status sv_default_tiling(int32_t n_qubits, sv_dtype dtype, int32_t backward,
                             int32_t *tile_bits, int32_t *low_bits, int32_t *group_bits);

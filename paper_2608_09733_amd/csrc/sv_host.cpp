@@ -3,13 +3,17 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
 #include <memory>
 #include <mutex>
+#include <new>
 #include <string>
+#include <system_error>
+#include <thread>
 #include <unordered_map>
 #include <vector>
 
@@ -305,7 +309,8 @@ struct SweepP {
 struct Tiling {
   int M = 13, c = 3, R = 5;
   bool dense = false;         // stages that are no Kronecker stage run as dense matrices
-  bool pick = false;          // a default: FP32 plans may choose R
+  bool pick = false;          // a default: the planner may choose c, in FP32 also R
+  bool zero = true;           // plans are modeled as starting from |0..0>
 };
 
 static int popc(uint64_t v) { return __builtin_popcountll(v); }
@@ -333,6 +338,32 @@ static int closure(const std::vector<GateRec> &recs, const std::vector<int> &can
     } else {
       if (diag && !vetoed) blocked_nd |= q;
       else blocked |= q;
+      if ((blocked & T) == T) break;
+    }
+  }
+  return cnt;
+}
+
+// What closure() without vetoes reads of a pending record, close together:
+// the tile search counts closures of every qubit it might add.
+struct PendRec {
+  uint64_t q;
+  double cost;
+  bool diag;
+};
+
+static int closure_count(const std::vector<PendRec> &pend, uint64_t T, double cost_cap) {
+  uint64_t blocked = 0, blocked_nd = 0;
+  int cnt = 0;
+  double cost = 0.0;
+  for (const PendRec &r : pend) {
+    const bool free = (r.q & blocked) == 0 && (r.diag || (r.q & blocked_nd) == 0);
+    if ((r.q & ~T) == 0 && free && cost + r.cost <= cost_cap) {
+      cnt++;
+      cost += r.cost;
+    } else {
+      if (r.diag) blocked_nd |= r.q;
+      else blocked |= r.q;
       if ((blocked & T) == T) break;
     }
   }
@@ -573,17 +604,24 @@ static void plan_auto(const std::vector<GateRec> &recs, int n, const Tiling &tl,
   size_t start = 0;
   while (left) {
     while (start < cand.size() && done[cand[start]]) start++;
-    std::vector<int> sub(cand.begin() + start, cand.end());
+    std::vector<int> sub;
+    std::vector<PendRec> pend;
+    for (size_t i = start; i < cand.size(); i++)
+      if (!done[cand[i]]) {
+        const GateRec &g = recs[cand[i]];
+        sub.push_back(cand[i]);
+        pend.push_back(PendRec{g.qmask, g.cost, is_diag(g)});
+      }
     uint64_t T = 0;
     for (int p = 0; p < c; p++) T |= 1ull << occ[p];
     if (n <= M) {
       T = n >= 64 ? ~0ull : ((1ull << n) - 1);
     } else {
       for (int step = c; step < M; step++) {
-        int best = -1, bestv = closure(recs, sub, done, T, nullptr, nullptr, cost_cap);
+        int best = -1, bestv = closure_count(pend, T, cost_cap);
         for (int q = 0; q < n; q++) {
           if (T & (1ull << q)) continue;
-          int v = closure(recs, sub, done, T | (1ull << q), nullptr, nullptr, cost_cap);
+          int v = closure_count(pend, T | (1ull << q), cost_cap);
           if (v > bestv) { bestv = v; best = q; }
         }
         if (best < 0) {
@@ -1635,8 +1673,8 @@ static std::string plan_key(int mode, int n, const Tiling &tl, bool dbl, const s
   std::string k;
   k.reserve(64 + (size_t)n_ops * 24);
   char buf[96];
-  snprintf(buf, sizeof buf, "%d|%d|%d,%d,%d,%d,%d|%d|%d|", mode, n, tl.M, tl.c, tl.R, (int)tl.dense,
-           (int)tl.pick, (int)dbl, n_params);
+  snprintf(buf, sizeof buf, "%d|%d|%d,%d,%d,%d,%d,%d|%d|%d|", mode, n, tl.M, tl.c, tl.R, (int)tl.dense,
+           (int)tl.pick, (int)tl.zero, (int)dbl, n_params);
   k += buf;
   for (int i = 0; i < n_ops; i++) {
     const sv_op &o = ops[i];
@@ -1668,56 +1706,134 @@ static void collect_user_mats(Plan &P, const sv_op *ops, int n_ops) {
   for (int v : P.mat_dim) P.nstatic += v;
 }
 
-// Modeled time of a tile-sweep plan, in units of one register stage of
-// 3-qubit groups over the whole state.  A sweep streams the state through HBM
-// while its tiles run their stages; measured on MI355X (FP64, 13-qubit
-// tiles), a sweep takes about max(11, 5.3 + s) such units for s stages: the
-// HBM copy of the state costs as much as 11 stages, and stages beyond about 5
-// are not hidden under it.  Wider register groups cost more per stage.
-static double plan_model(const std::vector<SweepP> &sweeps, int R) {
-  const double w = R <= 3 ? 1.0 : R == 4 ? 1.2 : 1.6;
+// Modeled time of a tile-sweep plan, in ms per 2^28 amplitudes, fitted to 700
+// sweeps of layered and HEA plans of 26 to 30 qubits in the default tilings (6%
+// rms).  A sweep overlaps its traffic and its stages in part (a 2.4-norm of
+// the two).  The traffic depends on the rows that a tile takes, 2^e consecutive
+// amplitudes of a plane (e = the low bits and the tile's high bits that follow
+// them without a gap): rows of 8 amplitudes cost half as much again as 64; and
+// on how far apart they lie, by the number of high bits that reach past the
+// pages the address translation holds.  A stage costs a share for its passage
+// through LDS, one for each of its tables, and a dense one 1.3 times as much.
+// From |0..0> (Tiling::zero) a sweep touches only the tiles inside the qubits
+// that the sweeps before it touched, and the first only writes.
+static double plan_model(const std::vector<SweepP> &sweeps, int n, bool dbl, const Tiling &tl) {
+  static const double io8[4] = {2.33, 1.74, 1.64, 1.62}, far8[4] = {0.46, 0.33, 0.16, 0.13};
+  static const double io4[4] = {1.59, 0.93, 0.93, 0.80}, far4[4] = {0.07, 0.058, 0.017, 0.01};
+  const double w = dbl ? (tl.R <= 3 ? 1.0 : tl.R == 4 ? 1.2 : 1.6) : (tl.R <= 4 ? 1.0 : 1.2);
+  const double lds = (dbl ? 0.18 : 0.133) * w, tab = (dbl ? 0.035 : 0.03) * w;
+  const int far_bit = dbl ? 23 : 18, far_free = dbl ? 4 : 2;
   double t = 0.0;
+  uint64_t support = tl.zero ? 0 : ~0ull;
   for (const SweepP &sw : sweeps) {
-    double s = 0.0;
-    for (const StageP &st : sw.stages) s += st.dense ? 1.3 * w : w;
-    t += std::max(11.0, 5.3 + s);
+    uint64_t tile = (1ull << sw.c) - 1;
+    int e = sw.c, far = -far_free;
+    for (int k = 0; k < sw.nh; k++) {
+      tile |= 1ull << sw.hb[k];
+      if (sw.hb[k] == e) e++;
+      if (sw.hb[k] >= far_bit) far++;
+    }
+    const int row = std::min(std::max(e - 3, 0), 3);
+    const double io = (dbl ? io8 : io4)[row] + std::max(0, far) * (dbl ? far8 : far4)[row];
+    if (!support && tl.zero) {
+      t += 0.5 * io;
+    } else {
+      double st = 0.0;
+      for (const StageP &g : sw.stages)
+        st += g.kron ? lds + tab * ((g.dbefore.empty() ? 0 : 1) + (g.rops.empty() && g.dafter.empty() ? 0 : 1))
+                     : 1.3 * lds;
+      const int zero = std::max(0, n - popc(support | tile));
+      t += std::ldexp(std::pow(std::pow(io, 2.4) + std::pow(st, 2.4), 1 / 2.4), -zero);
+    }
+    support |= tile;
   }
   return t;
 }
 
-// AUTO plan: the greedy tile planner with and without qubit remapping; for
-// large states also with per-sweep caps on the gates a sweep takes (which
-// spread the register stages over the sweeps more evenly), keeping the plan
-// of least modeled time.  The candidate list depends only on the circuit and
-// the state size, so the choice is deterministic.
-static void plan_auto_best(const std::vector<GateRec> &recs, int n, const Tiling &tl,
+// AUTO plan of least modeled time: the greedy tile planner with and without
+// qubit remapping and, for large states, with per-sweep caps on the gates a
+// sweep takes (which spread the register stages over the sweeps more evenly),
+// each with several numbers of contiguous low qubits where the tiling is the
+// default.  The candidates depend only on the circuit and the state size, and
+// of equal ones the first is taken, so the choice is deterministic.  They are
+// planned by several threads: planned one after the other, 33 of them took
+// 70 ms at 30 qubits and 20 layers, a third of the pass.
+static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Tiling &tl,
                            std::vector<SweepP> &out, bool allow_remap) {
-  plan_auto(recs, n, tl, out, 1e300, true, false);
-  double best = plan_model(out, tl.R);
-  auto consider = [&](double cap, bool remap) {
-    std::vector<SweepP> alt;
-    plan_auto(recs, n, tl, alt, cap, true, remap);
-    if (remap && !layout_consistent(alt, n)) return;
-    const double m = plan_model(alt, tl.R);
-    if (m < best) {
-      best = m;
-      out.swap(alt);
-    }
-  };
-  if (allow_remap) consider(1e300, true);
-  // Searching costs about a millisecond of host time per candidate at 30
-  // qubits and is done once per circuit structure (plans are cached); the
-  // number of candidates grows with the modeled sweep time of the state.
-  if (n < 24) return;
+  struct Cand { int c; double cap; bool remap; };
   static const double caps[] = {500, 300, 400, 600, 350, 450, 250, 550, 700, 200, 480, 520,
                                 280, 320, 380, 420, 460, 540, 580, 620, 660, 240, 260, 220,
                                 180, 150, 510, 490, 310, 290, 470, 430, 390, 410, 370, 330};
   const int ncap = (int)(sizeof caps / sizeof caps[0]);
-  const int budget = std::min(ncap, 4 << std::min(n - 24, 3));   // 4 at 24 qubits, 32 from 27
-  for (int k = 0; k < budget; k++) {
-    if (allow_remap) consider(caps[k], true);
-    else consider(caps[k], false);
+  std::vector<Cand> cand;
+  double best = 1e300;
+  double low_best[SVI_MMAX + 1];   // by number of low qubits
+  std::fill(low_best, low_best + SVI_MMAX + 1, 1e300);
+  Tiling won = tl;
+  auto run = [&](size_t from) {
+    const size_t cnt = cand.size() - from;
+    std::vector<std::vector<SweepP>> plans(cnt);
+    std::vector<double> model(cnt, 1e300);
+    std::atomic<size_t> next{0};
+    auto work = [&]() {
+      for (size_t i; (i = next.fetch_add(1)) < cnt;) {
+        const Cand &k = cand[from + i];
+        Tiling t = tl;
+        t.c = k.c;
+        try {
+          plan_auto(recs, n, t, plans[i], k.cap, true, k.remap);
+          if (k.remap && !layout_consistent(plans[i], n)) continue;
+          model[i] = plan_model(plans[i], n, dbl, t);
+        } catch (const std::bad_alloc &) {
+          // a candidate without memory is left out
+        }
+      }
+    };
+    std::vector<std::thread> pool;
+    if (n >= 24) {
+      const int hw = (int)std::thread::hardware_concurrency();
+      const size_t want = std::min<size_t>(cnt, (size_t)std::min(std::max(hw, 1), 8));
+      try {
+        while (pool.size() + 1 < want) pool.emplace_back(work);
+      } catch (const std::system_error &) {
+        // no more threads: those there are plan the rest
+      }
+    }
+    work();
+    for (std::thread &t : pool) t.join();
+    for (size_t i = 0; i < cnt; i++) {
+      double &low = low_best[cand[from + i].c];
+      low = std::min(low, model[i]);
+      if (model[i] < best) {
+        best = model[i];
+        won = tl;
+        won.c = cand[from + i].c;
+        out.swap(plans[i]);
+      }
+    }
+  };
+  std::vector<int> lows{tl.c};
+  if (tl.pick && n >= 24)
+    for (int c : {3, 4, 5, 6, 7})
+      if (c != tl.c && c <= tl.M - 6) lows.push_back(c);
+  for (int c : lows) {
+    cand.push_back({c, 1e300, false});
+    if (allow_remap) cand.push_back({c, 1e300, true});
   }
+  run(0);
+  // The caps are tried for states whose sweeps are worth the search, with the
+  // three numbers of low qubits that did best without.
+  if (n >= 24) {
+    const size_t from = cand.size();
+    const int budget = std::min(ncap, 4 << std::min(n - 24, 3));   // 4 at 24 qubits, 32 from 27
+    std::stable_sort(lows.begin(), lows.end(), [&](int a, int b) { return low_best[a] < low_best[b]; });
+    if (lows.size() > 3) lows.resize(3);
+    for (int c : lows)
+      for (int k = 0; k < budget; k++) cand.push_back({c, caps[k], allow_remap});
+    run(from);
+  }
+  tl = won;
+  if (best == 1e300) plan_auto(recs, n, tl, out, 1e300, true, false);
 }
 
 // split1q: write uncontrolled H, RX, Y, U2, U3 as Kronecker-stage parts.  The
@@ -1851,7 +1967,7 @@ static sv_status build_forward_plan(int mode, int n, bool dbl, Tiling tl, const 
     }
   } else {
     std::vector<SweepP> sweeps;
-    if (mode < 0) plan_auto_best(recs, n, tl, sweeps, remap);
+    if (mode < 0) plan_auto_best(recs, n, dbl, tl, sweeps, remap);
     else plan_fused(recs, n, tl, mode, sweeps, true);
     for (const SweepP &sw : sweeps) {
       int used = 0;
@@ -2145,8 +2261,15 @@ static sv_status widen_groups(bool dbl, int need, Tiling &tl) {
   return fail(SV_EUNSUPPORTED, "no kernel with %d-qubit register groups", need);
 }
 
-extern "C" sv_status sv_apply_layer(sv_state *st, const sv_op *ops, int32_t n_ops,
-                                    const double *params, int32_t n_params, int32_t fuse_width) {
+// Whether a call's plan is modeled from |0..0>: by the state that is there
+// from 26 qubits on (1 GiB; 30 qubits, 10 HEA layers: 82 ms from |0..0> with its
+// plan, 96 with the other; from any state 155 and 135).  Below, both kinds of
+// state take the plan from |0..0>, so that an uploaded |0..0> gives the same
+// bits (24 qubits: within 3% of each other from |0..0>).
+static bool plan_from_zero(const sv_state *st) { return st->n < 26 || st->pending_zero; }
+
+static sv_status apply_layer(sv_state *st, const sv_op *ops, int32_t n_ops, const double *params,
+                             int32_t n_params, int32_t fuse_width, bool zero) {
   if (!st) return fail(SV_EINVAL, "null handle");
   if (!(fuse_width == 0 || fuse_width == SV_FUSE_AUTO || (fuse_width >= 2 && fuse_width <= 5)))
     return fail(SV_EINVAL, "fuse_width %d: must be 0, 2..5 or SV_FUSE_AUTO", fuse_width);
@@ -2154,6 +2277,7 @@ extern "C" sv_status sv_apply_layer(sv_state *st, const sv_op *ops, int32_t n_op
   if (s) return s;
   if (n_ops == 0) return SV_OK;
   Tiling tl = st->tiling;
+  tl.zero = zero;
   // register groups must be as wide as the widest op (and a fused block)
   int need = fuse_width >= 2 ? fuse_width : 1;
   for (int i = 0; i < n_ops; i++)
@@ -2170,6 +2294,12 @@ extern "C" sv_status sv_apply_layer(sv_state *st, const sv_op *ops, int32_t n_op
   s = upload_call_data(st, *P, ops, n_ops, params, n_params);
   if (s) return s;
   return run_steps(st, *P, st->re, st->im, nullptr, nullptr, nullptr, 0);
+}
+
+extern "C" sv_status sv_apply_layer(sv_state *st, const sv_op *ops, int32_t n_ops,
+                                    const double *params, int32_t n_params, int32_t fuse_width) {
+  if (!st) return fail(SV_EINVAL, "null handle");
+  return apply_layer(st, ops, n_ops, params, n_params, fuse_width, plan_from_zero(st));
 }
 
 // ------------------------------------------------------- Pauli reductions
@@ -2522,8 +2652,8 @@ extern "C" sv_status sv_dm_apply(sv_state *st, int32_t n, const sv_op *ops, int3
     }
     out.push_back(col);
   }
-  return sv_apply_layer(st, out.data(), (int32_t)out.size(), p2.empty() ? nullptr : p2.data(),
-                        2 * n_params, SV_FUSE_AUTO);
+  return apply_layer(st, out.data(), (int32_t)out.size(), p2.empty() ? nullptr : p2.data(),
+                     2 * n_params, SV_FUSE_AUTO, st->pending_zero);
 }
 
 extern "C" sv_status sv_dm_apply_kraus(sv_state *st, int32_t n, const int32_t *qubits,
@@ -2698,6 +2828,7 @@ static sv_status adjoint_enqueue(sv_state *st, const sv_op *ops, int n_ops, cons
     return fail(SV_ENOMEM, "workspace too small for the adjoint (%zu < %zu)", st->ws_bytes,
                 sv_workspace_bytes(st->n, st->dtype, SV_WS_ADJOINT));
   Tiling tf = st->tiling;
+  tf.zero = plan_from_zero(st);
   Tiling tb = st->adj_tiling;
   int width = 1;
   for (int i = 0; i < n_ops; i++) width = std::max(width, ops[i].n_targets + ops[i].n_controls);
@@ -3039,6 +3170,7 @@ extern "C" sv_status sv_shot_estimate(sv_state *st, uint64_t seed, int64_t shots
       const double half_pi = 1.5707963267948966;
       if (!rot.empty()) {
         Tiling tl = st->tiling;
+        tl.zero = false;
         s = widen_groups(dbl, 1, tl);
         if (s) return s;
         Plan *P = nullptr;
@@ -3170,6 +3302,8 @@ extern "C" sv_status sv_plan_stats(int32_t n, const sv_op *ops, int32_t n_ops, i
   sv_status s = lower_all(n, ops, n_ops, recs);
   if (s) return s;
   Tiling tl = default_tiling(n, SV_C128, 1);
+  if (tile_bits || low_bits || group_bits) tl.pick = false;
+  tl.zero = n < 26;
   if (tile_bits) tl.M = tile_bits;
   if (low_bits) tl.c = low_bits;
   if (group_bits) tl.R = group_bits;
@@ -3184,7 +3318,7 @@ extern "C" sv_status sv_plan_stats(int32_t n, const sv_op *ops, int32_t n_ops, i
     if (n_blocks) *n_blocks = (int)live.size();
     return SV_OK;
   } else if (fuse_width < 0) {
-    plan_auto_best(live, n, tl, sweeps, true);
+    plan_auto_best(live, n, true, tl, sweeps, true);
   } else {
     plan_fused(live, n, tl, fuse_width, sweeps, true);
   }

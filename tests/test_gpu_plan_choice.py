@@ -1,0 +1,35 @@
+"""From 26 qubits on a plan is chosen by whether the state is |0..0>: both
+plans, and that of a tiling that was set, give the same state."""
+import numpy as np
+import pytest
+
+from paper_2608_09733_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+# bounds of a double and of a single amplitude, one from each of two plans
+@pytest.mark.parametrize("dtype,tol", [("c128", 2e-12), ("c64", 2e-5)])
+def test_plans_from_zero_from_a_state_and_of_a_set_tiling_agree(dtype, tol):
+    import torch
+    from paper_2608_09733_amd import sv
+    n = 26
+    circ = I.hea(n, 4, seed=5)
+    oa = sv.OpArray(circ.ops)
+    one = np.zeros(1 << n)
+    one[0] = 1.0
+    ref = None
+    for how in ("zero", "state", "set"):
+        st = sv.State(n, dtype)
+        if how == "set":
+            st.set_tiling(13, 4, 5)
+        if how == "state":
+            st.set_planes(one, np.zeros(1 << n))
+        st.apply(None, circ.params, op_array=oa)
+        re, im = st.re.clone(), st.im.clone()
+        st.close()
+        if ref is None:
+            ref = re, im
+            assert abs(float((re.double() ** 2 + im.double() ** 2).sum()) - 1.0) <= 1e-5
+        assert float((re - ref[0]).abs().max()) <= tol and float((im - ref[1]).abs().max()) <= tol
+    torch.cuda.empty_cache()
