@@ -580,24 +580,39 @@ __device__ __forceinline__ double grad_op(const MicroOp &op, const T *pr, const 
   return 0.0;
 }
 
-// MO_GRAD inside a Kronecker stage: the planner admits only diagonal
-// generators (x = 0) and the Y of an uncontrolled RY (x = one group bit,
-// n_Y = 1), so only those forms are compiled here (fewer code paths, fewer
-// live registers in the two-state kernel).
+// Gradient of an uncontrolled RY on group bit TB (generator Y):
+// Im <lam| Y |psi> over one group.
+template <typename T, int R, int TB>
+__device__ __forceinline__ double ry_grad(const T *pr, const T *pi, const T *lr, const T *li) {
+  double up = 0.0, down = 0.0;
+#pragma unroll
+  for (int j = 0; j < (1 << R); j++) {
+    if (j & (1 << TB)) continue;
+    const int k = j | (1 << TB);
+    up += (double)lr[k] * (double)pr[j] + (double)li[k] * (double)pi[j];
+    down += (double)lr[j] * (double)pr[k] + (double)li[j] * (double)pi[k];
+  }
+  return up - down;
+}
+
 template <typename T, int R>
-__device__ __forceinline__ double grad_kron(const MicroOp &op, const T *pr, const T *pi,
-                                            const T *lr, const T *li, const double *coef) {
-  const SVI_CONST double *tab = cptr(coef) + op.t0;
-  switch (op.mask) {
-    case 0: return mo_grad<T, R, 0, false>(pr, pi, lr, li, tab);
-    case 1: return mo_grad<T, R, 1, true>(pr, pi, lr, li, tab);
-    case 2: return mo_grad<T, R, 2, true>(pr, pi, lr, li, tab);
-    case 4: if constexpr (R > 2) return mo_grad<T, R, 4, true>(pr, pi, lr, li, tab); break;
-    case 8: if constexpr (R > 3) return mo_grad<T, R, 8, true>(pr, pi, lr, li, tab); break;
-    case 16: if constexpr (R > 4) return mo_grad<T, R, 16, true>(pr, pi, lr, li, tab); break;
+__device__ __forceinline__ double ry_grad_at(int t, const T *pr, const T *pi, const T *lr,
+                                             const T *li) {
+  switch (t) {
+    case 0: return ry_grad<T, R, 0>(pr, pi, lr, li);
+    case 1: return ry_grad<T, R, 1>(pr, pi, lr, li);
+    case 2: if constexpr (R > 2) return ry_grad<T, R, 2>(pr, pi, lr, li); break;
+    case 3: if constexpr (R > 3) return ry_grad<T, R, 3>(pr, pi, lr, li); break;
+    case 4: if constexpr (R > 4) return ry_grad<T, R, 4>(pr, pi, lr, li); break;
     default: break;
   }
   return 0.0;
+}
+
+// Gradient slot of a Kronecker stage's RY on group bit t (StageDesc::ry; -1: none).
+__device__ __forceinline__ int ry_slot(const SVI_CONST StageDesc &sd, int t) {
+  const uint32_t v = (sd.ry[t >> 1] >> (16 * (t & 1))) & 0xffffu;
+  return v == 0xffffu ? -1 : (int)v;
 }
 
 // MO_GRAD or MO_GRAD2L (the micro-op interpreter; Kronecker stages hold MO_GRAD only).
@@ -809,7 +824,8 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep(SweepArgs a) {
           auto grads = [&](int b, int e, double mult) {
             for (int o = b; o < e; o++) {
               const MicroOp op = op_at(a.ops, o);
-              double v = active ? mult * grad_kron<T, R>(op, re[0], im[0], re[1], im[1], a.coef) : 0.0;
+              double v = active ? mult * mo_grad<T, R, 0, false>(re[0], im[0], re[1], im[1],
+                                                                 cptr(a.coef) + op.t0) : 0.0;
               v = wave_sum(v);
               if ((tid & 63) == 0) wsum[tid >> 6][op.coef] = v;
             }
@@ -817,12 +833,17 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep(SweepArgs a) {
           grads(sd.op_begin, sd.g1, 1.0);
           kron_pre<T, R>(re[0], im[0], kc, sd.dflags);
           kron_pre<T, R>(re[1], im[1], kc, sd.dflags);
-          grads(sd.g1, sd.g2, 1.0);
+          for (int t = 0; t < R; t++) {
+            const int slot = ry_slot(sd, t);
+            if (slot < 0) continue;
+            const double v = wave_sum(active ? ry_grad_at<T, R>(t, re[0], im[0], re[1], im[1]) : 0.0);
+            if ((tid & 63) == 0) wsum[tid >> 6][slot] = v;
+          }
           kron_rot<T, R>(re[0], im[0], kc, sd.rmask);
           kron_rot<T, R>(re[1], im[1], kc, sd.rmask);
-          if (sd.g2 < sd.op_end) {
+          if (sd.g1 < sd.op_end) {
             const double sc = kc[4 * R + 4 * G];
-            grads(sd.g2, sd.op_end, sc * sc);
+            grads(sd.g1, sd.op_end, sc * sc);
           }
           kron_post<T, R>(re[0], im[0], kc, sd.dflags);
           kron_post<T, R>(re[1], im[1], kc, sd.dflags);
@@ -1447,9 +1468,14 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
 
 // ------------------------------------------- two-state Kronecker stage
 // One Kronecker stage applied to the psi and lambda tiles held side by side in
-// LDS (lb0, lb1), with the gradient terms Im <lam| G |psi> of the stage's
-// gradient micro-ops taken at the three stage points (stage input, after
-// D_before, after the rotations).  Terms go through in pairs: sink(s0, s1, t)
+// LDS (lb0, lb1), with the gradient terms Im <lam| G |psi> taken at the three
+// stage points: diagonal generators (the stage's micro-ops) on the stage input
+// and after the rotations, the RYs (StageDesc::ry) after D_before.  The RYs
+// come from the descriptor, one straight-line sum for each group bit: as
+// micro-ops with a table each, their loads came one after the other and the
+// choice among the generators' forms cost 45 more registers (26 qubits, 10 HEA
+// layers: 40.1 -> 36.0 ms a gradient; complex64, 24 qubits: 6.40 -> 4.71, the
+// kernel no longer spills).  Terms go through in pairs: sink(s0, s1, t)
 // receives the pair's wave_total2 result t and the pair's slots (s1 = -1: a
 // single term), uniform across the wave.  Ends with the barrier (or the wave
 // fence of a wave-local stage) that makes the stores visible to the next stage.
@@ -1472,55 +1498,54 @@ __device__ __forceinline__ void kron2_stage(char *lb0, char *lb1, int gbs,
     }
   }
   const SVI_CONST T *kc = coef + sd.kcoef;
-  auto grads = [&](int b, int e, double mult, int point) {
-    // two terms at a time, summed over the wave in one chain of lane moves
-    // (groups of four, in any arrangement, measured slower)
-    if ((sd.gdiag >> point) & 1) {
-      // every generator here is diagonal: one array of the products
-      // Im(conj(lam_j) psi_j), then a dot product with each term's table
-      double fz[G];
-#pragma unroll
-      for (int j = 0; j < G; j++)
-        fz[j] = (double)re[1][j] * (double)im[0][j] - (double)im[1][j] * (double)re[0][j];
-      auto dot = [&](const MicroOp &op) {
-        const SVI_CONST double *tab = cptr(gcoef) + op.t0;
-        double acc = 0.0;
-#pragma unroll
-        for (int j = 0; j < G; j++) acc += (double)tab[j] * fz[j];
-        return acc;
-      };
-      int o = b;
-#pragma clang loop unroll(disable)
-      for (; o + 1 < e; o += 2) {
-        const MicroOp op0 = op_at(ops, o), op1 = op_at(ops, o + 1);
-        const double v0 = active ? mult * dot(op0) : 0.0;
-        const double v1 = active ? mult * dot(op1) : 0.0;
-        sink(op0.coef, op1.coef, wave_total2(v0, v1));
-      }
-      if (o < e) {
-        const MicroOp op = op_at(ops, o);
-        sink(op.coef, -1, wave_total2(active ? mult * dot(op) : 0.0, 0.0));
-      }
-      return;
-    }
-    int o = b;
-#pragma clang loop unroll(disable)
-    for (; o + 1 < e; o += 2) {
-      const MicroOp op0 = op_at(ops, o), op1 = op_at(ops, o + 1);
-      const double v0 = active ? mult * grad_kron<T, R>(op0, re[0], im[0], re[1], im[1], gcoef) : 0.0;
-      const double v1 = active ? mult * grad_kron<T, R>(op1, re[0], im[0], re[1], im[1], gcoef) : 0.0;
-      sink(op0.coef, op1.coef, wave_total2(v0, v1));
-    }
-    if (o < e) {
-      const MicroOp op = op_at(ops, o);
-      const double v = active ? mult * grad_kron<T, R>(op, re[0], im[0], re[1], im[1], gcoef) : 0.0;
-      sink(op.coef, -1, wave_total2(v, 0.0));
+  // terms go through in pairs, summed over the wave in one chain of lane moves
+  // (groups of four, in any arrangement, measured slower): the first of a pair
+  // waits here
+  double wait_v = 0.0;
+  int wait_s = -1;
+  auto put = [&](int slot, double v) {
+    if (!active) v = 0.0;
+    if (wait_s < 0) {
+      wait_v = v;
+      wait_s = slot;
+    } else {
+      sink(wait_s, slot, wave_total2(wait_v, v));
+      wait_s = -1;
     }
   };
-  grads(sd.op_begin, sd.g1, 1.0, 0);
+  // diagonal generators: one array of the products Im(conj(lam_j) psi_j), then
+  // a dot product with each term's table
+  auto grads = [&](int b, int e, double mult) {
+    if (b >= e) return;
+    double fz[G];
+#pragma unroll
+    for (int j = 0; j < G; j++)
+      fz[j] = (double)re[1][j] * (double)im[0][j] - (double)im[1][j] * (double)re[0][j];
+#pragma clang loop unroll(disable)
+    for (int o = b; o < e; o++) {
+      const MicroOp op = op_at(ops, o);
+      const SVI_CONST double *tab = cptr(gcoef) + op.t0;
+      double acc = 0.0;
+#pragma unroll
+      for (int j = 0; j < G; j++) acc += (double)tab[j] * fz[j];
+      put(op.coef, mult * acc);
+    }
+  };
+  grads(sd.op_begin, sd.g1, 1.0);
   kron_pre<T, R>(re[0], im[0], kc, sd.dflags);
   kron_pre<T, R>(re[1], im[1], kc, sd.dflags);
-  grads(sd.g1, sd.g2, 1.0, 1);
+  {
+    auto ry = [&](auto bit) {
+      constexpr int TB = decltype(bit)::value;
+      const int slot = ry_slot(sd, TB);
+      if (slot >= 0) put(slot, ry_grad<T, R, TB>(re[0], im[0], re[1], im[1]));
+    };
+    ry(std::integral_constant<int, 0>{});
+    ry(std::integral_constant<int, 1>{});
+    if constexpr (R > 2) ry(std::integral_constant<int, 2>{});
+    if constexpr (R > 3) ry(std::integral_constant<int, 3>{});
+    if constexpr (R > 4) ry(std::integral_constant<int, 4>{});
+  }
   if (__builtin_expect(kron_form0<T, R>(kc, sd.rmask), 1)) {
     kron_rot<T, R, true>(re[0], im[0], kc, sd.rmask);
     kron_rot<T, R, true>(re[1], im[1], kc, sd.rmask);
@@ -1528,10 +1553,11 @@ __device__ __forceinline__ void kron2_stage(char *lb0, char *lb1, int gbs,
     kron_rot<T, R>(re[0], im[0], kc, sd.rmask);
     kron_rot<T, R>(re[1], im[1], kc, sd.rmask);
   }
-  if (sd.g2 < sd.op_end) {
+  if (sd.g1 < sd.op_end) {
     const double sc = cptr(gcoef)[sd.kcoef + 4 * R + 4 * G];
-    grads(sd.g2, sd.op_end, sc * sc, 2);
+    grads(sd.g1, sd.op_end, sc * sc);
   }
+  if (wait_s >= 0) sink(wait_s, -1, wave_total2(wait_v, 0.0));
   kron_post<T, R>(re[0], im[0], kc, sd.dflags);
   kron_post<T, R>(re[1], im[1], kc, sd.dflags);
   if (sd.dflags & SD_XCHG) lds_barrier();

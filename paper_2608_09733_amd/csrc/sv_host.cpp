@@ -1059,8 +1059,9 @@ static void emit_sweep(Plan &P, std::vector<GateRec> &recs, const SweepP &sw, in
         go.gbeta = g.gbeta;
         go.coef = gs;
         // per-slot table of the generator (sv_internal.h, MO_GRAD): plan
-        // constants, copied into the coefficient buffer on every call
-        {
+        // constants, copied into the coefficient buffer on every call (a
+        // Kronecker stage's RY needs none: StageDesc::ry)
+        if (!(st.kron && xl != 0)) {
           const int G = 1 << R;
           const int ny = __builtin_popcount(xl & zl) & 3;
           // beta multiplies the identity: the x = 0 form (phase gates only)
@@ -1206,33 +1207,27 @@ static void emit_sweep(Plan &P, std::vector<GateRec> &recs, const SweepP &sw, in
         sd.dflags |= 2;
         table(st.dafter, sd.kcoef + 4 * R + 2 * G, true);
       }
-      // gradient ops at the three stage points (diagonal gates before any
-      // rotation: stage input; rotations: after D_before; diagonal gates
-      // after a rotation: after the rotations)
+      // gradients at the three stage points: diagonal gates before any
+      // rotation on the stage input, rotations after D_before, diagonal gates
+      // after a rotation after the rotations
+      sd.ry[0] = sd.ry[1] = sd.ry[2] = ~0u;
+      for (int r : st.rops)
+        if (grad_mop[idx_of(r)].type == MO_GRAD) {
+          const int t = local_of(recs[r].t[0]), sh = 16 * (t & 1);
+          sd.ry[t >> 1] = (sd.ry[t >> 1] & ~(0xffffu << sh)) | ((uint32_t)grad_mop[idx_of(r)].coef << sh);
+        }
       sd.op_begin = (int)P.ops.size();
       for (int r : st.dbefore)
         if (grad_mop[idx_of(r)].type == MO_GRAD) P.ops.push_back(grad_mop[idx_of(r)]);
       sd.g1 = (int)P.ops.size();
-      for (int r : st.rops)
-        if (grad_mop[idx_of(r)].type == MO_GRAD) P.ops.push_back(grad_mop[idx_of(r)]);
-      sd.g2 = (int)P.ops.size();
       for (int r : st.dafter)
         if (grad_mop[idx_of(r)].type == MO_GRAD) P.ops.push_back(grad_mop[idx_of(r)]);
       sd.op_end = (int)P.ops.size();
-      // ranges whose generators are all diagonal (the kernel then makes one
-      // product array for them instead of one per generator form)
-      sd.gdiag = 0;
-      const int gb[4] = {sd.op_begin, sd.g1, sd.g2, sd.op_end};
-      for (int p = 0; p < 3; p++) {
-        bool diag = true;
-        for (int o = gb[p]; o < gb[p + 1]; o++) diag = diag && P.ops[o].mask == 0;
-        if (diag) sd.gdiag |= 1u << p;
-      }
       // the scalar slot holds the product of the fast-Givens scales: applied
       // to the state when there is no D_after to carry it, and used to rescale
       // gradients taken between the rotations and D_after
       const bool scalar = st.dafter.empty() && !st.rops.empty();
-      if (scalar || sd.g2 < sd.op_end) {
+      if (scalar || sd.g1 < sd.op_end) {
         if (scalar) sd.dflags |= 4;
         CoefDesc cd{};
         cd.fmt = CF_SCALE | (dag ? CF_DAGGER : 0) | (P.dbl ? CF_FORM0 : 0);
@@ -1248,7 +1243,7 @@ static void emit_sweep(Plan &P, std::vector<GateRec> &recs, const SweepP &sw, in
       sd.kind = ST_DENSE;
       sd.op_begin = (int)P.ops.size();
       for (const MicroOp &m : mops) P.ops.push_back(m);
-      sd.op_end = sd.g1 = sd.g2 = (int)P.ops.size();
+      sd.op_end = sd.g1 = (int)P.ops.size();
       sd.kcoef = P.ncoef;
       P.ncoef += (2 << (2 * R)) + 2;
       P.denses.push_back(DenseDesc{sd.op_begin, sd.op_end, sd.kcoef, 0});
@@ -1273,7 +1268,7 @@ static void emit_sweep(Plan &P, std::vector<GateRec> &recs, const SweepP &sw, in
       sd.op_begin = (int)P.ops.size();
       for (const MicroOp &m : body) P.ops.push_back(m);
       sd.op_end = (int)P.ops.size();
-      sd.g1 = sd.g2 = sd.op_end;
+      sd.g1 = sd.op_end;
     }
     // slot j's tile-local offsets: its group bits placed, then the leading
     // permutations undone (load) or the trailing ones applied (store), on tile

@@ -103,12 +103,15 @@ struct alignas(64) StageDesc {
   int32_t kind;                // ST_OPS / ST_KRON / ST_DENSE
   int8_t tpos[16] __attribute__((aligned(4)));   // tile bit of thread-index bit k (see above)
   int32_t op_begin, op_end;    // micro-ops [op_begin, op_end)
-  int32_t g1, g2;              // ST_KRON: MO_GRAD ops [op_begin, g1) run on the stage input,
-                               // [g1, g2) after D_before, [g2, op_end) after the rotations
-  uint32_t gdiag;              // ST_KRON: bit p set when every MO_GRAD op of range p
-                               // (0, 1, 2 as above) has a diagonal generator
-  uint32_t pm, pv;             // ST_DENSE: condition on the thread index
-  int32_t pad;
+  int32_t g1;                  // ST_KRON: MO_GRAD ops (diagonal generators) [op_begin, g1) run on
+                               // the stage input, [g1, op_end) after the rotations
+  union {
+    struct { uint32_t pm, pv; };   // ST_DENSE: condition on the thread index
+    uint32_t ry[3];            // ST_KRON of a backward program: gradient slot of the RY on group
+                               // bit t in the 16 bits from 16 (t & 1) of ry[t >> 1] (0xffff: none),
+                               // taken after D_before
+  };
+  int32_t pad[2];
   int32_t off[2 * SVI_GMAX];   // swizzled tile-local BYTE offsets: slot j is loaded from
                                // off[j] and stored to off[2^R + j]
 };
