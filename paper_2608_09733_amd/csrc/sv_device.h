@@ -1671,8 +1671,94 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron2(SweepArgs a) {
   const int tsw = swz<T>(tid * VN);
   T *const pr[2] = {(T *)a.re, (T *)a.re2};
   T *const pi[2] = {(T *)a.im, (T *)a.im2};
+  const T *const qr[2] = {(const T *)a.src_re, (const T *)a.re2};
+  const T *const qi[2] = {(const T *)a.src_im, (const T *)a.im2};
+  const bool active = tid < (1 << (m > R ? m - R : 0));
+  auto stages_run = [&]() {
+    for (int st = 0; st < nst; st++) {
+      const SVI_CONST StageDesc &sd = stages[st];
+      const int gbs = ((st < ntab ? (int)ltab[st * 64 + lane] : swz<T>(lane_base(lane, sd))) ^
+                       swz<T>(wave_base<M, R>(wave, sd))) * (int)sizeof(C2);
+      kron2_stage<T, R>((char *)lds[0], (char *)lds[1], gbs, sd, coef, a.ops, a.coef, active,
+                        [&](int s0, int s1, double t) {
+        // this tile's wave totals into the wave's LDS rows of their slots
+        // (LDS adds without return: the wave does not wait)
+        wave_deposit2(wacc[tid >> 6], s0, s1, t, tid & 63);
+      });
+    }
+  };
+  auto tile_in = [&](int s, int k, const V4 &vr, const V4 &vi) {
+    const int si = tsw ^ swz<T>(k * NT * VN);
+    lds[s][si] = C2{vr.x, vi.x};
+    lds[s][si ^ 1] = C2{vr.y, vi.y};
+    if constexpr (VN == 4) {
+      lds[s][si ^ 2] = C2{vr.z, vi.z};
+      lds[s][si ^ 3] = C2{vr.w, vi.w};
+    }
+  };
+  auto tile_out = [&](int s, int k, uint64_t g) {
+    const int si = tsw ^ swz<T>(k * NT * VN);
+    V4 vr, vi;
+    if constexpr (VN == 2) {
+      const C2 p0 = lds[s][si], p1 = lds[s][si ^ 1];
+      vr = V4{p0.x, p1.x};
+      vi = V4{p0.y, p1.y};
+    } else {
+      const C2 p0 = lds[s][si], p1 = lds[s][si ^ 1], p2 = lds[s][si ^ 2], p3 = lds[s][si ^ 3];
+      vr = V4{p0.x, p1.x, p2.x, p3.x};
+      vi = V4{p0.y, p1.y, p2.y, p3.y};
+    }
+    *(V4 *)(pr[s] + g) = vr;
+    *(V4 *)(pi[s] + g) = vi;
+  };
 
   int64_t r0 = 0;
+  // Full tiles, FP64: the next tile's loads are in flight behind this tile's
+  // stages (as in k_sweep_kron), in registers that the stages leave free at
+  // two waves per SIMD; FP32 stages leave none.
+  if (sizeof(T) == 8 && m == M && vec) {
+    V4 nr[2][NIT], ni[2][NIT];
+    auto fetch = [&](int64_t t) {
+      const uint64_t b0 = tile_base(t, c, hb_s, nh);
+#pragma unroll
+      for (int s = 0; s < 2; s++)
+#pragma unroll
+        for (int k = 0; k < NIT; k++) {
+          nr[s][k] = *(const V4 *)(qr[s] + b0 + roff[k]);
+          ni[s][k] = *(const V4 *)(qi[s] + b0 + roff[k]);
+        }
+    };
+    auto all_in = [&]() {
+#pragma unroll
+      for (int s = 0; s < 2; s++)
+#pragma unroll
+        for (int k = 0; k < NIT; k++) tile_in(s, k, nr[s][k], ni[s][k]);
+    };
+    int64_t tile = tile_of(0, blockIdx.x, gridDim.x);
+    if (tile < a.ntiles) {
+      int64_t next = tile_of(gridDim.x, blockIdx.x, gridDim.x);
+      fetch(tile);
+      all_in();
+      lds_barrier();
+      if (next < a.ntiles) fetch(next);
+      while (true) {
+        const uint64_t base = tile_base(tile, c, hb_s, nh);
+        stages_run();
+#pragma unroll
+        for (int s = 0; s < 2; s++)
+#pragma unroll
+          for (int k = 0; k < NIT; k++) tile_out(s, k, base + roff[k]);
+        lds_barrier();
+        if (next >= a.ntiles) break;
+        all_in();
+        lds_barrier();
+        r0 += gridDim.x;
+        tile = next;
+        next = tile_of(r0 + gridDim.x, blockIdx.x, gridDim.x);
+        if (next < a.ntiles) fetch(next);
+      }
+    }
+  } else
   for (int64_t tile = tile_of(0, blockIdx.x, gridDim.x); tile < a.ntiles;) {
     const uint64_t base = tile_base(tile, c, hb_s, nh);
     // ---- both tiles into LDS
@@ -1684,41 +1770,18 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron2(SweepArgs a) {
           const int i = (tid + k * NT) * VN;
           if (i < ntile_el) {
             const uint64_t g = base + roff[k];
-            const V4 vr = *(const V4 *)(pr[s] + g);
-            const V4 vi = *(const V4 *)(pi[s] + g);
-            const int si = tsw ^ swz<T>(k * NT * VN);
-            if constexpr (VN == 2) {
-              lds[s][si] = C2{vr.x, vi.x};
-              lds[s][si ^ 1] = C2{vr.y, vi.y};
-            } else {
-              lds[s][si] = C2{vr.x, vi.x};
-              lds[s][si ^ 1] = C2{vr.y, vi.y};
-              lds[s][si ^ 2] = C2{vr.z, vi.z};
-              lds[s][si ^ 3] = C2{vr.w, vi.w};
-            }
+            tile_in(s, k, *(const V4 *)(qr[s] + g), *(const V4 *)(qi[s] + g));
           }
         }
       } else {
         for (int i = tid; i < ntile_el; i += NT) {
           const uint64_t g = base + spread_row(i >> c, hb_s, nh) + (uint64_t)(i & ((1 << c) - 1));
-          lds[s][swz<T>(i)] = C2{pr[s][g], pi[s][g]};
+          lds[s][swz<T>(i)] = C2{qr[s][g], qi[s][g]};
         }
       }
     }
     lds_barrier();
-    // ---- stages
-    for (int st = 0; st < nst; st++) {
-      const SVI_CONST StageDesc &sd = stages[st];
-      const int gbs = ((st < ntab ? (int)ltab[st * 64 + lane] : swz<T>(lane_base(lane, sd))) ^
-                       swz<T>(wave_base<M, R>(wave, sd))) * (int)sizeof(C2);
-      const bool active = tid < (1 << (m > R ? m - R : 0));
-      kron2_stage<T, R>((char *)lds[0], (char *)lds[1], gbs, sd, coef, a.ops, a.coef, active,
-                        [&](int s0, int s1, double t) {
-        // this tile's wave totals into the wave's LDS rows of their slots
-        // (LDS adds without return: the wave does not wait)
-        wave_deposit2(wacc[tid >> 6], s0, s1, t, tid & 63);
-      });
-    }
+    stages_run();
     // ---- LDS to HBM
 #pragma unroll
     for (int s = 0; s < 2; s++) {
@@ -1727,20 +1790,7 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron2(SweepArgs a) {
         for (int k = 0; k < NIT; k++) {
           const int i = (tid + k * NT) * VN;
           if (i < ntile_el) {
-            const uint64_t g = base + roff[k];
-            const int si = tsw ^ swz<T>(k * NT * VN);
-            V4 vr, vi;
-            if constexpr (VN == 2) {
-              const C2 p0 = lds[s][si], p1 = lds[s][si ^ 1];
-              vr = V4{p0.x, p1.x};
-              vi = V4{p0.y, p1.y};
-            } else {
-              const C2 p0 = lds[s][si], p1 = lds[s][si ^ 1], p2 = lds[s][si ^ 2], p3 = lds[s][si ^ 3];
-              vr = V4{p0.x, p1.x, p2.x, p3.x};
-              vi = V4{p0.y, p1.y, p2.y, p3.y};
-            }
-            *(V4 *)(pr[s] + g) = vr;
-            *(V4 *)(pi[s] + g) = vi;
+            tile_out(s, k, base + roff[k]);
           }
         }
       } else {

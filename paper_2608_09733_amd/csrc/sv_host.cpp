@@ -2166,8 +2166,18 @@ static void restrict_to_support(SweepArgs &a, int n, uint64_t *support) {
   *support |= tile;
 }
 
+// The sweep runs in the lean kernels.  The two-state one takes gradient terms
+// over whole register groups, so it needs tiles at least one group wide.
+static bool lean_step(const Plan &P, const Step &stp) {
+  return stp.kind == 0 && stp.all_kron && svk_sweep_kron_occupancy(P.dbl, P.M, P.R, P.NS) > 0 &&
+         (P.NS == 1 || stp.sa.m >= P.R);
+}
+
+// src_re, src_im: planes from which the first sweep, a lean two-state one,
+// reads state 0 (null: its own).
 static sv_status run_steps(sv_state *st, Plan &P, void *re, void *im, void *re2, void *im2,
-                           double *gpart, int grid_override) {
+                           double *gpart, int grid_override, const void *src_re = nullptr,
+                           const void *src_im = nullptr) {
   DevInfo di;
   sv_status s = device_info(di);
   if (s) return s;
@@ -2197,9 +2207,10 @@ static sv_status run_steps(sv_state *st, Plan &P, void *re, void *im, void *re2,
       a.coef = P.d_coef;
       a.coef32 = P.d_coef32;
       a.gpart = gpart;
-      // the two-state lean kernel takes gradient terms over whole register
-      // groups, so it needs tiles at least one group wide
-      const bool lean = stp.all_kron && occk > 0 && (P.NS == 1 || stp.sa.m >= P.R);
+      const bool first = &stp == &P.steps[0];
+      a.src_re = first && src_re ? src_re : re;
+      a.src_im = first && src_im ? src_im : im;
+      const bool lean = lean_step(P, stp);
       if (track && !lean) track = false;
       if (track) restrict_to_support(a, st->n, &support);
       int64_t g = (int64_t)di.cus * (lean ? occk : occ);
@@ -2871,10 +2882,15 @@ static sv_status adjoint_enqueue(sv_state *st, const sv_op *ops, int n_ops, cons
   double *d_red = nullptr;
   s = run_pauli(st, terms, n_terms, st->re, st->im, lre, lim, &d_red);
   if (s) return s;
-  // working copy of psi for the backward sweep
-  size_t plane = ((size_t)1 << st->n) * elem_size(st->dtype);
-  HIPCHK(hipMemcpyAsync(wre, st->re, plane, hipMemcpyDeviceToDevice, st->stream));
-  HIPCHK(hipMemcpyAsync(wim, st->im, plane, hipMemcpyDeviceToDevice, st->stream));
+  // The backward sweeps work on a copy of psi: the first one reads psi itself
+  // and writes every tile of the copy (a copy made before it took 0.4 of 36 ms
+  // at 26 qubits); only the micro-op kernel needs the copy made.
+  const bool own = !B->steps.empty() && lean_step(*B, B->steps[0]);
+  if (!own) {
+    size_t plane = ((size_t)1 << st->n) * elem_size(st->dtype);
+    HIPCHK(hipMemcpyAsync(wre, st->re, plane, hipMemcpyDeviceToDevice, st->stream));
+    HIPCHK(hipMemcpyAsync(wim, st->im, plane, hipMemcpyDeviceToDevice, st->stream));
+  }
   // backward sweeps
   DevInfo di;
   s = device_info(di);
@@ -2901,7 +2917,8 @@ static sv_status adjoint_enqueue(sv_state *st, const sv_op *ops, int n_ops, cons
   double *grad = slot_sum + B->n_gslots;
   s = upload_call_data(st, *B, ops, n_ops, params, n_params);
   if (s) return s;
-  s = run_steps(st, *B, wre, wim, lre, lim, gpart, (int)grid);
+  s = run_steps(st, *B, wre, wim, lre, lim, gpart, (int)grid, own ? st->re : nullptr,
+                own ? st->im : nullptr);
   if (s) return s;
   hipError_t e = svk_launch_reduce_rows(gpart, B->n_gslots, (int)grid, slot_sum, st->stream);
   if (e != hipSuccess) return fail(SV_EDEVICE, "reduce: %s", hipGetErrorString(e));

@@ -135,6 +135,7 @@ static inline SVI_HD int svi_swz(int i, int B) {
 struct SweepArgs {
   void *re, *im;             // planes of state 0 (psi)
   void *re2, *im2;           // planes of state 1 (lambda; adjoint only)
+  const void *src_re, *src_im;   // k_sweep_kron2: planes that state 0 is read from
   const StageDesc *stages;
   const MicroOp *ops;
   const double *coef;
