@@ -431,9 +431,10 @@ sv_status sv_adjoint_plan_stats(int32_t n_qubits, const sv_op *ops, int32_t n_op
 /* Default tiling of sv_apply_layer (backward = 0) or of the backward sweeps
  * of sv_adjoint_grad (backward = 1) for an n_qubits state of this dtype, as
  * used by a handle without sv_set_tiling / sv_set_adjoint_tiling (host-only).
- * From 24 qubits on SV_FUSE_AUTO may choose other low_bits for a circuit than
- * this default, and FP32 circuits of Kronecker stages take 4 group_bits; a
- * tiling that was set is kept to.  Writes the three values (see sv_set_tiling); SV_EINVAL on a bad dtype or
+ * SV_FUSE_AUTO may run a circuit in another compiled tiling than this default
+ * (small FP64 states in 12-bit tiles, FP32 circuits of Kronecker stages in
+ * 4-qubit groups, other low_bits from 24 qubits on); a tiling that was set is
+ * kept to.  Writes the three values (see sv_set_tiling); SV_EINVAL on a bad dtype or
  * null output. */
 sv_status sv_default_tiling(int32_t n_qubits, sv_dtype dtype, int32_t backward,
                             int32_t *tile_bits, int32_t *low_bits, int32_t *group_bits);

@@ -1831,6 +1831,31 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
   if (best == 1e300) plan_auto(recs, n, tl, out, 1e300, true, false);
 }
 
+// Kernel of a default tiling's AUTO plan.
+// FP64 states of up to 22 qubits take 12-bit tiles with 3 low qubits: they have
+// no tiles to spare for the CUs, and of half the size a tile's loads, stages and
+// stores, which follow each other, take half as long (20 layers, 13-bit tiles
+// and 12-bit ones, us: 12 qubits HEA 190, 155; 16 layered 264, 206; 18 layered
+// 300, 215; 21 layered 436, 383; 22 HEA 819, 765; 23 layered 1305, 1376).  13
+// qubits fit one tile of 13 bits: one sweep (HEA 200, 208).  11-bit tiles have
+// more sweeps (18 layered 253).
+// FP32 circuits whose stages are all Kronecker stages take 4-qubit groups: 16
+// wavefronts a CU instead of 8 (28 qubits, 20 layers: 29.8 -> 28.1 ms, HEA 33.0
+// -> 29.7).  The micro-op kernel spills less in 5-qubit ones.
+static void pick_kernel(const std::vector<GateRec> &recs, int n, bool dbl, Tiling &tl) {
+  if (!tl.pick) return;
+  if (dbl) {
+    if (n <= 22 && n != 13) {
+      tl.M = 12;
+      tl.c = 3;
+    }
+    return;
+  }
+  bool kron = true;
+  for (const GateRec &g : recs) kron = kron && kron_eligible(g) && popc(g.qmask) <= 4;
+  if (kron) tl.R = 4;
+}
+
 // split1q: write uncontrolled H, RX, Y, U2, U3 as Kronecker-stage parts.  The
 // batch planner keeps them whole: a batch launches its Kronecker-only kernel
 // only when every circuit qualifies, and a circuit must round the same alone
@@ -1936,13 +1961,10 @@ static sv_status build_forward_plan(int mode, int n, bool dbl, Tiling tl, const 
     if (tl.dense) to_group(g);
     recs.push_back(g);
   }
-  if (tl.pick && !dbl && mode < 0) {
-    // FP32 circuits whose stages are all Kronecker stages take 4-qubit groups:
-    // 16 wavefronts a CU instead of 8 (28 qubits, 20 layers: 29.8 -> 28.1 ms,
-    // HEA 33.0 -> 29.7).  The micro-op kernel spills less in 5-qubit ones.
-    bool kron = true;
-    for (const GateRec &g : recs) kron = kron && kron_eligible(g) && popc(g.qmask) <= 4;
-    if (kron) P.R = tl.R = 4;
+  if (mode < 0) {
+    pick_kernel(recs, n, dbl, tl);
+    P.M = tl.M;
+    P.R = tl.R;
   }
   if (mode == 0) {
     for (GateRec &g : recs) {
@@ -2222,7 +2244,7 @@ static sv_status run_steps(sv_state *st, Plan &P, void *re, void *im, void *re2,
         e1 = next_event(st);
         if (e0) (void)hipEventRecord(e0, st->stream);
       }
-      hipError_t e = stp.has_dense ? svk_launch_sweep_dense(a, (int)g, st->stream)
+      hipError_t e = stp.has_dense ? svk_launch_sweep_dense(P.M, a, (int)g, st->stream)
                      : lean ? svk_launch_sweep_kron(dbl, P.M, P.R, P.NS, a, (int)g, st->stream)
                           : svk_launch_sweep(dbl, P.M, P.R, P.NS, a, (int)g, st->stream);
       if (e != hipSuccess) return fail(SV_EDEVICE, "sweep kernel: %s", hipGetErrorString(e));
@@ -2251,10 +2273,10 @@ static sv_status run_steps(sv_state *st, Plan &P, void *re, void *im, void *re2,
 // every slot of its group to hold an amplitude: 3 qubits).  The micro-op kernel
 // took groups as wide as the circuit's widest gate and spilled: 200 gates of
 // all kinds on 27 qubits took 92.6 ms in 5-qubit groups (13-bit tiles, and 160
-// to 200 ms in 3- and 4-qubit ones), 28.4 ms so.  FP64 with 13-bit tiles, the
-// default; other tilings, fused blocks and FP32 keep the micro-op kernel.
+// to 200 ms in 3- and 4-qubit ones), 28.4 ms so.  FP64 with 13- and 12-bit
+// tiles; other tilings, fused blocks and FP32 keep the micro-op kernel.
 static bool dense_plan(int n, bool dbl, const Tiling &tl) {
-  return dbl && tl.M == 13 && tl.R == 3 && n >= 3;
+  return dbl && (tl.M == 13 || tl.M == 12) && tl.R == 3 && n >= 3;
 }
 
 // Smallest compiled register-group width >= need (same tile size if possible).
@@ -3330,6 +3352,7 @@ extern "C" sv_status sv_plan_stats(int32_t n, const sv_op *ops, int32_t n_ops, i
     if (n_blocks) *n_blocks = (int)live.size();
     return SV_OK;
   } else if (fuse_width < 0) {
+    pick_kernel(live, n, true, tl);
     plan_auto_best(live, n, true, tl, sweeps, true);
   } else {
     plan_fused(live, n, tl, fuse_width, sweeps, true);

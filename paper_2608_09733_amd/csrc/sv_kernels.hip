@@ -1719,6 +1719,12 @@ hipError_t svk_launch_sweep_kron(int dbl, int M, int R, int NS, const SweepArgs 
   return hipErrorInvalidValue;
 }
 
+hipError_t svk_launch_sweep_dense(int M, const SweepArgs &a, int grid, hipStream_t s) {
+  if (M == 13) return svk_launch_sweep_dense13(a, grid, s);
+  if (M == 12) return svk_launch_sweep_dense12(a, grid, s);
+  return hipErrorInvalidValue;
+}
+
 int svk_sweep_kron_occupancy(int dbl, int M, int R, int NS) {
 #define X(T, MM, RR, NN)                                                        \
   if (NN == NS && (dbl == (sizeof(T) == 8)) && M == MM && R == RR)              \

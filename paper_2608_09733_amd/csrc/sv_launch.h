@@ -24,8 +24,10 @@ hipError_t svk_launch_sweep_kron(int dbl, int M, int R, int NS, const SweepArgs 
                                  hipStream_t s);
 int svk_sweep_kron_occupancy(int dbl, int M, int R, int NS);
 int svk_has_sweep(int dbl, int M, int R, int NS);
-// FP64, 13-bit tiles, 3-qubit groups: Kronecker and dense stages
-hipError_t svk_launch_sweep_dense(const SweepArgs &a, int grid, hipStream_t s);
+// FP64, 12- or 13-bit tiles, 3-qubit groups: Kronecker and dense stages
+hipError_t svk_launch_sweep_dense(int M, const SweepArgs &a, int grid, hipStream_t s);
+hipError_t svk_launch_sweep_dense12(const SweepArgs &a, int grid, hipStream_t s);
+hipError_t svk_launch_sweep_dense13(const SweepArgs &a, int grid, hipStream_t s);
 // matrices of dense stages (3-qubit groups) from their micro-ops
 hipError_t svk_launch_denses(const DenseDesc *d, int nd, const MicroOp *ops, double *coef,
                              hipStream_t s);

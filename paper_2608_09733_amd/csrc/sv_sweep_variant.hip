@@ -43,8 +43,12 @@ int SVI_VNAME(occk, SVI_VT, SVI_VM, SVI_VR, SVI_VNS)() {
   return nb > 0 ? nb : 1;
 }
 #else
-#if SVI_VM == 13 && SVI_VR == 3
-hipError_t svk_launch_sweep_dense(const SweepArgs &a, int grid, hipStream_t s) {
+#if (SVI_VM == 13 || SVI_VM == 12) && SVI_VR == 3
+#if SVI_VM == 13
+hipError_t svk_launch_sweep_dense13(const SweepArgs &a, int grid, hipStream_t s) {
+#else
+hipError_t svk_launch_sweep_dense12(const SweepArgs &a, int grid, hipStream_t s) {
+#endif
   hipLaunchKernelGGL((svk::k_sweep_kron<SVI_VT, SVI_VM, SVI_VR, true>), dim3(grid),
                      dim3(1 << (SVI_VM - SVI_VR)), 0, s, a);
   return hipGetLastError();
