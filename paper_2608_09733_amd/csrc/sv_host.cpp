@@ -1841,7 +1841,10 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
 // more sweeps (18 layered 253).
 // FP32 circuits whose stages are all Kronecker stages take 4-qubit groups: 16
 // wavefronts a CU instead of 8 (28 qubits, 20 layers: 29.8 -> 28.1 ms, HEA 33.0
-// -> 29.7).  The micro-op kernel spills less in 5-qubit ones.
+// -> 29.7).  The micro-op kernel spills less in 5-qubit ones.  Up to 21 qubits
+// they take 13-bit tiles, two a CU, instead of 14-bit ones, for the same reason
+// (20 layers, us: 12 qubits HEA 192, 161; 16 layered 303, 223; 20 layered 390,
+// 307; 21 HEA 531, 489; 22 HEA 547, 604).
 static void pick_kernel(const std::vector<GateRec> &recs, int n, bool dbl, Tiling &tl) {
   if (!tl.pick) return;
   if (dbl) {
@@ -1853,7 +1856,12 @@ static void pick_kernel(const std::vector<GateRec> &recs, int n, bool dbl, Tilin
   }
   bool kron = true;
   for (const GateRec &g : recs) kron = kron && kron_eligible(g) && popc(g.qmask) <= 4;
-  if (kron) tl.R = 4;
+  if (!kron) return;
+  tl.R = 4;
+  if (n <= 21) {
+    tl.M = 13;
+    tl.c = n <= 20 ? 3 : 4;
+  }
 }
 
 // split1q: write uncontrolled H, RX, Y, U2, U3 as Kronecker-stage parts.  The

@@ -20,9 +20,10 @@
   X(float, 14, 5, 1)         \
   X(float, 13, 5, 1)         \
   X(float, 14, 4, 1)         \
+  X(float, 13, 4, 1)         \
   X(float, 13, 4, 2)
 
-#define SVI_NVARIANTS 17
+#define SVI_NVARIANTS 18
 #define SVI_VCAT(a, b, c, d, e, f) svk_##a##_##b##_##c##_##d##_##e##f
 #define SVI_VNAME(what, T, M, R, NS) SVI_VCAT(what, T, M, R, NS, _v)
 
