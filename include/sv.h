@@ -372,11 +372,12 @@ sv_status sv_batch_autotune(const sv_circuit_desc *circuits, int32_t n_circuits,
  * request per state; Section 6.3 task-parallel queues): each request is an
  * independent circuit with its own qubit count, angles and observable, and
  * asks for E = <psi|H|psi> and dE/dtheta by the adjoint method.  A submission
- * is one persistent launch over a device queue of requests; one workgroup
- * takes one request and runs all of it -- forward sweeps, lambda = H|psi>,
- * backward sweeps with the gradient terms, the gather into dE/dtheta -- with
- * the request's planes held in the L2 and last-level caches.  Results are bitwise independent
- * of the other requests in the submission (one workgroup, fixed order).
+ * is one persistent launch over a device queue of units: a request of up to
+ * 12 qubits is one unit, run by one workgroup -- forward sweeps, lambda =
+ * H|psi>, backward sweeps with the gradient terms, the gather into dE/dtheta --
+ * with its planes in LDS between sweeps; a larger one is split into its tiles,
+ * one workgroup to a tile of each phase.  Results are bitwise independent of
+ * the other requests in the submission (fixed order of every sum).
  * Requests must have 3 <= n_qubits <= sv_serve_max_qubits() (16), ops on at
  * most 3 qubits (targets and controls) and no user matrices; FP64 only.
  * Plans are built on first sight of a request structure (qubits, ops,
@@ -442,7 +443,7 @@ sv_status sv_default_tiling(int32_t n_qubits, sv_dtype dtype, int32_t backward,
 /* Tiling used by SV_FUSE_AUTO for a handle (0 = keep the default): tile_bits =
  * qubits per LDS tile, low_bits = contiguous low qubits in every tile (rows of
  * 2^low_bits elements in HBM), group_bits = qubits per register block.  A
- * combination without a compiled kernel is SV_EINVAL. */
+ * combination without a kernel of its own is SV_EINVAL. */
 sv_status sv_set_tiling(sv_state *st, int32_t tile_bits, int32_t low_bits, int32_t group_bits);
 
 /* The same for the backward sweeps of sv_adjoint_grad (two states per tile). */

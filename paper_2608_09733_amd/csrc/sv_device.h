@@ -933,8 +933,8 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep(SweepArgs a) {
 
 
 // ------------------------------------------------- Kronecker-only sweep
-// Lean variant for sweeps whose every stage is a Kronecker stage.  Stage
-// descriptors and coefficients are uniform and read with scalar loads; LDS
+// Lean variant for sweeps whose every stage is a Kronecker stage or (DN) a dense
+// one.  Stage descriptors and coefficients are uniform and read with scalar loads; LDS
 // holds only the tile, and the code holds only the static stage body, so the
 // register groups stay in VGPRs with no interpreter paths competing for them.
 
@@ -998,8 +998,8 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron(SweepArgs a) {
   // that runs several tiles takes those of the first GTAB stages from a table
   // built once per launch in the LDS the tile leaves free (sized so the
   // workgroups per CU stay as they are).  One that runs a single tile forms
-  // them as it goes: building the table cost it 3 us a launch (21 qubits, 11
-  // sweeps: 619 -> 588 us a pass), while forming them in every tile costs the
+  // them as it goes: building the table cost it 3 us a launch (21 qubits in
+  // 13-bit tiles, 11 sweeps: 619 -> 588 us a pass), while forming them in every tile costs the
   // large states 2% (30 qubits: 202 -> 207 ms).
   constexpr int TILE_BYTES = (1 << M) * (int)sizeof(C2);
   constexpr int GTAB_BYTES = TILE_BYTES >= 131072 ? 30720 : TILE_BYTES >= 65536 ? 14336 : 6144;

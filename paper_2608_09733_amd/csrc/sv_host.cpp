@@ -1563,6 +1563,12 @@ extern "C" sv_status sv_set_stream(sv_state *st, void *stream) {
   return SV_OK;
 }
 
+// Tilings a caller may set: the compiled ones.  FP32 groups of 4 qubits are no
+// setting: the planner takes them for circuits of Kronecker stages (pick_kernel).
+static bool settable(sv_dtype dt, int M, int R) {
+  return svk_has_sweep(dt == SV_C128, M, R, 1) && (dt == SV_C128 || R != 4);
+}
+
 extern "C" sv_status sv_set_tiling(sv_state *st, int32_t tile_bits, int32_t low_bits,
                                    int32_t group_bits) {
   if (!st) return fail(SV_EINVAL, "null handle");
@@ -1571,14 +1577,14 @@ extern "C" sv_status sv_set_tiling(sv_state *st, int32_t tile_bits, int32_t low_
   if (tile_bits) t.M = tile_bits;
   if (low_bits) t.c = low_bits;
   if (group_bits) {
-    if (!svk_has_sweep(st->dtype == SV_C128, t.M, group_bits, 1))
+    if (!settable(st->dtype, t.M, group_bits))
       return fail(SV_EINVAL, "no kernel for tile_bits=%d group_bits=%d", t.M, group_bits);
     t.R = group_bits;
   }
-  if (!svk_has_sweep(st->dtype == SV_C128, t.M, t.R, 1)) {
+  if (!settable(st->dtype, t.M, t.R)) {
     // try the other register width
     int altR = t.R == 5 ? 4 : 5;
-    if (svk_has_sweep(st->dtype == SV_C128, t.M, altR, 1)) t.R = altR;
+    if (settable(st->dtype, t.M, altR)) t.R = altR;
     else return fail(SV_EINVAL, "no kernel for tile_bits=%d", t.M);
   }
   if (t.c < 1 || t.c > t.M - t.R + 1) return fail(SV_EINVAL, "low_bits %d out of range", t.c);
@@ -1745,6 +1751,11 @@ static double plan_model(const std::vector<SweepP> &sweeps, int n, bool dbl, con
   return t;
 }
 
+// What other low qubits than the default's have to gain in the model, whose
+// error is 6%, to be taken (a 13-qubit density matrix took 6 low qubits for 1.6%
+// and lost 2%; what is worth taking gains 4 to 30%).
+static constexpr double kOtherLow = 1.03;
+
 // AUTO plan of least modeled time: the greedy tile planner with and without
 // qubit remapping and, for large states, with per-sweep caps on the gates a
 // sweep takes (which spread the register stages over the sweeps more evenly),
@@ -1778,7 +1789,7 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
         try {
           plan_auto(recs, n, t, plans[i], k.cap, true, k.remap);
           if (k.remap && !layout_consistent(plans[i], n)) continue;
-          model[i] = plan_model(plans[i], n, dbl, t);
+          model[i] = plan_model(plans[i], n, dbl, t) * (k.c == tl.c ? 1.0 : kOtherLow);
         } catch (const std::bad_alloc &) {
           // a candidate without memory is left out
         }

@@ -2146,7 +2146,7 @@ hipError_t svk_launch_batch_reduce(const int32_t *rowptr, const int32_t *slot, c
 }
 
 // ------------------------------------------------------------- serving
-// Small adjoint requests, one workgroup each (see ServeReq).  The tiling is
+// Small adjoint requests, in units of one workgroup (see ServeReq).  The tiling is
 // fixed: 12-qubit tiles of 8-amplitude register groups, 512 threads; psi and
 // lambda tiles side by side take 128 KiB of LDS, so one workgroup runs per CU
 // and a request of n <= 12 qubits is one tile per sweep.
