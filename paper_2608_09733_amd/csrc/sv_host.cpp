@@ -1851,11 +1851,11 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
 // qubits fit one tile of 13 bits: one sweep (HEA 200, 208).  11-bit tiles have
 // more sweeps (18 layered 253).
 // FP32 circuits whose stages are all Kronecker stages take 4-qubit groups: 16
-// wavefronts a CU instead of 8 (28 qubits, 20 layers: 29.8 -> 28.1 ms, HEA 33.0
-// -> 29.7).  The micro-op kernel spills less in 5-qubit ones.  Up to 21 qubits
-// they take 13-bit tiles, two a CU, instead of 14-bit ones, for the same reason
-// (20 layers, us: 12 qubits HEA 192, 161; 16 layered 303, 223; 20 layered 390,
-// 307; 21 HEA 531, 489; 22 HEA 547, 604).
+// wavefronts a CU instead of 8 (22 qubits, 20 HEA layers: 0.92 -> 0.71 ms).  The
+// micro-op kernel spills less in 5-qubit ones.  Up to 21 qubits they take 13-bit
+// tiles, two a CU, instead of 14-bit ones, for the same reason as FP64 (before
+// the tables were kept in FP64, 20 layers, us: 12 qubits HEA 192, 161; 16 layered
+// 303, 223; 20 layered 390, 307; 21 HEA 531, 489; 22 HEA 547, 604).
 static void pick_kernel(const std::vector<GateRec> &recs, int n, bool dbl, Tiling &tl) {
   if (!tl.pick) return;
   if (dbl) {
