@@ -8,11 +8,10 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <exception>
 #include <memory>
 #include <mutex>
-#include <new>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <unordered_map>
 #include <vector>
@@ -1790,7 +1789,7 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
           plan_auto(recs, n, t, plans[i], k.cap, true, k.remap);
           if (k.remap && !layout_consistent(plans[i], n)) continue;
           model[i] = plan_model(plans[i], n, dbl, t) * (k.c == tl.c ? 1.0 : kOtherLow);
-        } catch (const std::bad_alloc &) {
+        } catch (const std::exception &) {
           // a candidate without memory is left out
         }
       }
@@ -1799,9 +1798,10 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
     if (n >= 24) {
       const int hw = (int)std::thread::hardware_concurrency();
       const size_t want = std::min<size_t>(cnt, (size_t)std::min(std::max(hw, 1), 8));
+      pool.reserve(want);   // (so that nothing but a thread's start can throw below)
       try {
         while (pool.size() + 1 < want) pool.emplace_back(work);
-      } catch (const std::system_error &) {
+      } catch (const std::exception &) {
         // no more threads: those there are plan the rest
       }
     }
@@ -2903,6 +2903,8 @@ static sv_status adjoint_enqueue(sv_state *st, const sv_op *ops, int n_ops, cons
                   "ops on at most 4", width);
   }
   Plan *F = nullptr, *B = nullptr;
+  // room for both: get_plan empties a full cache, and F must outlive B's making
+  if (st->plans.size() > 63) st->plans.clear();
   if (n_ops > 0) {
     s = get_plan(st, SV_FUSE_AUTO, tf, ops, n_ops, n_params, false, &F);
     if (s) return s;

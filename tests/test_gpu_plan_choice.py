@@ -33,3 +33,20 @@ def test_plans_from_zero_from_a_state_and_of_a_set_tiling_agree(dtype, tol):
             assert abs(float((re.double() ** 2 + im.double() ** 2).sum()) - 1.0) <= 1e-5
         assert float((re - ref[0]).abs().max()) <= tol and float((im - ref[1]).abs().max()) <= tol
     torch.cuda.empty_cache()
+
+
+def test_a_gradient_on_a_full_plan_cache():
+    from oracle import oracle as O
+    from paper_2608_09733_amd import sv
+    n = 4
+    st = sv.State(n, adjoint=True)
+    for k in range(64):   # as many plans as the handle keeps
+        ops = [I.Op("ry", (q,), params=(0,)) for q in range(n)]
+        ops += [I.Op("x" if k >> b & 1 else "z", (b % n,), ((b + 1) % n,)) for b in range(6)]
+        st.apply(ops, np.array([0.3]))
+    circ, ham = I.hea(n, 2, seed=1), I.tfim(n)
+    st.reset()
+    e, g = st.adjoint_grad(circ.ops, circ.params, ham)
+    st.close()
+    er, gr = O.adjoint_grad(circ, ham)
+    assert abs(e - er) <= 1e-12 and np.max(np.abs(g - gr)) <= 1e-12
