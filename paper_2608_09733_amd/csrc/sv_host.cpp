@@ -1796,8 +1796,11 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
     };
     std::vector<std::thread> pool;
     if (n >= 24) {
+      // a candidate takes about 20 ns for each gate and qubit, a thread 25 us to
+      // start: one for every 60 us of planning
       const int hw = (int)std::thread::hardware_concurrency();
-      const size_t want = std::min<size_t>(cnt, (size_t)std::min(std::max(hw, 1), 8));
+      const size_t fill = 1 + (size_t)((double)cnt * (double)recs.size() * n * 0.02 / 60.0);
+      const size_t want = std::min({cnt, fill, (size_t)std::min(std::max(hw, 1), 8)});
       pool.reserve(want);   // (so that nothing but a thread's start can throw below)
       try {
         while (pool.size() + 1 < want) pool.emplace_back(work);
@@ -1821,19 +1824,22 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
   std::vector<int> lows{tl.c};
   if (tl.pick && n >= 24)
     for (int c : {3, 4, 5, 6, 7})
-      if (c != tl.c && c <= tl.M - 6) lows.push_back(c);
+      if (c != tl.c && c <= tl.M - 6 && (n > 24 || c == 4 || c == 6)) lows.push_back(c);
   for (int c : lows) {
     cand.push_back({c, 1e300, false});
     if (allow_remap) cand.push_back({c, 1e300, true});
   }
   run(0);
   // The caps are tried for states whose sweeps are worth the search, with the
-  // three numbers of low qubits that did best without.
+  // three numbers of low qubits that did best without (at 24, where the whole
+  // search would lengthen a short circuit's first pass, with the best, of 4, 6
+  // and the default's: four layers of a 12-qubit density matrix 3.83 ms before
+  // there was a search, 4.60 with all of it, 3.94 so).
   if (n >= 24) {
     const size_t from = cand.size();
     const int budget = std::min(ncap, 4 << std::min(n - 24, 3));   // 4 at 24 qubits, 32 from 27
     std::stable_sort(lows.begin(), lows.end(), [&](int a, int b) { return low_best[a] < low_best[b]; });
-    if (lows.size() > 3) lows.resize(3);
+    lows.resize(std::min(lows.size(), (size_t)(n > 24 ? 3 : 1)));
     for (int c : lows)
       for (int k = 0; k < budget; k++) cand.push_back({c, caps[k], allow_remap});
     run(from);
