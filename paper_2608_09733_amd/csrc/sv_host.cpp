@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <exception>
+#include <iterator>
 #include <memory>
 #include <mutex>
 #include <string>
@@ -2143,8 +2144,10 @@ static sv_status build_adjoint_plan(int n, bool dbl, const Tiling &tl, const sv_
   return SV_OK;
 }
 
+// The handle's plan of a circuit, made on first sight.  A cache that is full
+// then starts anew, but for `keep`, a plan that the caller still needs.
 static sv_status get_plan(sv_state *st, int mode, const Tiling &tl, const sv_op *ops, int n_ops,
-                          int n_params, bool adjoint, Plan **out) {
+                          int n_params, bool adjoint, Plan **out, const Plan *keep = nullptr) {
   std::string key = (adjoint ? "A" : "F") + plan_key(mode, st->n, tl, st->dtype == SV_C128, ops, n_ops, n_params);
   auto it = st->plans.find(key);
   if (it != st->plans.end()) {
@@ -2157,7 +2160,9 @@ static sv_status get_plan(sv_state *st, int mode, const Tiling &tl, const sv_op 
   if (s) return s;
   s = upload_plan(*P);
   if (s) return s;
-  if (st->plans.size() > 64) st->plans.clear();
+  if (st->plans.size() > 64)
+    for (auto p = st->plans.begin(); p != st->plans.end();)
+      p = p->second.get() == keep ? std::next(p) : st->plans.erase(p);
   *out = P.get();
   st->plans.emplace(key, std::move(P));
   return SV_OK;
@@ -2909,13 +2914,11 @@ static sv_status adjoint_enqueue(sv_state *st, const sv_op *ops, int n_ops, cons
                   "ops on at most 4", width);
   }
   Plan *F = nullptr, *B = nullptr;
-  // room for both: get_plan empties a full cache, and F must outlive B's making
-  if (st->plans.size() > 63) st->plans.clear();
   if (n_ops > 0) {
     s = get_plan(st, SV_FUSE_AUTO, tf, ops, n_ops, n_params, false, &F);
     if (s) return s;
   }
-  s = get_plan(st, SV_FUSE_AUTO, tb, ops, n_ops, n_params, true, &B);
+  s = get_plan(st, SV_FUSE_AUTO, tb, ops, n_ops, n_params, true, &B, F);
   if (s) return s;
   double *S, *Pp;
   void *lre, *lim, *wre, *wim;

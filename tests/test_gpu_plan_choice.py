@@ -50,3 +50,27 @@ def test_a_gradient_on_a_full_plan_cache():
     st.close()
     er, gr = O.adjoint_grad(circ, ham)
     assert abs(e - er) <= 1e-12 and np.max(np.abs(g - gr)) <= 1e-12
+
+
+def test_gradients_of_as_many_circuits_as_the_cache_holds_keep_their_plans():
+    import torch
+    from paper_2608_09733_amd import sv
+    n, count = 10, 32            # two plans each, 64 in all
+    circ, ham = I.hea(n, 40, seed=1), I.tfim(n)
+    oas = [sv.OpArray(circ.ops + [I.Op("x" if k >> b & 1 else "z", (b,), (b + 1,)) for b in range(5)])
+           for k in range(count)]
+    st = sv.State(n, adjoint=True)
+
+    def one(oa):
+        st.reset()
+        st.adjoint_grad(None, circ.params, ham, op_array=oa)
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    first = one(oas[0])
+    free = [one(oa) for oa in oas[1:]][-1]
+    used = first - free          # device memory of 62 plans
+    assert used > 0
+    # dropping them would give that memory back
+    assert max(one(oa) for oa in oas) - free < used // 4
+    st.close()
