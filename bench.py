@@ -502,7 +502,9 @@ def main():
     gates = len(circ.ops)
     zs = I.hamiltonian(n, [("Z", [q], 1.0) for q in range(n)])
     oa = sv.OpArray(circ.ops)
-    sweeps, blocks = sv.plan_stats(n, circ.ops, args.fuse, args.tile, args.low, args.group)
+    # the plan of every step: from the |0..0> that it begins with
+    sweeps, blocks = sv.plan_stats(n, circ.ops, args.fuse, args.tile, args.low, args.group,
+                                   from_zero=True)
     log(f"workload n={n} L={L} gates={gates} plan fuse={args.fuse}: {sweeps} sweeps, {blocks} blocks")
 
     st = sv.State(n, "c128")

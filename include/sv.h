@@ -414,12 +414,19 @@ sv_status sv_serve_submit(sv_serve *s, const sv_circuit_desc *requests, int32_t 
 sv_status sv_serve_free(sv_serve *s);
 
 /* ------------------------------------------------------- plan inspection
- * Number of full-state sweeps and register blocks sv_apply_layer would use
- * for this circuit with these settings (host-only; for tests and tuning).  From
- * 26 qubits on, that of a state other than |0..0>, whose plan is chosen apart. */
+ * Number of full-state sweeps and register blocks of the plan that
+ * sv_apply_layer makes of this circuit on an FP64 handle with this fuse_width
+ * and tiling (0 = the default; see sv_set_tiling), without the pass that a
+ * remaining |0..0> may take (host-only; for tests and tuning).  fuse_width 0: a
+ * pass per gate.  From 26 qubits on a circuit has two plans: this is that of a
+ * state other than |0..0>, sv_plan_stats_zero that of a handle just reset.
+ * Below 26 qubits the two are one.  Errors as for sv_apply_layer's op checks. */
 sv_status sv_plan_stats(int32_t n_qubits, const sv_op *ops, int32_t n_ops, int32_t fuse_width,
                         int32_t tile_bits, int32_t low_bits, int32_t group_bits,
                         int32_t *n_sweeps, int32_t *n_blocks);
+sv_status sv_plan_stats_zero(int32_t n_qubits, const sv_op *ops, int32_t n_ops, int32_t fuse_width,
+                             int32_t tile_bits, int32_t low_bits, int32_t group_bits,
+                             int32_t *n_sweeps, int32_t *n_blocks);
 
 /* Backward program sv_adjoint_grad would run for this circuit (FP64; 0 for a
  * setting = the default backward tiling): its tile sweeps, register stages

@@ -1886,18 +1886,10 @@ static void pick_kernel(const std::vector<GateRec> &recs, int n, bool dbl, Tilin
 // batch planner keeps them whole: a batch launches its Kronecker-only kernel
 // only when every circuit qualifies, and a circuit must round the same alone
 // and in any mix.
-static sv_status build_forward_plan(int mode, int n, bool dbl, Tiling tl, const sv_op *ops,
-                                    int n_ops, int n_params, Plan &P, bool remap = true,
-                                    bool split1q = true) {
-  P.n = n;
-  P.dbl = dbl;
-  P.M = tl.M;
-  P.R = tl.R;
-  P.NS = 1;
-  P.dense = tl.dense;
+static sv_status plan_forward(int mode, int n, bool dbl, Tiling &tl, const sv_op *ops, int n_ops,
+                              int n_params, Plan &P, std::vector<GateRec> &recs,
+                              std::vector<SweepP> &sweeps, bool remap, bool split1q) {
   P.n_user_params = n_params;
-  collect_user_mats(P, ops, n_ops);
-  std::vector<GateRec> recs;
   int um = 0;
   int half_pi = -1;  // parameter slot of the constant pi/2, once needed
   auto const_half_pi = [&]() {
@@ -1989,9 +1981,28 @@ static sv_status build_forward_plan(int mode, int n, bool dbl, Tiling tl, const 
   }
   if (mode < 0) {
     pick_kernel(recs, n, dbl, tl);
-    P.M = tl.M;
-    P.R = tl.R;
+    plan_auto_best(recs, n, dbl, tl, sweeps, remap);
+  } else if (mode > 0) {
+    plan_fused(recs, n, tl, mode, sweeps, true);
   }
+  if (!layout_consistent(sweeps, n)) return fail(SV_EINVAL, "internal: inconsistent qubit layout in plan");
+  return SV_OK;
+}
+
+static sv_status build_forward_plan(int mode, int n, bool dbl, Tiling tl, const sv_op *ops,
+                                    int n_ops, int n_params, Plan &P, bool remap = true,
+                                    bool split1q = true) {
+  P.n = n;
+  P.dbl = dbl;
+  P.NS = 1;
+  P.dense = tl.dense;
+  collect_user_mats(P, ops, n_ops);
+  std::vector<GateRec> recs;
+  std::vector<SweepP> sweeps;
+  sv_status s = plan_forward(mode, n, dbl, tl, ops, n_ops, n_params, P, recs, sweeps, remap, split1q);
+  if (s) return s;
+  P.M = tl.M;
+  P.R = tl.R;
   if (mode == 0) {
     for (GateRec &g : recs) {
       if (g.mo == MO_2L || g.mo == MO_DENSE) {
@@ -2008,14 +2019,10 @@ static sv_status build_forward_plan(int mode, int n, bool dbl, Tiling tl, const 
         emit_gate(P, g, n);
       }
     }
-  } else {
-    std::vector<SweepP> sweeps;
-    if (mode < 0) plan_auto_best(recs, n, dbl, tl, sweeps, remap);
-    else plan_fused(recs, n, tl, mode, sweeps, true);
-    for (const SweepP &sw : sweeps) {
-      int used = 0;
-      emit_sweep(P, recs, sw, n, tl.R, 0, 0, used);
-    }
+  }
+  for (const SweepP &sw : sweeps) {
+    int used = 0;
+    emit_sweep(P, recs, sw, n, tl.R, 0, 0, used);
   }
   return SV_OK;
 }
@@ -2319,12 +2326,25 @@ static sv_status widen_groups(bool dbl, int need, Tiling &tl) {
   return fail(SV_EUNSUPPORTED, "no kernel with %d-qubit register groups", need);
 }
 
+// Tiling that a circuit's plan takes from a handle's: dense stages, or register
+// groups as wide as the widest op (and a fused block).
+static sv_status layer_tiling(int n, bool dbl, const sv_op *ops, int n_ops, int fuse_width, Tiling &tl) {
+  if (fuse_width == SV_FUSE_AUTO && dense_plan(n, dbl, tl)) {
+    tl.dense = true;
+    return SV_OK;
+  }
+  int need = fuse_width >= 2 ? fuse_width : 1;
+  for (int i = 0; i < n_ops; i++) need = std::max(need, ops[i].n_targets + ops[i].n_controls);
+  return widen_groups(dbl, need, tl);
+}
+
 // Whether a call's plan is modeled from |0..0>: by the state that is there
 // from 26 qubits on (1 GiB; 30 qubits, 10 HEA layers: 82 ms from |0..0> with its
 // plan, 96 with the other; from any state 155 and 135).  Below, both kinds of
 // state take the plan from |0..0>, so that an uploaded |0..0> gives the same
 // bits (24 qubits: within 3% of each other from |0..0>).
-static bool plan_from_zero(const sv_state *st) { return st->n < 26 || st->pending_zero; }
+static constexpr int kPlanByState = 26;
+static bool plan_from_zero(const sv_state *st) { return st->n < kPlanByState || st->pending_zero; }
 
 static sv_status apply_layer(sv_state *st, const sv_op *ops, int32_t n_ops, const double *params,
                              int32_t n_params, int32_t fuse_width, bool zero) {
@@ -2336,16 +2356,8 @@ static sv_status apply_layer(sv_state *st, const sv_op *ops, int32_t n_ops, cons
   if (n_ops == 0) return SV_OK;
   Tiling tl = st->tiling;
   tl.zero = zero;
-  // register groups must be as wide as the widest op (and a fused block)
-  int need = fuse_width >= 2 ? fuse_width : 1;
-  for (int i = 0; i < n_ops; i++)
-    need = std::max(need, ops[i].n_targets + ops[i].n_controls);
-  if (fuse_width == SV_FUSE_AUTO && dense_plan(st->n, st->dtype == SV_C128, tl)) {
-    tl.dense = true;
-  } else {
-    s = widen_groups(st->dtype == SV_C128, need, tl);
-    if (s) return s;
-  }
+  s = layer_tiling(st->n, st->dtype == SV_C128, ops, n_ops, fuse_width, tl);
+  if (s) return s;
   Plan *P = nullptr;
   s = get_plan(st, fuse_width, tl, ops, n_ops, n_params, false, &P);
   if (s) return s;
@@ -2888,14 +2900,10 @@ static sv_status adjoint_enqueue(sv_state *st, const sv_op *ops, int n_ops, cons
   Tiling tf = st->tiling;
   tf.zero = plan_from_zero(st);
   Tiling tb = st->adj_tiling;
+  s = layer_tiling(st->n, st->dtype == SV_C128, ops, n_ops, SV_FUSE_AUTO, tf);
+  if (s) return s;
   int width = 1;
   for (int i = 0; i < n_ops; i++) width = std::max(width, ops[i].n_targets + ops[i].n_controls);
-  if (dense_plan(st->n, st->dtype == SV_C128, tf)) {
-    tf.dense = true;
-  } else {
-    s = widen_groups(st->dtype == SV_C128, width, tf);
-    if (s) return s;
-  }
   if (width > tb.R) {
     // wider ops need wider backward register groups (same tile if compiled)
     bool found = false;
@@ -3356,42 +3364,58 @@ extern "C" sv_status sv_fuse_blocks(const sv_op *ops, int32_t n_ops, int32_t wid
   return SV_OK;
 }
 
-extern "C" sv_status sv_plan_stats(int32_t n, const sv_op *ops, int32_t n_ops, int32_t fuse_width,
-                                   int32_t tile_bits, int32_t low_bits, int32_t group_bits,
-                                   int32_t *n_sweeps, int32_t *n_blocks) {
+// Counts of the plan that apply_layer makes of this circuit (`zero`: modeled
+// from |0..0>, Tiling::zero).
+static sv_status plan_counts(int n, const sv_op *ops, int n_ops, int fuse_width, int tile_bits,
+                             int low_bits, int group_bits, bool zero, int32_t *n_sweeps,
+                             int32_t *n_blocks) {
   if (n < 1 || n > SVI_NMAX) return fail(SV_EINVAL, "n %d outside 1..%d", n, SVI_NMAX);
   if (!(fuse_width == 0 || fuse_width == SV_FUSE_AUTO || (fuse_width >= 2 && fuse_width <= 5)))
     return fail(SV_EINVAL, "fuse_width %d", fuse_width);
   std::vector<GateRec> recs;
   sv_status s = lower_all(n, ops, n_ops, recs);
   if (s) return s;
+  if (fuse_width == 0) {   // a pass per gate
+    int live = 0;
+    for (const GateRec &g : recs) live += g.mo != MO_NOP;
+    if (n_sweeps) *n_sweeps = live;
+    if (n_blocks) *n_blocks = live;
+    return SV_OK;
+  }
   Tiling tl = default_tiling(n, SV_C128, 1);
   if (tile_bits || low_bits || group_bits) tl.pick = false;
-  tl.zero = n < 26;
+  tl.zero = zero;
   if (tile_bits) tl.M = tile_bits;
   if (low_bits) tl.c = low_bits;
   if (group_bits) tl.R = group_bits;
-  if (fuse_width > tl.R) tl.R = 5;
-  std::vector<GateRec> live;
-  for (auto &g : recs)
-    if (g.mo != MO_NOP) live.push_back(g);
+  s = layer_tiling(n, true, ops, n_ops, fuse_width, tl);
+  if (s) return s;
+  int np = 0;
+  for (const GateRec &g : recs)
+    for (int p : g.pidx) np = std::max(np, p + 1);
+  Plan P;   // (constants only: nothing is laid out)
+  recs.clear();
   std::vector<SweepP> sweeps;
+  s = plan_forward(fuse_width, n, true, tl, ops, n_ops, np, P, recs, sweeps, true, true);
+  if (s) return s;
   int blocks = 0;
-  if (fuse_width == 0) {
-    if (n_sweeps) *n_sweeps = (int)live.size();
-    if (n_blocks) *n_blocks = (int)live.size();
-    return SV_OK;
-  } else if (fuse_width < 0) {
-    pick_kernel(live, n, true, tl);
-    plan_auto_best(live, n, true, tl, sweeps, true);
-  } else {
-    plan_fused(live, n, tl, fuse_width, sweeps, true);
-  }
-  if (!layout_consistent(sweeps, n)) return fail(SV_EINVAL, "internal: inconsistent qubit layout in plan");
-  for (auto &sw : sweeps) blocks += (int)sw.stages.size();
+  for (const SweepP &sw : sweeps) blocks += (int)sw.stages.size();
   if (n_sweeps) *n_sweeps = (int)sweeps.size();
   if (n_blocks) *n_blocks = blocks;
   return SV_OK;
+}
+
+extern "C" sv_status sv_plan_stats(int32_t n, const sv_op *ops, int32_t n_ops, int32_t fuse_width,
+                                   int32_t tile_bits, int32_t low_bits, int32_t group_bits,
+                                   int32_t *n_sweeps, int32_t *n_blocks) {
+  return plan_counts(n, ops, n_ops, fuse_width, tile_bits, low_bits, group_bits, n < kPlanByState,
+                     n_sweeps, n_blocks);
+}
+
+extern "C" sv_status sv_plan_stats_zero(int32_t n, const sv_op *ops, int32_t n_ops,
+                                        int32_t fuse_width, int32_t tile_bits, int32_t low_bits,
+                                        int32_t group_bits, int32_t *n_sweeps, int32_t *n_blocks) {
+  return plan_counts(n, ops, n_ops, fuse_width, tile_bits, low_bits, group_bits, true, n_sweeps, n_blocks);
 }
 
 extern "C" sv_status sv_adjoint_plan_stats(int32_t n, const sv_op *ops, int32_t n_ops, int32_t n_params,

@@ -86,6 +86,8 @@ def lib():
                                         C.POINTER(i32)]),
         "sv_plan_stats": (C.c_int, [i32, opp, i32, i32, i32, i32, i32, C.POINTER(i32),
                                     C.POINTER(i32)]),
+        "sv_plan_stats_zero": (C.c_int, [i32, opp, i32, i32, i32, i32, i32, C.POINTER(i32),
+                                         C.POINTER(i32)]),
         "sv_adjoint_plan_stats": (C.c_int, [i32, opp, i32, i32, i32, i32, i32, C.POINTER(i32),
                                             C.POINTER(i32), C.POINTER(i32)]),
         "sv_set_tiling": (C.c_int, [vp, i32, i32, i32]),
@@ -441,12 +443,14 @@ def adjoint_plan_stats(n: int, ops, n_params: int, tile_bits: int = 0, low_bits:
 
 
 def plan_stats(n: int, ops, fuse: int = SV_FUSE_AUTO, tile_bits: int = 0, low_bits: int = 0,
-               group_bits: int = 0) -> Tuple[int, int]:
+               group_bits: int = 0, from_zero: bool = False) -> Tuple[int, int]:
+    """(sweeps, register blocks) of the plan that apply() makes of these ops;
+    from_zero: on a state just reset (from 26 qubits on that plan is another)."""
     oa = OpArray(ops)
     s = C.c_int32(0)
     b = C.c_int32(0)
-    _check(lib().sv_plan_stats(n, oa.ptr(), oa.n, fuse, tile_bits, low_bits, group_bits,
-                               C.byref(s), C.byref(b)))
+    f = lib().sv_plan_stats_zero if from_zero else lib().sv_plan_stats
+    _check(f(n, oa.ptr(), oa.n, fuse, tile_bits, low_bits, group_bits, C.byref(s), C.byref(b)))
     return int(s.value), int(b.value)
 
 
