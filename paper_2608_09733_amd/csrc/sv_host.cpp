@@ -2723,7 +2723,7 @@ extern "C" sv_status sv_dm_apply(sv_state *st, int32_t n, const sv_op *ops, int3
     out.push_back(col);
   }
   return apply_layer(st, out.data(), (int32_t)out.size(), p2.empty() ? nullptr : p2.data(),
-                     2 * n_params, SV_FUSE_AUTO, st->pending_zero);
+                     2 * n_params, SV_FUSE_AUTO, plan_from_zero(st));
 }
 
 extern "C" sv_status sv_dm_apply_kraus(sv_state *st, int32_t n, const int32_t *qubits,

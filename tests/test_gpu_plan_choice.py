@@ -74,3 +74,21 @@ def test_gradients_of_as_many_circuits_as_the_cache_holds_keep_their_plans():
     # dropping them would give that memory back
     assert max(one(oa) for oa in oas) - free < used // 4
     st.close()
+
+
+@pytest.mark.parametrize("circ", [I.random_circuit(10, 30, seed=0, max_qubits=3), I.layered(11, 2, seed=3),
+                                  I.hea(12, 1, seed=3)], ids=["mixed10", "layered11", "hea12"])
+def test_a_density_matrix_given_as_zero_takes_the_plan_of_a_reset_one(circ):
+    import torch
+    from paper_2608_09733_amd import sv
+    n = circ.n
+    st = sv.State(2 * n)
+    st.reset()
+    st.dm_apply(circ.ops, circ.params)
+    want = st.re.clone(), st.im.clone()
+    one = np.zeros(1 << 2 * n)
+    one[0] = 1.0
+    st.set_planes(one, np.zeros(1 << 2 * n))
+    st.dm_apply(circ.ops, circ.params)
+    assert torch.equal(st.re, want[0]) and torch.equal(st.im, want[1])
+    st.close()
