@@ -405,10 +405,23 @@ sv_status sv_serve_check(sv_serve *s, const sv_circuit_desc *request);
  * Device buffers grow with hipMalloc when a submission needs more than the
  * largest so far.  Every request is checked before any device work; the
  * first refusal returns its status with the request index in the message.
+ * The units of a request of more than 12 qubits wait for one another on the
+ * device; should such a wait expire (sv_serve_set_spin_limit), the request's
+ * values are NaN, those of the other requests stand, and sv_serve_status
+ * reports it.
  * Errors: SV_EINVAL, SV_EUNBOUND (bad parameter index or non-finite angle),
  * SV_EUNSUPPORTED, SV_EDEVICE. */
 sv_status sv_serve_submit(sv_serve *s, const sv_circuit_desc *requests, int32_t n_requests,
                           const double *params, double *d_out, void *hip_stream);
+
+/* Synchronise `hip_stream`, then SV_EDEVICE if a unit's wait expired in a
+ * submission that has run since the last such report. */
+sv_status sv_serve_status(sv_serve *s, void *hip_stream);
+
+/* Polls of a wait before it expires, for the submissions that follow (default
+ * 1048576, about a second).  A negative value makes every wait expire at once
+ * (tests of the error path). */
+sv_status sv_serve_set_spin_limit(sv_serve *s, int32_t polls);
 
 /* Wait for queued submissions, then release the handle and its buffers. */
 sv_status sv_serve_free(sv_serve *s);

@@ -4070,6 +4070,8 @@ struct ServeSlot {
 
 struct sv_serve {
   int dev = 0;
+  int32_t *d_err = nullptr;       // a wait expired in some submission
+  int32_t spin_limit = 1 << 20;   // about a second of polls
   std::unordered_map<std::string, std::shared_ptr<ServePlan>> plans;
   ServeSlot slot[SVS_SLOTS];
   int next = 0;
@@ -4178,6 +4180,11 @@ extern "C" sv_status sv_serve_submit(sv_serve *sv, const sv_circuit_desc *reques
   int dev = 0;
   HIPCHK(hipGetDevice(&dev));
   if (sv->dev < 0) {
+    if (!sv->d_err) {
+      const int32_t zero = 0;
+      HIPCHK(hipMalloc(&sv->d_err, 256));
+      HIPCHK(hipMemcpy(sv->d_err, &zero, 4, hipMemcpyHostToDevice));
+    }
     for (ServeSlot &sl : sv->slot) HIPCHK(hipEventCreateWithFlags(&sl.done, hipEventDisableTiming));
     sv->dev = dev;
   }
@@ -4428,13 +4435,33 @@ extern "C" sv_status sv_serve_submit(sv_serve *sv, const sv_circuit_desc *reques
     a.units = (const ServeUnit *)(d + o_units) + (g ? units[0].size() : 0);
     a.head = (int32_t *)d + g;
     a.nunits = (int32_t)units[g].size();
-    a.spin_limit = 1 << 20;   // about a second
+    a.err = sv->d_err;
+    a.spin_limit = sv->spin_limit;
     e = svk_launch_serve(a, g, std::min(a.nunits, std::max(1, di.cus)), stream);
   }
   if (e != hipSuccess) return fail(SV_EDEVICE, "serving kernels: %s", hipGetErrorString(e));
   HIPCHK(hipEventRecord(sl.done, stream));
   sl.busy = true;
   sl.held = std::move(plans);
+  return SV_OK;
+}
+
+extern "C" sv_status sv_serve_status(sv_serve *sv, void *stream) {
+  if (!sv) return fail(SV_EINVAL, "null handle");
+  if (sv->dev < 0) return SV_OK;
+  int32_t err = 0;
+  HIPCHK(hipMemcpyAsync(&err, sv->d_err, 4, hipMemcpyDeviceToHost, (hipStream_t)stream));
+  HIPCHK(hipStreamSynchronize((hipStream_t)stream));
+  if (!err) return SV_OK;
+  err = 0;
+  HIPCHK(hipMemcpyAsync(sv->d_err, &err, 4, hipMemcpyHostToDevice, (hipStream_t)stream));
+  HIPCHK(hipStreamSynchronize((hipStream_t)stream));
+  return fail(SV_EDEVICE, "serving: a unit's dependency wait expired; the results of its request are NaN");
+}
+
+extern "C" sv_status sv_serve_set_spin_limit(sv_serve *sv, int32_t polls) {
+  if (!sv) return fail(SV_EINVAL, "null handle");
+  sv->spin_limit = polls;
   return SV_OK;
 }
 
@@ -4446,6 +4473,7 @@ extern "C" sv_status sv_serve_free(sv_serve *sv) {
     if (sl.h_buf) (void)hipHostFree(sl.h_buf);
     if (sl.done) (void)hipEventDestroy(sl.done);
   }
+  if (sv->d_err) (void)hipFree(sv->d_err);
   delete sv;
   return SV_OK;
 }

@@ -306,6 +306,7 @@ struct ServeArgs {
   const SweepArgs *sweeps;
   const ServeUnit *units;
   int32_t *head;              // next unit to take (zero at launch)
+  int32_t *err;               // set when a wait expired (the handle's, see sv_serve_status)
   int32_t nunits;
-  int32_t spin_limit;         // polls before a wait expires
+  int32_t spin_limit;         // polls before a wait expires; < 0: every wait expires at once
 };

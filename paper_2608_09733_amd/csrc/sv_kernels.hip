@@ -2292,8 +2292,9 @@ __global__ void __launch_bounds__(1 << (M - R)) k_serve(ServeArgs sa) {
     if (wave0 && un.wait > 0) {
       // Bounded wait for the request's earlier units, which precede this one
       // in the queue: running workgroups have taken them, so the wait ends.
-      // One that expired all the same makes the request's results NaN.
-      bool expired = false;
+      // One that expired all the same makes the request's results NaN and is
+      // reported by sv_serve_status.
+      bool expired = sa.spin_limit < 0;
       for (int32_t spins = 0; !expired; spins++) {
         const int d = __builtin_amdgcn_readfirstlane(
             __hip_atomic_load(q.ctl, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
@@ -2301,7 +2302,11 @@ __global__ void __launch_bounds__(1 << (M - R)) k_serve(ServeArgs sa) {
         if (spins >= sa.spin_limit) expired = true;
         else __builtin_amdgcn_s_sleep(16);
       }
-      if (expired) __hip_atomic_fetch_or(q.ctl + 1, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (expired) {
+        __hip_atomic_fetch_or(q.ctl + 1, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_fetch_or(sa.err, one, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        stores_done();   // in memory before this workgroup's other waves look at them
+      }
     }
     __syncthreads();
     const int p0 = whole ? 0 : un.phase, p1 = whole ? nf + nb + 2 : un.phase + 1;

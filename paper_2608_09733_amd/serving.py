@@ -232,6 +232,8 @@ class GpuExecutor:
         if not ev.query():
             return None
         v = host.numpy()
+        if np.isnan(v[offs[:-1]]).any():
+            self.serve.check(self.bstream)   # raises if a wait on the device expired
         return [(float(v[offs[k]]), v[offs[k] + 1:offs[k + 1]].copy()) for k in range(len(offs) - 1)]
 
     def close(self):

@@ -117,6 +117,8 @@ def lib():
         "sv_serve_max_qubits": (i32, []),
         "sv_serve_check": (C.c_int, [vp, C.POINTER(SvCircuitDesc)]),
         "sv_serve_submit": (C.c_int, [vp, C.POINTER(SvCircuitDesc), i32, dp, vp, vp]),
+        "sv_serve_status": (C.c_int, [vp, vp]),
+        "sv_serve_set_spin_limit": (C.c_int, [vp, i32]),
         "sv_serve_free": (C.c_int, [vp]),
     }
     for name, (res, args) in sig.items():
@@ -592,9 +594,10 @@ class Batch:
 
 
 class Serve:
-    """Small adjoint requests run whole, one workgroup per request, in one
-    persistent launch per submission (sv_serve_*).  A request is a circuit
-    (.n .ops .params) and an observable; each returns E and dE/dtheta."""
+    """Small adjoint requests in one persistent launch per submission
+    (sv_serve_*): those of up to 12 qubits whole, one workgroup per request,
+    larger ones one workgroup per tile.  A request is a circuit (.n .ops
+    .params) and an observable; each returns E and dE/dtheta."""
 
     def __init__(self):
         h = C.c_void_p()
@@ -644,3 +647,11 @@ class Serve:
                                      C.c_void_p(out_tensor.data_ptr()), _stream_ptr(stream)))
         del keep
         return offs
+
+    def check(self, stream=None):
+        """Synchronise `stream`; raises if a wait between a request's units
+        expired since the last report (that request's values are NaN)."""
+        _check(lib().sv_serve_status(self.h, _stream_ptr(stream)))
+
+    def set_spin_limit(self, polls: int):
+        _check(lib().sv_serve_set_spin_limit(self.h, int(polls)))

@@ -146,3 +146,33 @@ def test_serve_refuses_before_device_work(serve):
     assert ei.value.status == -5 and "request 1" in str(ei.value)
     torch.cuda.synchronize()
     assert bool((out == 7.0).all())
+
+
+def test_expired_waits_are_reported():
+    # forced from the host: a negative spin limit makes every wait expire at
+    # once, so the kernels still exit normally
+    import torch
+    from paper_2608_09733_amd import sv
+    reqs = _requests()
+    S = sv.Serve()
+    S.check()                                # nothing submitted
+    S.set_spin_limit(-1)
+    print("[case] serve expired waits", flush=True)
+    out, offs = _submit(S, reqs)
+    with pytest.raises(sv.SvError, match="dependency wait expired"):
+        S.check()
+    S.check()                                # reported once
+    bad = _split(out, offs)
+    S.set_spin_limit(1 << 20)
+    out, offs = _submit(S, reqs)
+    S.check()
+    good = _split(out, offs)
+    for (c, _), (e, g), (be, bg) in zip(reqs, good, bad):
+        if c.n > 12:                         # several units, which wait
+            assert np.isnan(be) and np.isnan(bg).all()
+        else:
+            assert be == e and np.array_equal(bg, g)
+    for k, (c, h) in enumerate(reqs):
+        e_ref, g_ref = O.adjoint_grad(c, h)
+        assert _close(good[k], (e_ref, np.asarray(g_ref)[:c.n_params])), (k, c.n)
+    S.close()
