@@ -1155,19 +1155,6 @@ static void emit_sweep(Plan &P, std::vector<GateRec> &recs, const SweepP &sw, in
       sd.kcoef = P.ncoef;
       const int G = 1 << R;
       P.ncoef += 4 * R + 4 * G + 2;
-      uint32_t rmask = 0;
-      for (int r : st.rops) {
-        GateRec &g = recs[r];
-        int t = local_of(g.t[0]);
-        rmask |= 1u << t;
-        CoefDesc cd{};
-        cd.kind = g.coef_kind;
-        cd.fmt = CF_FASTR | (g.dagger ? CF_DAGGER : 0) | (P.dbl ? CF_FORM0 : 0);
-        for (int k = 0; k < 3; k++) cd.pidx[k] = g.pidx[k];
-        cd.dst = sd.kcoef + 4 * t;
-        P.coefs.push_back(cd);
-      }
-      sd.rmask = rmask;
       // fast-Givens scales of the stage's real gates (folded into D_after or a scalar)
       auto push_scales = [&]() {
         for (int r : st.rops) {
@@ -1178,6 +1165,28 @@ static void emit_sweep(Plan &P, std::vector<GateRec> &recs, const SweepP &sw, in
           P.factors.push_back(f);
         }
       };
+      uint32_t rmask = 0;
+      const int rot0 = (int)P.factors.size();
+      if (!P.dbl) push_scales();
+      for (size_t i = 0; i < st.rops.size(); i++) {
+        GateRec &g = recs[st.rops[i]];
+        int t = local_of(g.t[0]);
+        rmask |= 1u << t;
+        CoefDesc cd{};
+        cd.kind = g.coef_kind;
+        if (P.dbl) {
+          cd.fmt = CF_FASTR | (g.dagger ? CF_DAGGER : 0) | CF_FORM0;
+          for (int k = 0; k < 3; k++) cd.pidx[k] = g.pidx[k];
+        } else {
+          cd.fmt = CF_FASTS | (g.dagger ? CF_DAGGER : 0);
+          cd.src = rot0;
+          cd.pidx[0] = (int)st.rops.size();
+          cd.pidx[1] = (int)i;
+        }
+        cd.dst = sd.kcoef + 4 * t;
+        P.coefs.push_back(cd);
+      }
+      sd.rmask = rmask;
       bool dag = false;
       for (int r : st.recs) dag = dag || recs[r].dagger;
       auto table = [&](const std::vector<int> &rs, int dst, bool scales) {
@@ -3603,7 +3612,7 @@ extern "C" sv_status sv_batch_plan(const sv_circuit_desc *circuits, int32_t n_ci
     for (CoefDesc cd : P.coefs) {
       const int fmt = cd.fmt & 0xff;
       cd.dst += (int32_t)coef_off;
-      if (fmt == CF_TABLE || fmt == CF_SCALE) cd.src += (int32_t)factor_off;
+      if (fmt == CF_TABLE || fmt == CF_SCALE || fmt == CF_FASTS) cd.src += (int32_t)factor_off;
       else if (fmt == CF_COPY) cd.src += (int32_t)static_off;
       else if (fmt != CF_IDENT2)
         for (int q = 0; q < 3; q++)

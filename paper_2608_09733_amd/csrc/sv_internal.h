@@ -72,7 +72,7 @@ struct MicroOp {
 //              form 0: x' = x - k y, y' = k x + y      (k = s/c, scale c)
 //              form 1: x' = k x - y, y' = x + k y      (k = c/s, scale s)
 //            FP64 plans always take form 0 (CF_FORM0); FP32 plans take form 1
-//            when |c| < 2^-12 |s| (fast_givens).
+//            for |c| < |s| in a stage whose k would grow too far (fast_givens).
 //   ST_DENSE: one 2^R x 2^R complex matrix on the group (row-major at kcoef, and
 //            behind it the mask of the entries that are not zero), made on the
 //            device from the stage's micro-ops, in the threads whose index has
@@ -179,6 +179,7 @@ enum {
   CF_FASTR = 9,    // fast-Givens record {form, k, scale, 0} of a real 1q gate (see CF_FORM0)
   CF_SCALE = 10,   // real scalar: product of the fast-Givens scales of factors [src, +pidx[0])
   CF_CONSTS = 11,  // copy `len` doubles from the parameter vector at `src` (plan constants)
+  CF_FASTS = 12,   // as CF_FASTR, of factor pidx[1] among a stage's factors [src, +pidx[0]) (see CF_FORM0)
 };
 
 // One factor of a diagonal table: entry j is multiplied, when (j & cm) == cv,
@@ -194,8 +195,9 @@ struct TabFactor {
 #define CF_DAGGER 0x100
 // CF_FASTR / CF_SCALE / CF_TABLE scale factors: a rotation always takes form 0
 // (k = s / c, scale c; the FP64 kernels apply it without a form branch).
-// Without the flag the form with |k| <= 1 is chosen (FP32, whose range a
-// product of large k could leave).
+// Without the flag (FP32, whose range a product of large k could leave) the
+// rotations of a stage take form 0 together or each the form with |k| <= 1
+// (fast_givens); CF_SCALE and CF_TABLE list the stage's rotations first.
 #define CF_FORM0 0x200
 
 struct CoefDesc {

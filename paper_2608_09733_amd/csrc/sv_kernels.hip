@@ -162,13 +162,16 @@ __device__ void gate_local(int kind, const double *th, double *m /* interleaved,
 // (Gentleman 1973): out = {form, k, scale, 0}, r = scale * (form matrix).
 // form0: a rotation always takes form 0 (k = s / c; c is never exactly zero
 // for a rotation angle that is a double, so k is finite, and the error of
-// (x - k y) c stays within a few ulps of |x c| + |y s|).  FP32 takes form 0
-// while |c| >= 2^-12 |s|, so that the products of a stage's k (up to 2^60 for
-// five rotations) and scales stay well inside the range of a float, and its k
-// is a float with the scale that makes the two an exact rotation: rounding k
-// then turns the angle by at most a quarter ulp, whatever |k|, and loses no
-// norm.
-__device__ void fast_givens(const double *r, double *out, bool form0 = false) {
+// (x - k y) c stays within a few ulps of |x c| + |y s|).  FP32 takes form 0 too
+// unless the stage's k are large (small_k, set when the product of the |k| above
+// 1 passes 2^12: 1% of the stages of four random rotations), so that an
+// amplitude between a stage's rotations and its scales is at most about 2^14
+// times the largest; its k is a float with the scale that makes the two an
+// exact rotation: rounding k then turns the angle by at most a quarter ulp,
+// whatever |k|, and loses no norm.  (28 qubits, 20 layers: 21.4 ms, as with
+// form 1 only below |c| = 2^-12 |s|, which let a stage grow by 2^48; every |k|
+// at most 1: 23.2 ms.)
+__device__ void fast_givens(const double *r, double *out, bool form0 = false, bool small_k = false) {
   // rotation [[c,-s],[s,c]] vs reflection [[a,b],[b,-a]]
   const bool rot = fabs(r[0] - r[3]) + fabs(r[1] + r[2]) <= fabs(r[0] + r[3]) + fabs(r[1] - r[2]);
   if (rot) {
@@ -177,7 +180,7 @@ __device__ void fast_givens(const double *r, double *out, bool form0 = false) {
     if (form0) {
       out[0] = 0; out[1] = s / c; out[2] = c;
     } else {
-      const bool f1 = fabs(c) < 0x1p-12 * fabs(s);
+      const bool f1 = small_k && fabs(c) < fabs(s);
       const double k = (double)(float)(f1 ? c / s : s / c);
       out[0] = f1 ? 1 : 0;
       out[1] = k;
@@ -192,8 +195,8 @@ __device__ void fast_givens(const double *r, double *out, bool form0 = false) {
   out[3] = 0.0;
 }
 
-// Coefficients of one descriptor that is no product of factors (CF_TABLE,
-// CF_SCALE), written at coef + cd.dst.
+// Coefficients of one descriptor without factors (those: CF_TABLE, CF_SCALE,
+// CF_FASTS), written at coef + cd.dst.
 __device__ void build_coef(const CoefDesc &cd, const double *params, const double *statics,
                            const TabFactor *fac, double *coef) {
   const int fmt = cd.fmt & 0xff;
@@ -303,12 +306,8 @@ __device__ void build_coef_group(const CoefDesc &cd, const double *params, const
                                  float *coef32 = nullptr) {
   const int fmt = cd.fmt & 0xff;
   const bool table = fmt == CF_TABLE;
-  if (!table && fmt != CF_SCALE) {
-    if (l == 0) {
-      build_coef(cd, params, statics, fac, coef);
-      if (coef32 && fmt == CF_FASTR)
-        for (int k = 0; k < 4; k++) coef32[cd.dst + k] = (float)coef[cd.dst + k];
-    }
+  if (!table && fmt != CF_SCALE && fmt != CF_FASTS) {
+    if (l == 0) build_coef(cd, params, statics, fac, coef);
     return;
   }
   const bool dag = (cd.fmt & CF_DAGGER) != 0;
@@ -326,19 +325,38 @@ __device__ void build_coef_group(const CoefDesc &cd, const double *params, const
     // this lane's factor: the diagonal (d0, d1), or a real scale in both
     double d0r = 1.0, d0i = 0.0, d1r = 1.0, d1i = 0.0;
     uint32_t mask = 0, cm = 0, cv = 0;
+    double m[8], r[4] = {1.0, 0.0, 0.0, 1.0};   // r: a scale's real 2x2
+    bool scale = false;
+    TabFactor tf{};
     if (f1 + l < nf) {
-      const TabFactor tf = fac[cd.src + f1 + l];
+      tf = fac[cd.src + f1 + l];
+      double tt[3] = {tf.pidx >= 0 ? params[tf.pidx] : 0.0, 0.0, 0.0};
+      gate_local(tf.kind, tt, m);
+      scale = !table || tf.neg == 2;
+      if (scale) {
+        r[0] = m[0]; r[1] = dag ? m[4] : m[2]; r[2] = dag ? m[2] : m[4]; r[3] = m[6];
+      }
+    }
+    bool small_k = false;   // (at most 5 rotations, listed first: the first round has them all)
+    if (!f0) {
+      double grow = fmax(1.0, fabs(r[2]) / fabs(r[0]));
+#pragma unroll
+      for (int d = 1; d < COEF_LANES; d <<= 1) grow *= __shfl_xor(grow, d, COEF_LANES);
+      small_k = grow > 0x1p12;
+    }
+    if (f1 + l < nf) {
       mask = tf.mask;
       cm = tf.cm;
       cv = tf.cv;
-      double m[8];
-      double tt[3] = {tf.pidx >= 0 ? params[tf.pidx] : 0.0, 0.0, 0.0};
-      gate_local(tf.kind, tt, m);
-      if (!table || tf.neg == 2) {
-        double r[4] = {m[0], m[2], m[4], m[6]}, rec[4];   // real 2x2
-        if (dag) { const double t = r[1]; r[1] = r[2]; r[2] = t; }
-        fast_givens(r, rec, f0);
+      if (scale) {
+        double rec[4];
+        fast_givens(r, rec, f0, small_k);
         d0r = d1r = rec[2];
+        if (fmt == CF_FASTS && l == cd.pidx[1])
+          for (int k = 0; k < 4; k++) {
+            coef[cd.dst + k] = rec[k];
+            if (coef32) coef32[cd.dst + k] = (float)rec[k];
+          }
       } else if (tf.neg) {
         d0r = d1r = -1.0;
       } else {
@@ -363,6 +381,7 @@ __device__ void build_coef_group(const CoefDesc &cd, const double *params, const
       }
     }
   }
+  if (fmt == CF_FASTS) return;
   double *out = coef + cd.dst;
 #pragma unroll
   for (int e = 0; e < EPL; e++) {

@@ -58,3 +58,27 @@ def test_gradients_near_a_flip():
     er, gr = O.adjoint_grad(circ, ham)
     # sums over 2 n terms of |coefficient| <= 1
     assert abs(e - er) <= 2 * n * TOL32 and np.max(np.abs(g - gr)) <= 2 * n * TOL32
+
+
+# Amplitudes may be far from 1: between a stage's rotations and its scales they
+# grow by at most about 2^14, so 2^100 times a state gives 2^100 times the result.
+@pytest.mark.parametrize("n", [5, 13, 16])
+@pytest.mark.parametrize("group", [0, 5])
+@pytest.mark.parametrize("mixed", [False, True])
+def test_large_amplitudes_stay_finite(n, group, mixed):
+    from paper_2608_09733_amd import sv
+    near = [math.pi - 1e-3, 1.0, math.pi + 2e-3, math.pi - 5e-4, -math.pi + 1e-3]
+    circ = _circuit(n, lambda l, q: near[(3 * l + q) % len(near)])
+    ops = circ.ops + ([I.Op("rxx", (0, n - 1), params=(0,))] if mixed else [])
+    re, im = I.random_state(n, n)
+    re, im = re.astype(np.float32), im.astype(np.float32)
+    st = sv.State(n, "c64")
+    if group:
+        st.set_tiling(0, 0, group)
+    got = []
+    for scale in (np.float32(1), np.float32(2.0 ** 100)):
+        st.set_planes(re * scale, im * scale)
+        st.apply(ops, circ.params)
+        got.append([p / scale for p in st.planes()])
+    st.close()
+    assert np.isfinite(got[1]).all() and np.array_equal(got[0], got[1])
