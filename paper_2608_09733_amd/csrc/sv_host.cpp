@@ -1,6 +1,7 @@
 // Host runtime of libsv: argument validation, circuit lowering, the sweep /
 // stage planner, plan cache, kernel launches and the C ABI of include/sv.h.
 #include <hip/hip_runtime.h>
+#include <sched.h>
 
 #include <algorithm>
 #include <atomic>
@@ -352,22 +353,150 @@ struct PendRec {
   bool diag;
 };
 
-static int closure_count(const std::vector<PendRec> &pend, uint64_t T, double cost_cap) {
-  uint64_t blocked = 0, blocked_nd = 0;
-  int cnt = 0;
-  double cost = 0.0;
-  for (const PendRec &r : pend) {
-    const bool free = (r.q & blocked) == 0 && (r.diag || (r.q & blocked_nd) == 0);
-    if ((r.q & ~T) == 0 && free && cost + r.cost <= cost_cap) {
-      cnt++;
-      cost += r.cost;
-    } else {
-      if (r.diag) blocked_nd |= r.q;
-      else blocked |= r.q;
-      if ((blocked & T) == T) break;
+// Bit-sliced whole numbers, one for each bit of a word: += v in these lanes.
+static void add_lanes(uint64_t (&slice)[32], uint64_t lanes, uint32_t v) {
+  for (int b = 0; v >> b; b++) {
+    uint64_t c = (v >> b) & 1u ? lanes : 0;
+    for (int k = b; c && k < 32; k++) {
+      const uint64_t t = slice[k] & c;
+      slice[k] ^= c;
+      c = t;
     }
   }
-  return cnt;
+}
+
+static int lane_value(const uint64_t (&slice)[32], int lane) {
+  int v = 0;
+  for (int b = 0; b < 31; b++) v |= (int)((slice[b] >> lane) & 1) << b;
+  return v;
+}
+
+// Closure sizes of T (at [n]) and of T with each qubit q that is not in it (at
+// [q]), all in one pass over the pending records: bit l of a word stands for
+// tile l.  Counts and costs are bit-sliced (costs are whole numbers).  With one
+// pass per tile, and for the stages one per group, the 106 plans of 30 qubits and
+// 20 layers took 291 ms on one core and 43 on eight, with these 100 to 118 and 20.
+static void closure_counts(const std::vector<PendRec> &pend, int n, uint64_t T, double cost_cap,
+                           int *cnt) {
+  uint64_t all = 1ull << n;
+  for (int q = 0; q < n; q++)
+    if (!((T >> q) & 1)) all |= 1ull << q;
+  uint64_t blocked[SVI_NMAX] = {0}, blocked_nd[SVI_NMAX] = {0};
+  // what every tile takes is counted aside, and `most` bounds any tile's cost
+  uint64_t count[32] = {0}, cost[32] = {0};
+  int count_all = 0;
+  double cost_all = 0.0, most = 0.0;
+  int since = 0;
+  uint64_t dead = 0;   // qubits blocked for every tile: a record on such alone changes nothing
+  for (const PendRec &r : pend) {
+    if ((r.q & ~dead) == 0) continue;
+    const uint64_t miss = r.q & ~T;
+    uint64_t take = miss == 0 ? all : (miss & (miss - 1)) == 0 ? miss : 0;
+    if (take)
+      for (uint64_t m = r.q; m; m &= m - 1) {
+        const int p = __builtin_ctzll(m);
+        take &= ~(r.diag ? blocked[p] : blocked[p] | blocked_nd[p]);
+      }
+    if (take && most + r.cost > cost_cap) {
+      // lanes whose cost stays within the cap: cost <= room
+      const double room = cost_cap - r.cost - cost_all;
+      uint64_t le = 0;
+      if (room >= 0.0) {
+        const uint32_t v = (uint32_t)std::min(room, 1e9);
+        uint64_t eq = ~0ull;
+        for (int b = 31 - __builtin_clz((uint32_t)(most - cost_all) | v | 1u); b >= 0; b--) {
+          if ((v >> b) & 1u) {
+            le |= eq & ~cost[b];
+            eq &= cost[b];
+          } else {
+            eq &= ~cost[b];
+          }
+        }
+        le |= eq;
+      }
+      take &= le;
+    }
+    if (take == all) {
+      count_all++;
+      cost_all += r.cost;
+    } else {
+      add_lanes(count, take, 1);
+      add_lanes(cost, take, (uint32_t)r.cost);
+    }
+    if (take) most += r.cost;
+    if (take != all) {
+      for (uint64_t m = r.q; m; m &= m - 1) {
+        const int p = __builtin_ctzll(m);
+        if (r.diag) blocked_nd[p] |= all & ~take;
+        else if ((blocked[p] |= all & ~take) == all) dead |= 1ull << p;
+      }
+      if (++since == 32) {
+        // over where every tile's own qubits are all blocked
+        since = 0;
+        uint64_t over = 1ull << n;
+        for (uint64_t m = all & ~over; m; m &= m - 1) over |= blocked[__builtin_ctzll(m)] & (m & -m);
+        for (uint64_t m = T; m && over; m &= m - 1) over &= blocked[__builtin_ctzll(m)];
+        if (over == all) break;
+      }
+    }
+  }
+  for (int l = 0; l <= n; l++) cnt[l] = count_all + lane_value(count, l);
+}
+
+// What closure_kron() reads of a pending record.
+struct PendKron {
+  int rec;
+  uint64_t q;         // its qubits
+  uint64_t need;      // those that must be in the group
+  int role;           // 0 permutation, 1 diagonal, 2 rotation, -1 fits no Kronecker stage
+  bool diag;
+};
+
+// closure_kron's scores of S (at [n]) and of S with each other qubit of the tile
+// Tt (at [q]), in one pass as in closure_counts.
+static void kron_scores(const std::vector<PendKron> &pend, int n, uint64_t S, uint64_t Tt, int *score) {
+  const uint64_t all = (1ull << n) | (Tt & ~S);
+  uint64_t blocked[SVI_NMAX] = {0}, blocked_nd[SVI_NMAX] = {0};
+  uint64_t rq[SVI_NMAX] = {0}, dA[SVI_NMAX] = {0}, pq[SVI_NMAX] = {0};
+  uint64_t sum[32] = {0}, leading = all, over = 0, dead = 0;
+  for (const PendKron &r : pend) {
+    if ((r.q & ~dead) == 0) continue;
+    const uint64_t miss = r.need & ~S;
+    uint64_t take = r.role < 0 ? 0 : miss == 0 ? all : (miss & (miss - 1)) == 0 ? miss & all : 0;
+    take &= ~over;
+    if (take) {
+      uint64_t bad = 0, after = 0;
+      for (uint64_t m = r.q; m; m &= m - 1) {
+        const int p = __builtin_ctzll(m);
+        bad |= r.diag ? blocked[p] : blocked[p] | blocked_nd[p];
+        if (r.role == 1) bad |= pq[p], after |= rq[p];
+        if (r.role == 2) bad |= rq[p] | dA[p] | pq[p];
+      }
+      take &= ~bad;
+      for (uint64_t m = r.q; m; m &= m - 1) {
+        const int p = __builtin_ctzll(m);
+        if (r.role == 0) pq[p] |= take & ~leading;
+        if (r.role == 1) dA[p] |= take & after;
+        if (r.role == 2) rq[p] |= take;
+      }
+      if (r.role != 0) leading &= ~take;
+      add_lanes(sum, take, r.role == 2 ? kRotWeight : 1);
+    }
+    if (take != all) {
+      for (uint64_t m = r.q; m; m &= m - 1) {
+        const int p = __builtin_ctzll(m);
+        if (r.diag) blocked_nd[p] |= all & ~take;
+        else if ((blocked[p] |= all & ~take) == all) dead |= 1ull << p;
+      }
+      // a group is over where its own qubits are all blocked
+      uint64_t o = 1ull << n;
+      for (uint64_t m = Tt & ~S; m; m &= m - 1) o |= blocked[__builtin_ctzll(m)] & (m & -m);
+      for (uint64_t m = S; m && o; m &= m - 1) o &= blocked[__builtin_ctzll(m)];
+      over |= o;
+      if (over == all) break;
+    }
+  }
+  for (int l = 0; l <= n; l++) score[l] = lane_value(sum, l);
 }
 
 // Qubits of the earliest pending record that is blocked w.r.t. T (tie-break).
@@ -427,11 +556,19 @@ static void plan_stages(const std::vector<GateRec> &recs, const std::vector<int>
   std::vector<char> done(recs.size(), 0);
   std::vector<char> veto(recs.size(), 0);
   bool mixed = false;   // some record fits no Kronecker stage
-  for (int r : take) {
-    if (dense ? recs[r].pmask != 0 : recs[r].mo == MO_DENSE) veto[r] = 1;
-    mixed = mixed || !kron_eligible(recs[r]);
-  }
   const uint64_t Ttile = tile_mask(sw);
+  std::vector<PendKron> pend;
+  for (int r : take) {
+    const GateRec &g = recs[r];
+    if (dense ? g.pmask != 0 : g.mo == MO_DENSE) veto[r] = 1;
+    mixed = mixed || !kron_eligible(g);
+    if (!allow_kron) continue;
+    // (an X's target may be any tile qubit)
+    const uint64_t tq = g.mo == MO_X ? 1ull << g.t[0] : 0;
+    pend.push_back(PendKron{r, g.qmask, tq & Ttile ? g.qmask & ~tq : g.qmask,
+                            !kron_eligible(g) ? -1 : g.mo == MO_X || g.mo == MO_SWAP ? 0
+                            : is_diag(g) ? 1 : 2, is_diag(g)});
+  }
   size_t left = take.size();
   const int mm = std::max(sw.m, R);
   while (left) {
@@ -464,40 +601,37 @@ static void plan_stages(const std::vector<GateRec> &recs, const std::vector<int>
       }
       return S;
     };
+    auto grow_kron = [&]() {
+      pend.erase(std::remove_if(pend.begin(), pend.end(), [&](const PendKron &r) { return done[r.rec]; }),
+                 pend.end());
+      uint64_t S = recs[first].qmask;
+      int score[SVI_NMAX + 1];
+      while (popc(S) < R) {
+        kron_scores(pend, n, S, Ttile, score);
+        int best = -1, bestv = score[n];
+        for (int q = 0; q < n; q++) {
+          if (!(Ttile & (1ull << q)) || (S & (1ull << q))) continue;
+          if (score[q] > bestv) { bestv = score[q]; best = q; }
+        }
+        if (best < 0) break;
+        S |= 1ull << best;
+      }
+      return S;
+    };
     bool kron = allow_kron && kron_eligible(recs[first]);
     if (kron && dense && mixed) {
       // a dense stage costs about 1.3 Kronecker stages: taken if it holds more
       // records for that (27 qubits, 200 mixed gates: 28.4 ms with 1.3 as with
       // 1.8 and with 1, most sweeps being bound by memory)
       StageP probe;
-      uint64_t S = recs[first].qmask;
-      while (popc(S) < R) {
-        int best = -1, bestv = closure_kron(recs, take, done, S, Ttile, nullptr);
-        for (int q = 0; q < n; q++) {
-          if (!(Ttile & (1ull << q)) || (S & (1ull << q))) continue;
-          int v = closure_kron(recs, take, done, S | (1ull << q), Ttile, nullptr);
-          if (v > bestv) { bestv = v; best = q; }
-        }
-        if (best < 0) break;
-        S |= 1ull << best;
-      }
+      const uint64_t S = grow_kron();
       closure_kron(recs, take, done, S, Ttile, &probe);
       std::vector<int> got;
       closure(recs, take, done, grow(), &got, &veto);
       if (10 * got.size() > 13 * probe.recs.size()) kron = false;
     }
     if (kron) {
-      uint64_t S = recs[first].qmask;
-      while (popc(S) < R) {
-        int best = -1, bestv = closure_kron(recs, take, done, S, Ttile, nullptr);
-        for (int q = 0; q < n; q++) {
-          if (!(Ttile & (1ull << q)) || (S & (1ull << q))) continue;
-          int v = closure_kron(recs, take, done, S | (1ull << q), Ttile, nullptr);
-          if (v > bestv) { bestv = v; best = q; }
-        }
-        if (best < 0) break;
-        S |= 1ull << best;
-      }
+      const uint64_t S = grow_kron();
       st.kron = true;
       closure_kron(recs, take, done, S, Ttile, &st);
       for (int r : st.recs) { done[r] = 1; left--; }
@@ -535,7 +669,7 @@ static void plan_stages(const std::vector<GateRec> &recs, const std::vector<int>
     for (int i = 0; i < used; i++) taken |= 1ull << st.gq[i];
     for (int p = mm - 1; p >= 0 && used < R; p--)
       if (!(taken & (1ull << p))) { st.gq[used++] = p; taken |= 1ull << p; }
-    sw.stages.push_back(st);
+    sw.stages.push_back(std::move(st));
   }
 }
 
@@ -602,27 +736,23 @@ static void plan_auto(const std::vector<GateRec> &recs, int n, const Tiling &tl,
   // occupants in one tile
   remap = remap && n > M && 2 * c <= M;
   size_t start = 0;
+  std::vector<int> sub = cand;       // the records that are left
+  std::vector<PendRec> pend;
+  for (const GateRec &g : recs) pend.push_back(PendRec{g.qmask, g.cost, is_diag(g)});
   while (left) {
     while (start < cand.size() && done[cand[start]]) start++;
-    std::vector<int> sub;
-    std::vector<PendRec> pend;
-    for (size_t i = start; i < cand.size(); i++)
-      if (!done[cand[i]]) {
-        const GateRec &g = recs[cand[i]];
-        sub.push_back(cand[i]);
-        pend.push_back(PendRec{g.qmask, g.cost, is_diag(g)});
-      }
     uint64_t T = 0;
     for (int p = 0; p < c; p++) T |= 1ull << occ[p];
     if (n <= M) {
       T = n >= 64 ? ~0ull : ((1ull << n) - 1);
     } else {
       for (int step = c; step < M; step++) {
-        int best = -1, bestv = closure_count(pend, T, cost_cap);
+        int cnt[SVI_NMAX + 1];
+        closure_counts(pend, n, T, cost_cap, cnt);
+        int best = -1, bestv = cnt[n];
         for (int q = 0; q < n; q++) {
           if (T & (1ull << q)) continue;
-          int v = closure_count(pend, T | (1ull << q), cost_cap);
-          if (v > bestv) { bestv = v; best = q; }
+          if (cnt[q] > bestv) { bestv = cnt[q]; best = q; }
         }
         if (best < 0) {
           uint64_t fq = first_blocked_qubits(recs, sub, done, T) & ~T;
@@ -645,6 +775,14 @@ static void plan_auto(const std::vector<GateRec> &recs, int n, const Tiling &tl,
     set_tile(sw, n, T, c, occ.data());
     plan_stages(recs, take, sw, tl.R, n, kron, tl.dense);
     for (int r : take) { done[r] = 1; left--; }
+    size_t kept = 0;
+    for (size_t i = 0; i < sub.size(); i++)
+      if (!done[sub[i]]) {
+        sub[kept] = sub[i];
+        pend[kept++] = pend[i];
+      }
+    sub.resize(kept);
+    pend.resize(kept);
     if (remap) {
       std::vector<int> want = occ;
       if (!left) {
@@ -1794,14 +1932,22 @@ static double plan_model(const std::vector<GateRec> &recs, const std::vector<Swe
 // and lost 2%; what is worth taking gains 4 to 30%).
 static constexpr double kOtherLow = 1.03;
 
+// CPUs that this process may run on (a process held to one core plans alone).
+static int usable_cpus() {
+  cpu_set_t set;
+  const int n = sched_getaffinity(0, sizeof set, &set) == 0 ? CPU_COUNT(&set) : 0;
+  return n > 0 ? n : (int)std::thread::hardware_concurrency();
+}
+
 // AUTO plan of least modeled time: the greedy tile planner with and without
 // qubit remapping and, for large states, with per-sweep caps on the gates a
 // sweep takes (which spread the register stages over the sweeps more evenly),
 // each with several numbers of contiguous low qubits where the tiling is the
 // default.  The candidates depend only on the circuit and the state size, and
 // of equal ones the first is taken, so the choice is deterministic.  They are
-// planned by several threads: planned one after the other, 33 of them took
-// 70 ms at 30 qubits and 20 layers, a third of the pass.
+// planned by as many threads as there are cores for, up to 8 (106 of them at 30
+// qubits and 20 layers, where a pass takes 198 ms: 100 to 118 ms on one core, 20
+// on eight).
 static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Tiling &tl,
                            std::vector<SweepP> &out, bool allow_remap) {
   struct Cand { int c; double cap; bool remap; };
@@ -1814,8 +1960,6 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
   double low_best[SVI_MMAX + 1];   // by number of low qubits
   std::fill(low_best, low_best + SVI_MMAX + 1, 1e300);
   Tiling won = tl;
-  bool lean = true;   // every stage runs in the lean kernels
-  for (const GateRec &g : recs) lean = lean && (tl.dense || kron_eligible(g));
   auto run = [&](size_t from) {
     const size_t cnt = cand.size() - from;
     std::vector<std::vector<SweepP>> plans(cnt);
@@ -1839,7 +1983,7 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
     if (n >= 24) {
       // a candidate takes about 20 ns for each gate and qubit, a thread 25 us to
       // start: one for every 60 us of planning
-      const int hw = (int)std::thread::hardware_concurrency();
+      const int hw = usable_cpus();
       const size_t fill = 1 + (size_t)((double)cnt * (double)recs.size() * n * 0.02 / 60.0);
       const size_t want = std::min({cnt, fill, (size_t)std::min(std::max(hw, 1), 8)});
       pool.reserve(want);   // (so that nothing but a thread's start can throw below)
@@ -1865,17 +2009,19 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
   std::vector<int> lows{tl.c};
   if (tl.pick && n >= 24)
     for (int c : {3, 4, 5, 6, 7})
-      if (c != tl.c && c <= tl.M - 6 && (n > 24 || c == 4 || c == 6)) lows.push_back(c);
+      if (c != tl.c && c <= tl.M - 6) lows.push_back(c);
   for (int c : lows) {
     cand.push_back({c, 1e300, false});
     if (allow_remap) cand.push_back({c, 1e300, true});
   }
   run(0);
-  // The caps are tried for states whose sweeps are worth the search, with the
-  // three numbers of low qubits that did best without (at 24, where the whole
-  // search would lengthen a short circuit's first pass, with the best, of 4, 6
-  // and the default's: four layers of a 12-qubit density matrix 3.83 ms before
-  // there was a search, 4.60 with all of it, 3.94 so).
+  // The caps are tried for states whose sweeps are worth the search, more of
+  // them the larger the state, with the numbers of low qubits that did best
+  // without: three of them from 25 qubits on (80 plans of layered, HEA, QFT and
+  // mixed circuits of 25 to 30 qubits: with two up to 14% slower in the model,
+  // with one 33%), one at 24, where 16 such plans are the same with more and the
+  // search has to stay short beside a pass (three layers of a 12-qubit density
+  // matrix on a new handle: 2.16 ms, as before low qubits were searched).
   if (n >= 24) {
     const size_t from = cand.size();
     const int budget = std::min(ncap, 4 << std::min(n - 24, 3));   // 4 at 24 qubits, 32 from 27

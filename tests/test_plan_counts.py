@@ -30,3 +30,25 @@ def test_blocks_of_gates_that_are_written_as_others():
     # which is no part of its register group
     assert sv.plan_stats(12, [I.Op("rx", (q,), params=(q,)) for q in (1, 4, 9)]) == (1, 1)
     assert sv.plan_stats(12, [I.Op("dexc", (1, 4, 9, 11), params=(0,))])[1] > 1
+
+
+# The planner counts what every qubit would add to a tile or a group in one pass
+# over the pending gates.  These plans are those of a search that counts for one
+# qubit at a time: default tiling, two that are set, and from |0..0>.
+PLANS = [
+    (14, "layered", 8, [(3, 45), (3, 47), (3, 31), (3, 45)]),
+    (23, "hea", 6, [(4, 60), (4, 60), (6, 39), (4, 60)]),
+    (24, "layered", 20, [(17, 206), (20, 191), (23, 137), (17, 206)]),
+    (26, "mixed", 150, [(19, 112), (19, 112), (25, 76), (19, 112)]),
+    (27, "qft", 0, [(10, 177), (10, 177), (13, 72), (10, 179)]),
+    (30, "layered", 20, [(26, 236), (26, 236), (27, 153), (22, 245)]),
+]
+
+
+@pytest.mark.parametrize("n,kind,arg,counts", PLANS, ids=[f"{p[1]}{p[0]}" for p in PLANS])
+def test_plans_are_those_of_the_search_qubit_by_qubit(n, kind, arg, counts):
+    from paper_2608_09733_amd import sv
+    ops = (I.layered_structure(n, arg) if kind == "layered" else I.hea_structure(n, arg) if kind == "hea"
+           else I.qft(n).ops if kind == "qft" else I.random_circuit(n, arg, seed=4).ops)
+    assert [sv.plan_stats(n, ops), sv.plan_stats(n, ops, -1, 13, 5, 3), sv.plan_stats(n, ops, -1, 11, 3, 5),
+            sv.plan_stats(n, ops, from_zero=True)] == counts
