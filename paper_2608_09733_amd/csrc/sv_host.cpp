@@ -1854,15 +1854,18 @@ static void collect_user_mats(Plan &P, const sv_op *ops, int n_ops) {
   for (int v : P.mat_dim) P.nstatic += v;
 }
 
-// Modeled time of a tile-sweep plan, in ms per 2^28 amplitudes, fitted to 700
-// sweeps of layered and HEA plans of 26 to 30 qubits in the default tilings (6%
-// rms).  A sweep overlaps its traffic and its stages in part (a 2.4-norm of
-// the two).  The traffic depends on the rows that a tile takes, 2^e consecutive
-// amplitudes of a plane (e = the low bits and the tile's high bits that follow
-// them without a gap): rows of 8 amplitudes cost half as much again as 64; and
-// on how far apart they lie, by the number of high bits that reach past the
-// pages the address translation holds.  A stage costs a share for its passage
-// through LDS, one for each of its tables, and a dense one 1.3 times as much.
+// Modeled time of a tile-sweep plan, in ms per 2^28 amplitudes, fitted to sweeps
+// in the default tilings: FP64 700 of layered and HEA plans of 26 to 30 qubits
+// (6% rms), FP32 400 of layered, HEA and QFT plans of 25 to 29 (5%).  A sweep
+// overlaps its traffic and its stages in part (a 2.4-norm of the two).  The
+// traffic depends on the rows that a tile takes, 2^e consecutive amplitudes of a
+// plane (e = the low bits and the tile's high bits that follow them without a
+// gap): rows of 8 amplitudes cost half as much again as 64; and on how far apart
+// they lie, by the number of high bits that reach past the pages the address
+// translation holds.  A stage costs a share for its passage through LDS, one for
+// each of its tables, in FP32, whose tables are multiplied in FP64, one for each
+// rotation, and a dense one 0.234 ms.  FP32 sweeps also have a fixed part (at 24
+// qubits 0.1 to 0.4 ms of these units).
 // From |0..0> (Tiling::zero) a sweep touches only the tiles inside the qubits
 // that the sweeps before it touched, and the first only writes.
 // A sweep with micro-op stages runs in another kernel, over every tile, and is
@@ -1884,9 +1887,12 @@ static double plan_model(const std::vector<GateRec> &recs, const std::vector<Swe
   static const MicroCost ops4 = {1.71, 0.43, 0.08, 1.04, 0.08, 0.08, 0.41, 0.63, 0.22};
   const MicroCost &mc = dbl ? ops8[std::min(std::max(tl.R, 3), 5) - 3] : ops4;
   static const double io8[4] = {2.33, 1.74, 1.64, 1.62}, far8[4] = {0.46, 0.33, 0.16, 0.13};
-  static const double io4[4] = {1.59, 0.93, 0.93, 0.80}, far4[4] = {0.07, 0.058, 0.017, 0.01};
-  const double w = dbl ? (tl.R <= 3 ? 1.0 : tl.R == 4 ? 1.2 : 1.6) : (tl.R <= 4 ? 1.0 : 1.2);
-  const double lds = (dbl ? 0.18 : 0.133) * w, tab = (dbl ? 0.035 : 0.03) * w;
+  static const double io4[4] = {1.44, 1.05, 0.85, 0.79}, far4[4] = {0.098, 0.030, 0.021, 0.004};
+  const double w = tl.R <= 3 ? 1.0 : tl.R == 4 ? 1.2 : 1.6;   // FP64, against 3-qubit groups
+  const double lds = dbl ? 0.18 * w : 0.087;
+  const double tab = dbl ? 0.035 * w : tl.R <= 4 ? 0.058 : 0.085;
+  const double rot = dbl ? 0.0 : tl.R <= 4 ? 0.016 : 0.022;
+  const double fix = dbl ? 0.0 : std::ldexp(0.007, 28 - n), fix_stage = dbl ? 0.0 : std::ldexp(0.0012, 28 - n);
   const int far_bit = dbl ? 23 : 18, far_free = dbl ? 4 : 2;
   double t = 0.0;
   uint64_t support = tl.zero ? 0 : ~0ull;
@@ -1917,10 +1923,12 @@ static double plan_model(const std::vector<GateRec> &recs, const std::vector<Swe
     } else {
       double st = 0.0;
       for (const StageP &g : sw.stages)
-        st += g.kron ? lds + tab * ((g.dbefore.empty() ? 0 : 1) + (g.rops.empty() && g.dafter.empty() ? 0 : 1))
-                     : 1.3 * lds;
+        st += g.kron ? lds + tab * ((g.dbefore.empty() ? 0 : 1) + (g.rops.empty() && g.dafter.empty() ? 0 : 1)) +
+                           rot * (double)g.rops.size()
+                     : 0.234;
       const int zero = std::max(0, n - popc(support | tile));
-      t += std::ldexp(std::pow(std::pow(io, 2.4) + std::pow(st, 2.4), 1 / 2.4), -zero);
+      t += std::ldexp(std::pow(std::pow(io, 2.4) + std::pow(st, 2.4), 1 / 2.4), -zero) + fix +
+           fix_stage * (double)sw.stages.size();
     }
     support |= tile;
   }
@@ -2016,17 +2024,19 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
   }
   run(0);
   // The caps are tried for states whose sweeps are worth the search, more of
-  // them the larger the state, with the numbers of low qubits that did best
-  // without: three of them from 25 qubits on (80 plans of layered, HEA, QFT and
-  // mixed circuits of 25 to 30 qubits: with two up to 14% slower in the model,
-  // with one 33%), one at 24, where 16 such plans are the same with more and the
-  // search has to stay short beside a pass (three layers of a 12-qubit density
-  // matrix on a new handle: 2.16 ms, as before low qubits were searched).
+  // them the larger the state; from 25 qubits on with every number of low qubits
+  // (374 plans of layered, HEA, QFT and mixed circuits of 25 to 30 qubits, both
+  // precisions: with the three that did best without caps up to 19% slower in the
+  // model, 4 layers at 29 qubits in complex64 7.0 ms instead of 5.9), at 24 with
+  // the one that did best: 16 such plans are the same with more, and the search
+  // has to stay short beside a pass (three layers of a 12-qubit density matrix on
+  // a new handle: 2.16 ms, as before low qubits were searched).
   if (n >= 24) {
     const size_t from = cand.size();
     const int budget = std::min(ncap, 4 << std::min(n - 24, 3));   // 4 at 24 qubits, 32 from 27
-    std::stable_sort(lows.begin(), lows.end(), [&](int a, int b) { return low_best[a] < low_best[b]; });
-    lows.resize(std::min(lows.size(), (size_t)(n > 24 ? 3 : 1)));
+    if (n == 24) lows = {*std::min_element(lows.begin(), lows.end(), [&](int a, int b) {
+      return low_best[a] < low_best[b];
+    })};
     for (int c : lows)
       for (int k = 0; k < budget; k++) cand.push_back({c, caps[k], allow_remap});
     run(from);
@@ -2046,9 +2056,12 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
 // FP32 circuits whose stages are all Kronecker stages take 4-qubit groups: 16
 // wavefronts a CU instead of 8 (22 qubits, 20 HEA layers: 0.92 -> 0.71 ms).  The
 // micro-op kernel spills less in 5-qubit ones.  Up to 21 qubits they take 13-bit
-// tiles, two a CU, instead of 14-bit ones, for the same reason as FP64 (before
-// the tables were kept in FP64, 20 layers, us: 12 qubits HEA 192, 161; 16 layered
-// 303, 223; 20 layered 390, 307; 21 HEA 531, 489; 22 HEA 547, 604).
+// tiles, two a CU, instead of 14-bit ones, for the same reason as FP64 (20
+// layers, us: 14 qubits layered 253, 283; 16 layered 285, 372; 18 layered 336,
+// 415; 20 layered 400, 480; 20 HEA 558, 617; 21 layered 564, 588; 21 HEA 689, 685;
+// 22 layered 621, 664; 22 HEA 778, 710), with 3 low qubits up to 20 (with 4: 18
+// layered 328, 20 layered 386, 20 HEA 604) and 4 at 21 (with 3: layered 612, HEA
+// 691).
 static void pick_kernel(const std::vector<GateRec> &recs, int n, bool dbl, Tiling &tl) {
   if (!tl.pick) return;
   if (dbl) {
