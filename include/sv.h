@@ -431,9 +431,9 @@ sv_status sv_serve_free(sv_serve *s);
  * sv_apply_layer makes of this circuit on an FP64 handle with this fuse_width
  * and tiling (0 = the default; see sv_set_tiling), without the pass that a
  * remaining |0..0> may take (host-only; for tests and tuning).  fuse_width 0: a
- * pass per gate.  From 26 qubits on a circuit has two plans: this is that of a
+ * pass per gate.  From 25 qubits on a circuit has two plans: this is that of a
  * state other than |0..0>, sv_plan_stats_zero that of a handle just reset.
- * Below 26 qubits the two are one.  Errors as for sv_apply_layer's op checks. */
+ * Below 25 qubits the two are one.  Errors as for sv_apply_layer's op checks. */
 sv_status sv_plan_stats(int32_t n_qubits, const sv_op *ops, int32_t n_ops, int32_t fuse_width,
                         int32_t tile_bits, int32_t low_bits, int32_t group_bits,
                         int32_t *n_sweeps, int32_t *n_blocks);

@@ -2537,12 +2537,12 @@ static sv_status layer_tiling(int n, bool dbl, const sv_op *ops, int n_ops, int 
   return widen_groups(dbl, need, tl);
 }
 
-// Whether a call's plan is modeled from |0..0>: by the state that is there
-// from 26 qubits on (1 GiB; 30 qubits, 10 HEA layers: 82 ms from |0..0> with its
-// plan, 96 with the other; from any state 155 and 135).  Below, both kinds of
-// state take the plan from |0..0>, so that an uploaded |0..0> gives the same
-// bits (24 qubits: within 3% of each other from |0..0>).
-static constexpr int kPlanByState = 26;
+// Whether a call's plan is modeled from |0..0>: by the state that is there from
+// 25 qubits on (30 qubits, 10 HEA layers: 82 ms from |0..0> with its plan, 96 with
+// the other; from any state 155 and 135; 25 qubits, 6 layers, from any state 2.61
+// and 2.31).  Below, both kinds of state take the plan from |0..0>, so that an
+// uploaded |0..0> gives the same bits (24 qubits: within 3% of each other).
+static constexpr int kPlanByState = 25;
 static bool plan_from_zero(const sv_state *st) { return st->n < kPlanByState || st->pending_zero; }
 
 static sv_status apply_layer(sv_state *st, const sv_op *ops, int32_t n_ops, const double *params,

@@ -447,7 +447,7 @@ def adjoint_plan_stats(n: int, ops, n_params: int, tile_bits: int = 0, low_bits:
 def plan_stats(n: int, ops, fuse: int = SV_FUSE_AUTO, tile_bits: int = 0, low_bits: int = 0,
                group_bits: int = 0, from_zero: bool = False) -> Tuple[int, int]:
     """(sweeps, register blocks) of the plan that apply() makes of these ops;
-    from_zero: on a state just reset (from 26 qubits on that plan is another)."""
+    from_zero: on a state just reset (from 25 qubits on that plan is another)."""
     oa = OpArray(ops)
     s = C.c_int32(0)
     b = C.c_int32(0)
