@@ -75,7 +75,7 @@ __device__ void pauli_tiles(const SVI_CONST PauliPassArgs &p, int64_t t0, int64_
     const uint64_t base = tile_base(tile, c, L.hb, nh);
     for (int i = tid; i < nel; i += NT) {
       const uint64_t g = base + spread_row(i >> c, L.hb, nh) + (uint64_t)(i & ((1 << c) - 1));
-      L.tile[swz<T>(i)] = C2{state_load<true>(pre + g), state_load<true>(pim + g)};
+      L.tile[swz<T>(i)] = C2{state_load(pre + g), state_load(pim + g)};
     }
     __syncthreads();
     for (int t = 0; t < nterm; t++) {
@@ -157,7 +157,7 @@ __global__ void __launch_bounds__(1 << (M - R)) k_batch(BatchKernelArgs b) {
     __syncthreads();
     // (state accesses are coherent across XCDs: no cache maintenance here)
     if (un.kind == UK_SWEEP)
-      sweep_tiles<T, M, R, KO, true>(cptr(b.sweeps)[un.arg], un.t0, un.t1, L.tile);
+      sweep_tiles<T, M, R, KO>(cptr(b.sweeps)[un.arg], un.t0, un.t1, L.tile);
     else
       pauli_tiles<T, M, R>(cptr(b.passes)[un.arg], un.t0, un.t1, b.part + un.part, L);
     // this wave's state stores are in memory before the count

@@ -57,15 +57,6 @@ __device__ __forceinline__ uint64_t insert_zeros64(uint64_t x, const int32_t *po
   return x;
 }
 
-__device__ __forceinline__ int insert_zeros32c(int x, const SVI_CONST int32_t *pos, int np) {
-  for (int k = 0; k < np; k++) {
-    const int p = pos[k];
-    const int lo = x & ((1 << p) - 1);
-    x = ((x >> p) << (p + 1)) | lo;
-  }
-  return x;
-}
-
 // Micro-op o, read through the constant address space (uniform index:
 // scalar loads, not vector loads whose waits would also wait for other
 // memory traffic in flight).
@@ -125,15 +116,6 @@ __device__ __forceinline__ int warm_sweep(const Args &a) {
   lines(a.stages, (int64_t)a.stage_begin * sizeof(StageDesc), (int64_t)a.stage_end * sizeof(StageDesc));
   lines(a.coef, (int64_t)a.coef_begin * 8, (int64_t)a.coef_end * 8);
   lines(a.ops, (int64_t)a.op_begin * sizeof(MicroOp), (int64_t)a.op_end * sizeof(MicroOp));
-  return x;
-}
-
-__device__ __forceinline__ int insert_zeros32(int x, const int32_t *pos, int np) {
-  for (int k = 0; k < np; k++) {
-    const int p = pos[k];
-    const int lo = x & ((1 << p) - 1);
-    x = ((x >> p) << (p + 1)) | lo;
-  }
   return x;
 }
 
@@ -1300,22 +1282,20 @@ __global__ void __launch_bounds__(1 << (M - R)) k_sweep_kron(SweepArgs a) {
 
 // ------------------------------------------------ tile sweep, one workgroup
 // State accesses of kernels whose workgroups hand a state on to each other
-// within one launch (CO): relaxed agent-scope accesses, which go past the L1
+// within one launch: relaxed agent-scope accesses, which go past the L1
 // and the XCD's L2 to memory that every XCD sees.  A workgroup publishes its
 // stores by waiting for them (stores_done) and then counting up; a reader
 // needs no more than to see the count.  (Ordinary accesses with agent-scope
 // fences write back and invalidate the whole L2 at every hand-over: the
 // 96-circuit batch took 13.1 ms that way.)
-template <bool CO, typename T>
+template <typename T>
 __device__ __forceinline__ T state_load(const T *p) {
-  if constexpr (CO) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  else return *p;
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <bool CO, typename T>
+template <typename T>
 __device__ __forceinline__ void state_store(T *p, T v) {
-  if constexpr (CO) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  else *p = v;
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Every store of this wave has reached memory.
@@ -1340,58 +1320,58 @@ __device__ __forceinline__ void tile_stages(const SVI_CONST SweepArgs &a,
   char *const lb = (char *)lt;
   // waves whose threads hold no part of a small state (m < M) have no group
   const bool on = wave * 64 < (1 << (mm - R));
-      for (int st = st_begin; st < st_end; st++) {
-        const SVI_CONST StageDesc &sd = stages[st];
-        const int gbs =
-            (swz<T>(lane_base(tid & 63, sd)) ^ swz<T>(wave_base<M, R>(wave, sd))) * (int)sizeof(C2);
-        // a full Kronecker stage (every group bit rotated, then D_after) runs as
-        // its own straight-line body, loads to stores; the general body branches
-        auto body = [&](auto full_stage) {
-          T re[G], im[G];
-  #pragma unroll
-          for (int j = 0; j < G; j++) {
-            const C2 v = *(const C2 *)(lb + (gbs ^ sd.off[j]));
-            re[j] = v.x;
-            im[j] = v.y;
-          }
-          if constexpr (decltype(full_stage)::value) {
-            kron_rot_all<T, R>(re, im, cptr(coef) + sd.kcoef);
-            mo_diagt<T, R>(re, im, cptr(coef) + sd.kcoef + 4 * R + 2 * G);
-          } else if (KO || sd.kind == ST_KRON) {
-            kron_stage<T, R>(re, im, cptr(coef) + sd.kcoef, sd.rmask, sd.dflags);
-          } else {
-            for (int o = sd.op_begin; o < sd.op_end; o++) {
-              const MicroOp op = op_at(ops, o);
-              apply_op<T, R>(op, re, im, coef);
-            }
-          }
-          if (sd.dflags & SD_XCHG) lds_barrier();
-  #pragma unroll
-          for (int j = 0; j < G; j++) *(C2 *)(lb + (gbs ^ sd.off[G + j])) = C2{re[j], im[j]};
-        };
-        if (!on) {
-          if (sd.dflags & SD_XCHG) lds_barrier();
-        } else if (sd.kind == ST_KRON && sd.rmask == (1u << R) - 1 && (sd.dflags & 7) == 2) {
-          body(std::true_type{});
-        } else {
-          body(std::false_type{});
-        }
-        if (sd.dflags & SD_WLOCAL) {
-          // the next stage reads only slots this wave wrote
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-          __builtin_amdgcn_wave_barrier();
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-        } else {
-          lds_barrier();
+  for (int st = st_begin; st < st_end; st++) {
+    const SVI_CONST StageDesc &sd = stages[st];
+    const int gbs =
+        (swz<T>(lane_base(tid & 63, sd)) ^ swz<T>(wave_base<M, R>(wave, sd))) * (int)sizeof(C2);
+    // a full Kronecker stage (every group bit rotated, then D_after) runs as
+    // its own straight-line body, loads to stores; the general body branches
+    auto body = [&](auto full_stage) {
+      T re[G], im[G];
+#pragma unroll
+      for (int j = 0; j < G; j++) {
+        const C2 v = *(const C2 *)(lb + (gbs ^ sd.off[j]));
+        re[j] = v.x;
+        im[j] = v.y;
+      }
+      if constexpr (decltype(full_stage)::value) {
+        kron_rot_all<T, R>(re, im, cptr(coef) + sd.kcoef);
+        mo_diagt<T, R>(re, im, cptr(coef) + sd.kcoef + 4 * R + 2 * G);
+      } else if (KO || sd.kind == ST_KRON) {
+        kron_stage<T, R>(re, im, cptr(coef) + sd.kcoef, sd.rmask, sd.dflags);
+      } else {
+        for (int o = sd.op_begin; o < sd.op_end; o++) {
+          const MicroOp op = op_at(ops, o);
+          apply_op<T, R>(op, re, im, coef);
         }
       }
+      if (sd.dflags & SD_XCHG) lds_barrier();
+#pragma unroll
+      for (int j = 0; j < G; j++) *(C2 *)(lb + (gbs ^ sd.off[G + j])) = C2{re[j], im[j]};
+    };
+    if (!on) {
+      if (sd.dflags & SD_XCHG) lds_barrier();
+    } else if (sd.kind == ST_KRON && sd.rmask == (1u << R) - 1 && (sd.dflags & 7) == 2) {
+      body(std::true_type{});
+    } else {
+      body(std::false_type{});
+    }
+    if (sd.dflags & SD_WLOCAL) {
+      // the next stage reads only slots this wave wrote
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    } else {
+      lds_barrier();
+    }
+  }
 }
 
 // Tiles [t0, t1) of one sweep of one state, run by one workgroup of 2^(M-R)
 // threads through the LDS tile `lt` (2^M amplitudes).  No qubit remapping
 // on the way out (SW_OPERM is not taken).  KO: every stage is a Kronecker
 // stage (no micro-op interpreter in the caller's kernel).
-template <typename T, int M, int R, bool KO, bool CO>
+template <typename T, int M, int R, bool KO>
 __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1,
                             typename C2T<T>::type *lt) {
   constexpr int NT = 1 << (M - R);
@@ -1447,8 +1427,8 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
 #pragma unroll
       for (int k = 0; k < G; k++)
         if (tid + k * NT < ntile_el) {
-          state_store<CO>(tr + koff(k) + toff, (T)0);
-          state_store<CO>(ti + koff(k) + toff, (T)0);
+          state_store(tr + koff(k) + toff, (T)0);
+          state_store(ti + koff(k) + toff, (T)0);
         }
       continue;
     }
@@ -1467,8 +1447,8 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
 #pragma unroll
       for (int k = 0; k < G; k++)
         if (tid + k * NT < ntile_el) {
-          vr[k] = state_load<CO>(tr + koff(k) + toff);
-          vi[k] = state_load<CO>(ti + koff(k) + toff);
+          vr[k] = state_load(tr + koff(k) + toff);
+          vi[k] = state_load(ti + koff(k) + toff);
         }
 #pragma unroll
       for (int k = 0; k < G; k++)
@@ -1483,8 +1463,8 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
     for (int k = 0; k < G; k++)
       if (tid + k * NT < ntile_el) {
         const C2 p = lt[tsl ^ swz<T>(k * NT)];
-        state_store<CO>(tr + koff(k) + toff, p.x);
-        state_store<CO>(ti + koff(k) + toff, p.y);
+        state_store(tr + koff(k) + toff, p.x);
+        state_store(ti + koff(k) + toff, p.y);
       }
     __syncthreads();
   }

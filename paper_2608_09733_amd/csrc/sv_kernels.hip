@@ -2214,8 +2214,8 @@ struct ServeTile {
 #pragma unroll
     for (int k = 0; k < G; k++) {
       const uint32_t ko = base + off_of((uint32_t)(k * NT));
-      vr[k] = state_load<true>(pr + ko + toff);
-      vi[k] = state_load<true>(pi + ko + toff);
+      vr[k] = state_load(pr + ko + toff);
+      vi[k] = state_load(pi + ko + toff);
     }
 #pragma unroll
     for (int k = 0; k < G; k++) t[swz<T>((int)threadIdx.x + k * NT)] = {vr[k], vi[k]};
@@ -2226,12 +2226,12 @@ struct ServeTile {
     for (int k = 0; k < G; k++) {
       const uint32_t ko = base + off_of((uint32_t)(k * NT));
       const auto v = t[swz<T>((int)threadIdx.x + k * NT)];
-      state_store<true>(pr + ko + toff, v.x);
-      state_store<true>(pi + ko + toff, v.y);
+      state_store(pr + ko + toff, v.x);
+      state_store(pi + ko + toff, v.y);
     }
   }
   __device__ __forceinline__ void zero(T *p, int NT, int G) const {
-    for (int k = 0; k < G; k++) state_store<true>(p + base + off_of((uint32_t)(k * NT)) + toff, (T)0);
+    for (int k = 0; k < G; k++) state_store(p + base + off_of((uint32_t)(k * NT)) + toff, (T)0);
   }
 };
 
@@ -2271,7 +2271,7 @@ __device__ __forceinline__ void serve_backward(const SVI_CONST SweepArgs &a,
   for (int sl = tid; sl < a.n_gslots; sl += NT) {
     double v = 0.0;
     for (int w = 0; w < NWAVE; w++) v += wacc[w][sl];
-    state_store<true>(slots + a.gslot_begin + sl, v);
+    state_store(slots + a.gslot_begin + sl, v);
   }
   __syncthreads();
 }
@@ -2375,8 +2375,8 @@ __global__ void __launch_bounds__(1 << (M - R)) k_serve(ServeArgs sa) {
               sr[k] = v.x;
               si[k] = v.y;
             } else {
-              sr[k] = state_load<true>(pr + b0 + i);
-              si[k] = state_load<true>(pim + b0 + i);
+              sr[k] = state_load(pr + b0 + i);
+              si[k] = state_load(pim + b0 + i);
             }
           }
         }
@@ -2403,8 +2403,8 @@ __global__ void __launch_bounds__(1 << (M - R)) k_serve(ServeArgs sa) {
               ur = (double)v.x;
               ui = (double)v.y;
             } else {
-              ur = (double)state_load<true>(pr + src);
-              ui = (double)state_load<true>(pim + src);
+              ur = (double)state_load(pr + src);
+              ui = (double)state_load(pim + src);
             }
             const double c = __builtin_popcount(src & z) & 1 ? -pt.c : pt.c;
             switch (ny) {   // i^{nY}
@@ -2424,8 +2424,8 @@ __global__ void __launch_bounds__(1 << (M - R)) k_serve(ServeArgs sa) {
           if (whole) {
             ll[swz<T>(i)] = C2{(T)ar[k], (T)ai[k]};
           } else {
-            state_store<true>((T *)q.lre + b0 + i, (T)ar[k]);
-            state_store<true>((T *)q.lim + b0 + i, (T)ai[k]);
+            state_store((T *)q.lre + b0 + i, (T)ar[k]);
+            state_store((T *)q.lim + b0 + i, (T)ai[k]);
           }
         }
         e = wave_sum(e);
@@ -2434,7 +2434,7 @@ __global__ void __launch_bounds__(1 << (M - R)) k_serve(ServeArgs sa) {
         if (tid == 0) {
           e = 0.0;
           for (int w = 0; w < NWAVE; w++) e += wred[w];
-          state_store<true>(q.epart + (whole ? 0 : un.tile), e);
+          state_store(q.epart + (whole ? 0 : un.tile), e);
         }
         __syncthreads();
       } else if (ph <= nf + nb) {
@@ -2470,12 +2470,12 @@ __global__ void __launch_bounds__(1 << (M - R)) k_serve(ServeArgs sa) {
           double g = 0.0;
           for (int k = q.rowptr[p]; k < q.rowptr[p + 1]; k++)
             for (int t = 0; t < q.n_tiles; t++)
-              g += state_load<true>(q.slots + (int64_t)t * q.n_gslots + q.gslots[k]);
+              g += state_load(q.slots + (int64_t)t * q.n_gslots + q.gslots[k]);
           q.out[1 + p] = bad ? nan : g;
         }
         if (tid == 0) {
           double e = 0.0;
-          for (int t = 0; t < q.n_tiles; t++) e += state_load<true>(q.epart + t);
+          for (int t = 0; t < q.n_tiles; t++) e += state_load(q.epart + t);
           q.out[0] = bad ? nan : e;
         }
         __syncthreads();
