@@ -21,6 +21,7 @@
 #include "sv.h"
 #include "sv_internal.h"
 #include "sv_launch.h"
+#include "sv_variants.h"
 
 // ------------------------------------------------------------------ errors
 
@@ -1710,10 +1711,10 @@ extern "C" sv_status sv_set_stream(sv_state *st, void *stream) {
   return SV_OK;
 }
 
-// Tilings a caller may set: the compiled ones.  FP32 groups of 4 qubits are no
-// setting: the planner takes them for circuits of Kronecker stages (pick_kernel).
+// Tilings a caller may set: those compiled for every circuit.  (The planner takes
+// the others for circuits of Kronecker stages: pick_kernel.)
 static bool settable(sv_dtype dt, int M, int R) {
-  return svk_has_sweep(dt == SV_C128, M, R, 1) && (dt == SV_C128 || R != 4);
+  return svk_has_sweep(dt == SV_C128, M, R, 1) && svi_has_ops(dt == SV_C128, R, 1);
 }
 
 extern "C" sv_status sv_set_tiling(sv_state *st, int32_t tile_bits, int32_t low_bits,

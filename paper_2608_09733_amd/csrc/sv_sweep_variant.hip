@@ -11,20 +11,35 @@
 #error "compile with -DSVI_VT= -DSVI_VM= -DSVI_VR= -DSVI_VNS="
 #endif
 
+namespace {
+template <typename T, int M, int R, int NS>
+hipError_t launch_ops(const SweepArgs &a, int grid, hipStream_t s) {
+  if constexpr (!svi_has_ops(sizeof(T) == 8, R, NS)) {
+    return hipErrorInvalidValue;
+  } else {
+    hipLaunchKernelGGL((svk::k_sweep<T, M, R, NS>), dim3(grid), dim3(1 << (M - R)), 0, s, a);
+    return hipGetLastError();
+  }
+}
+
+template <typename T, int M, int R, int NS>
+int occupancy_ops() {
+  int nb = 0;
+  if constexpr (svi_has_ops(sizeof(T) == 8, R, NS))
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, svk::k_sweep<T, M, R, NS>, 1 << (M - R), 0) !=
+        hipSuccess)
+      return 1;
+  return nb > 0 ? nb : 1;
+}
+}  // namespace
+
 hipError_t SVI_VNAME(launch, SVI_VT, SVI_VM, SVI_VR, SVI_VNS)(const SweepArgs &a, int grid,
                                                               hipStream_t s) {
-  hipLaunchKernelGGL((svk::k_sweep<SVI_VT, SVI_VM, SVI_VR, SVI_VNS>), dim3(grid),
-                     dim3(1 << (SVI_VM - SVI_VR)), 0, s, a);
-  return hipGetLastError();
+  return launch_ops<SVI_VT, SVI_VM, SVI_VR, SVI_VNS>(a, grid, s);
 }
 
 int SVI_VNAME(occ, SVI_VT, SVI_VM, SVI_VR, SVI_VNS)() {
-  int nb = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb, svk::k_sweep<SVI_VT, SVI_VM, SVI_VR, SVI_VNS>, 1 << (SVI_VM - SVI_VR), 0) !=
-      hipSuccess)
-    return 1;
-  return nb > 0 ? nb : 1;
+  return occupancy_ops<SVI_VT, SVI_VM, SVI_VR, SVI_VNS>();
 }
 
 #if SVI_VNS != 1

@@ -24,6 +24,11 @@
   X(float, 13, 4, 2)
 
 #define SVI_NVARIANTS 18
+
+// Whether a tiling has the micro-op kernels (else the lean ones alone): the
+// one-state FP32 tilings of 4-qubit groups run circuits of Kronecker stages only.
+constexpr bool svi_has_ops(bool dbl, int R, int NS) { return dbl || R != 4 || NS != 1; }
+
 #define SVI_VCAT(a, b, c, d, e, f) svk_##a##_##b##_##c##_##d##_##e##f
 #define SVI_VNAME(what, T, M, R, NS) SVI_VCAT(what, T, M, R, NS, _v)
 
