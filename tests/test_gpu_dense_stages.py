@@ -79,3 +79,31 @@ def test_amplitudes_that_are_not_finite_stay_in_their_pairs():
         reach |= {x ^ 0b10000010 for x in reach}
     rest = np.array(sorted(set(range(1 << n)) - reach))
     assert np.array_equal(got[rest], want[rest])
+
+
+# the controlled gate's control clear and set in the amplitude that is not finite
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("bad", [0b10110000000101, 0b10111000000101])
+def test_amplitudes_that_are_not_finite_spread_as_far_as_the_gates_reach(bad, value):
+    from paper_2608_09733_amd import sv
+    n = 14
+    rng = np.random.default_rng(3)
+    re, im = rng.normal(size=(2, 1 << n))
+    ops = [I.Op("unitary", (4,), matrix=_unitary(rng, 1)), I.Op("rxx", (1, 7), (9,), 1, (0,))]
+    st = sv.State(n)
+    st.set_planes(re, im)
+    st.apply(ops, np.array([0.4]))
+    want = st.to_numpy()
+    re[bad] = value
+    st.set_planes(re, im)
+    st.apply(ops, np.array([0.4]))
+    got = st.to_numpy()
+    st.close()
+    # the pair of qubit 4; RXX pairs 1 and 7 where qubit 9 is 1
+    reach = {bad, bad ^ (1 << 4)}
+    if bad >> 9 & 1:
+        reach |= {x ^ 0b10000010 for x in reach}
+    reached = np.array(sorted(reach))
+    rest = np.setdiff1d(np.arange(1 << n), reached)
+    assert np.array_equal(got[rest], want[rest])
+    assert not np.isfinite(got[reached]).any()
