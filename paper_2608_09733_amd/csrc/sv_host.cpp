@@ -2051,6 +2051,8 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
   if (best == 1e300) plan_auto(recs, n, tl, out, 1e300, true, false);
 }
 
+static constexpr int kSmallTiles = 22;   // largest FP64 states that take 12-bit tiles
+
 // Kernel of a default tiling's AUTO plan.
 // FP64 states of up to 22 qubits take 12-bit tiles with 3 low qubits: they have
 // no tiles to spare for the CUs, and of half the size a tile's loads, stages and
@@ -2058,7 +2060,12 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
 // and 12-bit ones, us: 12 qubits HEA 190, 155; 16 layered 264, 206; 18 layered
 // 300, 215; 21 layered 436, 383; 22 HEA 819, 765; 23 layered 1305, 1376).  13
 // qubits fit one tile of 13 bits: one sweep (HEA 200, 208).  11-bit tiles have
-// more sweeps (18 layered 253).
+// more sweeps (18 layered 253).  At 22, where a sweep's traffic begins to count, a
+// plan keeps the 13-bit tiles if 12-bit ones take more than 4/3 as many sweeps: 12
+// layered layers, 8 sweeps and 12, 466 us and 525; 10 layers, 6 and 9, 367 and 403;
+// up to 1.29 times as many the 12-bit tiles are within 5% or ahead, by up to 12%.
+// (75 circuits of each size from 14 qubits on; up to 21 none takes longer
+// than it did when all took 13-bit tiles.)
 // FP32 circuits whose stages are all Kronecker stages take 4-qubit groups: 16
 // wavefronts a CU instead of 8 (22 qubits, 20 HEA layers: 0.92 -> 0.71 ms).  The
 // micro-op kernel spills less in 5-qubit ones.  Up to 21 qubits they take 13-bit
@@ -2071,7 +2078,7 @@ static void plan_auto_best(const std::vector<GateRec> &recs, int n, bool dbl, Ti
 static void pick_kernel(const std::vector<GateRec> &recs, int n, bool dbl, Tiling &tl) {
   if (!tl.pick) return;
   if (dbl) {
-    if (n <= 22 && n != 13) {
+    if (n <= kSmallTiles && n != 13) {
       tl.M = 12;
       tl.c = 3;
     }
@@ -2185,8 +2192,19 @@ static sv_status plan_forward(int mode, int n, bool dbl, Tiling &tl, const sv_op
     recs.push_back(g);
   }
   if (mode < 0) {
+    const Tiling whole = tl;
     pick_kernel(recs, n, dbl, tl);
     plan_auto_best(recs, n, dbl, tl, sweeps, remap);
+    if (dbl && n == kSmallTiles && tl.M < whole.M) {
+      // (pick_kernel says why)
+      Tiling t = whole;
+      std::vector<SweepP> alt;
+      plan_auto_best(recs, n, dbl, t, alt, remap);
+      if (3 * sweeps.size() > 4 * alt.size()) {
+        sweeps.swap(alt);
+        tl = t;
+      }
+    }
   } else if (mode > 0) {
     plan_fused(recs, n, tl, mode, sweeps, true);
   }

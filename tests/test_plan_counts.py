@@ -61,3 +61,14 @@ def test_a_state_of_25_qubits_has_a_plan_of_its_own():
     for n, one in ((24, True), (25, False)):
         ops = I.layered_structure(n, 6)
         assert (sv.plan_stats(n, ops) == sv.plan_stats(n, ops, from_zero=True)) == one
+
+
+def test_22_qubits_keep_13_bit_tiles_where_12_bit_ones_take_many_more_sweeps():
+    # 10 and 12 layers took 403 and 525 us in 12-bit tiles, 367 and 466 in 13-bit
+    # ones; 8 layers are faster in 12-bit ones
+    from paper_2608_09733_amd import sv
+    for layers, tile, low in ((8, 12, 3), (10, 13, 5), (12, 13, 5)):
+        ops = I.layered_structure(22, layers)
+        small, whole = sv.plan_stats(22, ops, -1, 12, 3, 3), sv.plan_stats(22, ops, -1, 13, 5, 3)
+        assert (3 * small[0] > 4 * whole[0]) == (tile == 13)
+        assert sv.plan_stats(22, ops) == sv.plan_stats(22, ops, -1, tile, low, 3)
