@@ -1383,6 +1383,13 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
   const int ntile_el = 1 << m;
   const bool init0 = (a.flags & SW_INIT_ZERO) != 0;
   T *const pre = (T *)a.re, *const pim = (T *)a.im;
+  // Amplitudes of a thread in flight at a time.  The values and addresses of all G
+  // at once spilled beside the stages' registers (96 bytes a lane in FP64 with
+  // 3-qubit groups, 856 in the general kernel's 5-qubit ones; now 0 and 88): 96
+  // ragged circuits of 8 to 20 qubits 6.29 -> 4.93 ms, 16 of 16 qubits with gates of
+  // all kinds 586 -> 464 us (559 with cached 16-byte accesses; 8 at a time 6.28 and
+  // 462).  FP32 in 5-qubit groups, which never spilled here, is 1% slower with 4.
+  constexpr int LC = sizeof(T) == 8 || R == 3 ? 4 : 8;
 
   // Thread tid moves tile elements i = tid + k * NT, one amplitude per access
   // (consecutive lanes on consecutive addresses).  Offsets: a deposit of the
@@ -1443,16 +1450,20 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
         lt[swz<T>(i)] = C2{v, 0};
       }
     } else {
-      T vr[G], vi[G];
 #pragma unroll
-      for (int k = 0; k < G; k++)
-        if (tid + k * NT < ntile_el) {
-          vr[k] = state_load(tr + koff(k) + toff);
-          vi[k] = state_load(ti + koff(k) + toff);
-        }
+      for (int k0 = 0; k0 < G; k0 += LC) {
+        T vr[LC], vi[LC];
 #pragma unroll
-      for (int k = 0; k < G; k++)
-        if (tid + k * NT < ntile_el) lt[tsl ^ swz<T>(k * NT)] = C2{vr[k], vi[k]};
+        for (int k = 0; k < LC; k++)
+          if (tid + (k0 + k) * NT < ntile_el) {
+            vr[k] = state_load(tr + koff(k0 + k) + toff);
+            vi[k] = state_load(ti + koff(k0 + k) + toff);
+          }
+#pragma unroll
+        for (int k = 0; k < LC; k++)
+          if (tid + (k0 + k) * NT < ntile_el) lt[tsl ^ swz<T>((k0 + k) * NT)] = C2{vr[k], vi[k]};
+        asm volatile("" : "+v"(toff)::"memory");
+      }
     }
     __syncthreads();
 
@@ -1460,12 +1471,16 @@ __device__ void sweep_tiles(const SVI_CONST SweepArgs &a, int64_t t0, int64_t t1
 
     asm volatile("" : "+v"(toff));
 #pragma unroll
-    for (int k = 0; k < G; k++)
-      if (tid + k * NT < ntile_el) {
-        const C2 p = lt[tsl ^ swz<T>(k * NT)];
-        state_store(tr + koff(k) + toff, p.x);
-        state_store(ti + koff(k) + toff, p.y);
-      }
+    for (int k0 = 0; k0 < G; k0 += LC) {
+#pragma unroll
+      for (int k = k0; k < k0 + LC; k++)
+        if (tid + k * NT < ntile_el) {
+          const C2 p = lt[tsl ^ swz<T>(k * NT)];
+          state_store(tr + koff(k) + toff, p.x);
+          state_store(ti + koff(k) + toff, p.y);
+        }
+      asm volatile("" : "+v"(toff)::"memory");
+    }
     __syncthreads();
   }
 }
